@@ -93,7 +93,22 @@ __global__ __launch_bounds__(256) void k_bbox(const float* __restrict__ pts, int
     }
 }
 
-// Folds the nb partials of k_bbox into the control block (one workgroup).
+// The control block at the start of a build (one thread).
+__device__ __forceinline__ void init_ctrl(Ctrl* ctrl) {
+    for (int k = 0; k < 3; ++k) { ctrl->bb_min[k] = 0xFFFFFFFFu; ctrl->bb_max[k] = 0u; }
+    ctrl->nonfinite = 0; ctrl->root = kNone; ctrl->height = 0;
+    ctrl->ncomp_next = 0; ctrl->edge_count = 0; ctrl->error = 0;
+    ctrl->key_or = 0ull; ctrl->key_and = ~0ull;
+    ctrl->internal_tests = 0; ctrl->leaf_tests = 0; ctrl->dist_evals = 0; ctrl->touched = 0;
+    ctrl->long_ties = 0; ctrl->dup_codes = 0; ctrl->done = 0; ctrl->rounds_run = 0;
+}
+
+__global__ void k_init_ctrl(Ctrl* ctrl) {
+    if (threadIdx.x == 0) init_ctrl(ctrl);
+}
+
+// Starts the control block, with the box and the check of the nb partials of
+// k_bbox (one workgroup).
 __global__ __launch_bounds__(256) void k_bbox_final(const uint32_t* __restrict__ part, int nb, Ctrl* ctrl) {
     __shared__ uint32_t s[4][7];
     uint32_t v[7] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0u, 0u, 0u, 0u};
@@ -126,6 +141,7 @@ __global__ __launch_bounds__(256) void k_bbox_final(const uint32_t* __restrict__
             }
             v[6] |= s[u][6];
         }
+        init_ctrl(ctrl);
         for (int k = 0; k < 3; ++k) {
             ctrl->bb_min[k] = v[k];
             ctrl->bb_max[k] = v[3 + k];
@@ -140,17 +156,6 @@ hipError_t launch_bbox(const float* pts, int64_t n, uint32_t* part, Ctrl* ctrl, 
     k_bbox<DIM><<<nb, 256, 0, st>>>(pts, n, part);
     k_bbox_final<<<1, 256, 0, st>>>(part, nb, ctrl);
     return hipGetLastError();
-}
-
-__global__ void k_init_ctrl(Ctrl* ctrl) {
-    if (threadIdx.x == 0) {
-        for (int k = 0; k < 3; ++k) { ctrl->bb_min[k] = 0xFFFFFFFFu; ctrl->bb_max[k] = 0u; }
-        ctrl->nonfinite = 0; ctrl->root = kNone; ctrl->height = 0;
-        ctrl->ncomp_next = 0; ctrl->edge_count = 0; ctrl->error = 0;
-        ctrl->key_or = 0ull; ctrl->key_and = ~0ull;
-        ctrl->internal_tests = 0; ctrl->leaf_tests = 0; ctrl->dist_evals = 0; ctrl->touched = 0;
-        ctrl->long_ties = 0; ctrl->dup_codes = 0; ctrl->done = 0; ctrl->rounds_run = 0;
-    }
 }
 
 __device__ __forceinline__ uint64_t spread3(uint64_t x) {
@@ -238,19 +243,6 @@ __global__ __launch_bounds__(256) void k_morton(const float* __restrict__ pts, i
 // code width.  Ranks are monotone in the coordinates, so the Z-curve of the
 // ranks is still a spatial order, with resolution where the points are.
 
-// Sorted positions whose code equals the previous one (one atomic per block).
-__global__ __launch_bounds__(256) void k_count_dups(const uint64_t* __restrict__ codes, int64_t n, Ctrl* ctrl) {
-    __shared__ uint32_t s_cnt;
-    if (threadIdx.x == 0) s_cnt = 0;
-    __syncthreads();
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const bool dup = i > 0 && i < n && codes[i] == codes[i - 1];
-    const uint64_t b = __ballot(dup);
-    if (lane_id() == 0 && b) atomicAdd(&s_cnt, (uint32_t)__popcll(b));
-    __syncthreads();
-    if (threadIdx.x == 0 && s_cnt) atomicAdd(&ctrl->dup_codes, s_cnt);
-}
-
 // keys = order-preserving bits of coordinate `axis`, values = point index
 template <int DIM>
 __global__ __launch_bounds__(256) void k_axis_keys(const float* __restrict__ pts, int64_t n, int axis,
@@ -322,16 +314,21 @@ __device__ __forceinline__ int split_bit(const uint64_t* __restrict__ codes, int
 // between threads (agent-scope acquire/release would write back and
 // invalidate the per-XCD L2 caches at every step); every other store is read
 // by later kernels only.  The boxes are fitted afterwards (k_fit_tiles,
-// k_fit_span).  A node's leaf range, height and parent link go out together
+// k_fit_group).  A node's leaf range, height and parent link go out together
 // in one 16-byte NodeInfo once its parent is known (the fit, or
 // k_unpack_nodes, spreads them into their arrays): the stores of the climb
 // land at scattered nodes, and four separate stores per node each cost a
 // whole memory sector.  The child references are written with the boxes by
 // the fit (REFS: here as well, for the test hook that reads the hierarchy
-// without fitting it).
+// without fitting it).  It also counts the positions that repeat the
+// previous code (ctrl->dup_codes).
 struct alignas(16) NodeInfo {
     uint32_t lo, hi, link, height;
 };
+
+// Sorted positions that repeat the previous code, from which the tree is
+// rebuilt on rank-space codes.
+__host__ __device__ inline bool many_dups(uint32_t dups, int64_t n) { return (int64_t)dups * 64 > n; }
 
 template <int DIM, bool REFS>
 __global__ __launch_bounds__(256) void k_build(const uint64_t* __restrict__ codes,
@@ -339,6 +336,11 @@ __global__ __launch_bounds__(256) void k_build(const uint64_t* __restrict__ code
                                                uint32_t* __restrict__ leaf_parent, NodeInfo* __restrict__ info,
                                                uint64_t* exch, Ctrl* ctrl) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int dups = __syncthreads_count(i > 0 && i < n && codes[i] == codes[i - 1]);
+    // (past the threshold nobody needs the exact count, and thousands of
+    // additions to one address would take tens of microseconds)
+    if (threadIdx.x == 0 && dups && !many_dups(load_relaxed(&ctrl->dup_codes), n))
+        atomicAdd(&ctrl->dup_codes, (uint32_t)dups);
     if (i >= n) return;
     int64_t l = i, r = i;
     uint32_t h = 0;
@@ -409,33 +411,50 @@ __global__ __launch_bounds__(256) void k_unpack_nodes(const NodeInfo* __restrict
     height[k] = (uint8_t)x.height;
 }
 
-// Boxes, bottom-up.  One workgroup per tile of kFitTile consecutive leaves
-// fits every node whose leaf range lies inside its tile: each leaf's thread
+// Boxes, bottom-up, in levels of tiles.  The first level has one workgroup
+// per tile of kFitTile consecutive leaves, which fits every node whose leaf
+// range lies inside its tile: each leaf's thread
 // stores the leaf's box (its point) and reference into the parent's record
 // and climbs while the parent lies inside the tile; at each such node the
 // first child to arrive parks its box in LDS and stops, the second forms the
 // union, stores it with the node's reference into the node's parent's record
 // and climbs on.  Only LDS and one workgroup take part, so no thread waits
 // on another and no cross-XCD ordering is needed.  The same pass spreads the
-// tile's node records (range, parent link, height) into their arrays and
-// lists the tile's nodes whose range crosses a tile border; those (a few per
-// border and height) are fitted afterwards, one launch per height.
-constexpr int kFitTile = 512;  // 256 and 1024 measured slower (LDS per workgroup vs nodes across borders)
+// tile's node records (range, parent link) into their arrays and
+// lists the tile's nodes whose range crosses a tile border, which the next
+// levels fit (k_fit_group).  The fences order LDS accesses only: waiting
+// for the record stores at every step of a climb (__threadfence_block)
+// took 85 us instead of 70 us at 2M points.
+constexpr int kFitShift = 9;
+constexpr int kFitTile = 1 << kFitShift;  // 256 and 1024 measured slower (LDS per workgroup vs nodes across borders)
+
+// The children of node k, with the leaf ranges [lo, k] and [k + 1, hi], that
+// lie inside one tile of 2^shift leaves.
+__device__ __forceinline__ uint32_t fit_ready(uint32_t lo, uint32_t hi, uint32_t k, int shift) {
+    return (uint32_t)((uint64_t)lo >> shift == (uint64_t)k >> shift) +
+           (uint32_t)((uint64_t)(k + 1u) >> shift == (uint64_t)hi >> shift);
+}
+
+// Orders the LDS accesses of the workgroup's threads around it.  Unlike
+// __threadfence_block it does not wait for stores to memory, which nothing
+// in the launch reads back.
+__device__ __forceinline__ void lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup", "local");
+}
 
 template <int DIM>
 __global__ __launch_bounds__(256) void k_fit_tiles(const float* __restrict__ spts, const uint32_t* __restrict__ orig,
                                                    const uint32_t* __restrict__ leaf_parent,
                                                    const NodeInfo* __restrict__ info, int64_t n, Rec<DIM>* recs,
                                                    uint32_t* __restrict__ rlo, uint32_t* __restrict__ rhi,
-                                                   uint32_t* __restrict__ node_parent, uint8_t* __restrict__ height,
-                                                   uint2* __restrict__ span, uint32_t* __restrict__ span_count,
+                                                   uint32_t* __restrict__ node_parent, uint32_t* __restrict__ span,
+                                                   uint32_t* __restrict__ span_count, uint32_t* __restrict__ arrive,
                                                    Ctrl* ctrl) {
     if (ctrl->error) return;  // the build failed: its records are incomplete
     __shared__ uint32_t s_arrive[kFitTile];
     __shared__ float s_box[kFitTile][2][2 * DIM];  // per node of the tile and child side: lo, hi
     __shared__ uint32_t s_lo[kFitTile], s_hi[kFitTile], s_link[kFitTile];
-    __shared__ uint2 s_span[kFitTile];
-    __shared__ uint32_t s_nspan, s_base;
+    __shared__ uint32_t s_nspan;
     const int t = threadIdx.x;
     const int64_t t0 = (int64_t)blockIdx.x * kFitTile;
     const int64_t m = n - 1;
@@ -449,21 +468,16 @@ __global__ __launch_bounds__(256) void k_fit_tiles(const float* __restrict__ spt
         rlo[k] = v.lo;
         rhi[k] = v.hi;
         node_parent[k] = v.link;
-        height[k] = (uint8_t)v.height;
         s_lo[x] = v.lo;
         s_hi[x] = v.hi;
         s_link[x] = v.link;
-        if (v.lo / kFitTile != v.hi / kFitTile) s_span[atomicAdd(&s_nspan, 1u)] = make_uint2((uint32_t)k, v.height);
+        if (v.lo / kFitTile != v.hi / kFitTile) {
+            span[t0 + atomicAdd(&s_nspan, 1u)] = (uint32_t)k;  // the tile's segment has room for all of its nodes
+            arrive[k] = fit_ready(v.lo, v.hi, (uint32_t)k, kFitShift);
+        }
     }
     __syncthreads();
-    if (t == 0) s_base = s_nspan ? atomicAdd(span_count, s_nspan) : 0u;
-    __syncthreads();
-    // (the list has room for n - 1 entries, at most 129 per tile border of a
-    // valid tree)
-    for (uint32_t x = t; x < s_nspan; x += 256) {
-        if ((int64_t)s_base + x < m) span[s_base + x] = s_span[x];
-        else atomicOr(&ctrl->error, kErrStack);
-    }
+    if (t == 0) span_count[blockIdx.x] = s_nspan;
     const uint32_t lo_in = (uint32_t)t0, hi_in = (uint32_t)min<int64_t>(t0 + kFitTile - 1, n - 1);
     for (int x = t; x < kFitTile; x += 256) {
         const int64_t i = t0 + x;
@@ -489,9 +503,9 @@ __global__ __launch_bounds__(256) void k_fit_tiles(const float* __restrict__ spt
                 s_box[ps][side][k] = lo[k];
                 s_box[ps][side][DIM + k] = hi[k];
             }
-            __threadfence_block();
+            lds_fence();
             if (atomicAdd(&s_arrive[ps], 1u) == 0u) break;  // the sibling completes P
-            __threadfence_block();
+            lds_fence();
 #pragma unroll
             for (int k = 0; k < DIM; ++k) {
                 lo[k] = fminf(lo[k], s_box[ps][1 - side][k]);
@@ -504,30 +518,172 @@ __global__ __launch_bounds__(256) void k_fit_tiles(const float* __restrict__ spt
     }
 }
 
-// The listed nodes of height h (ranges across a tile border): box = union
-// of the two child boxes in the own record, stored with the node's
-// reference in the parent's record.  Their children are leaves and nodes
-// fitted by k_fit_tiles, or listed nodes of smaller height.
+// The next levels: one workgroup per kFitGroup tiles of the level below
+// (2^shift leaves each) fits the listed nodes whose leaf range lies inside
+// its own, larger tile, and lists the others for the level above.  The
+// nodes go to LDS (links resolved to slots through a hash table, the boxes
+// of children fitted by levels below loaded from the records), and the
+// climbs of k_fit_tiles run there.  A group of uniform points lists about
+// 11 nodes per tile of the first level and 15 per tile of the others; one
+// with more than kFitSlots nodes (points whose tree is a comb at most tile
+// borders) climbs through the records in memory instead (arrive[k] counts
+// the finished children of a listed node there), whose dependent loads and
+// stores cost 3 us a step.  The latency of loading a group bounds the
+// rest: two launches of 27 and 56 us at 2M points, three of 156, 71 and
+// 26 us at 37M.  One launch per height over all listed nodes took 39
+// launches and 116 us of kernel time (400 us with the gaps between them
+// where the host was behind) and 53 launches and 331 us.
+constexpr int kFitGroupShift = 6;
+constexpr int kFitGroup = 1 << kFitGroupShift;
+constexpr int kFitSlots = 1536;
+constexpr int kFitHash = 4096;
+constexpr int kFitThreads = 512;
+
+__device__ __forceinline__ uint32_t fit_hash(uint32_t k) { return (k * 2654435761u) >> (32 - 12); }
+static_assert(kFitHash == 1 << 12, "fit_hash gives 12 bits");
+
 template <int DIM>
-__global__ __launch_bounds__(256) void k_fit_span(const uint2* __restrict__ span,
-                                                  const uint32_t* __restrict__ span_count, int64_t cap, uint32_t h,
-                                                  const uint32_t* __restrict__ node_parent, Rec<DIM>* recs) {
-    const uint32_t cnt = (uint32_t)min<int64_t>(*span_count, cap);
-    for (uint32_t j = blockIdx.x * blockDim.x + threadIdx.x; j < cnt; j += gridDim.x * blockDim.x) {
-        const uint2 e = span[j];
-        if (e.y != h) continue;
-        const uint32_t k = e.x;
-        const uint32_t link = node_parent[k];
-        if (link == kNone) continue;
-        Child<DIM> c0, c1;
-        unpack<DIM>(recs[k], c0, c1);
-        float lo[DIM], hi[DIM];
+__global__ __launch_bounds__(kFitThreads) void k_fit_group(const uint32_t* __restrict__ span,
+                                                   const uint32_t* __restrict__ span_count, int64_t tiles, int shift,
+                                                   uint32_t* __restrict__ out, uint32_t* __restrict__ out_count,
+                                                   uint32_t* arrive, const uint32_t* __restrict__ rlo,
+                                                   const uint32_t* __restrict__ rhi,
+                                                   const uint32_t* __restrict__ node_parent, Rec<DIM>* recs,
+                                                   const Ctrl* ctrl) {
+    if (ctrl->error) return;
+    __shared__ uint32_t s_off[kFitGroup + 1];
+    __shared__ uint32_t s_out, s_in;
+    __shared__ uint32_t s_node[kFitSlots], s_link[kFitSlots], s_arrive[kFitSlots];
+    __shared__ uint32_t s_par[kFitSlots];  // (slot of the parent) << 1 | side, or kNone outside the group
+    __shared__ float s_box[kFitSlots][2][2 * DIM];
+    __shared__ uint32_t s_hash[kFitHash];  // slots
+    const int t = threadIdx.x;
+    const int64_t g0 = (int64_t)blockIdx.x * kFitGroup;  // first tile of the group
+    const int up = shift + kFitGroupShift;
+    for (int x = t; x < kFitHash; x += kFitThreads) s_hash[x] = kNone;
+    if (t < kFitGroup) {
+        uint32_t x = g0 + t < tiles ? span_count[g0 + t] : 0u;
 #pragma unroll
-        for (int d = 0; d < DIM; ++d) {
-            lo[d] = fminf(c0.lo[d], c1.lo[d]);
-            hi[d] = fmaxf(c0.hi[d], c1.hi[d]);
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t y = __shfl_up(x, off);
+            if (t >= off) x += y;
         }
-        set_child<DIM>(&recs[link >> 1], (int)(link & 1u), lo, hi, k);
+        s_off[t + 1] = x;
+        if (t == 0) s_off[0] = s_out = s_in = 0u;
+    }
+    __syncthreads();
+    const uint32_t total = s_off[kFitGroup];
+    for (uint32_t x = t; x < total; x += kFitThreads) {
+        int a = 0;  // the tile that listed entry x: the last one that starts at or before it
+#pragma unroll
+        for (int b = kFitGroup / 2; b > 0; b >>= 1)
+            if (s_off[a + b] <= x) a += b;
+        const uint32_t k = span[((g0 + a) << shift) + (x - s_off[a])];
+        const uint32_t lo = rlo[k], hi = rhi[k];
+        if ((uint64_t)lo >> up != (uint64_t)hi >> up) {
+            out[((int64_t)blockIdx.x << up) + atomicAdd(&s_out, 1u)] = k;
+            arrive[k] = fit_ready(lo, hi, k, up);
+            continue;
+        }
+        const uint32_t slot = atomicAdd(&s_in, 1u);
+        if (slot >= kFitSlots) continue;
+        const bool r0 = (uint64_t)lo >> shift == (uint64_t)k >> shift;
+        const bool r1 = (uint64_t)(k + 1u) >> shift == (uint64_t)hi >> shift;
+        s_node[slot] = k;
+        s_link[slot] = node_parent[k];
+        s_arrive[slot] = (uint32_t)r0 + (uint32_t)r1;
+        if (r0 || r1) {
+            Child<DIM> c[2];
+            unpack<DIM>(recs[k], c[0], c[1]);
+#pragma unroll
+            for (int side = 0; side < 2; ++side)
+                if (side ? r1 : r0)
+#pragma unroll
+                    for (int d = 0; d < DIM; ++d) {
+                        s_box[slot][side][d] = c[side].lo[d];
+                        s_box[slot][side][DIM + d] = c[side].hi[d];
+                    }
+        }
+        // (room for every slot: the table is larger than their number)
+        for (uint32_t h = fit_hash(k); atomicCAS(&s_hash[h], kNone, slot) != kNone; h = (h + 1) % kFitHash) {}
+    }
+    __syncthreads();
+    const uint32_t inside = s_in;
+    if (t == 0) out_count[blockIdx.x] = s_out;
+    if (inside <= kFitSlots) {
+        for (uint32_t x = t; x < inside; x += kFitThreads) {
+            const uint32_t link = s_link[x];
+            uint32_t par = kNone;
+            if (link != kNone)
+                for (uint32_t h = fit_hash(link >> 1); s_hash[h] != kNone; h = (h + 1) % kFitHash)
+                    if (s_node[s_hash[h]] == link >> 1) {
+                        par = (s_hash[h] << 1) | (link & 1u);
+                        break;
+                    }
+            s_par[x] = par;
+            // only climbs change the counts from here on, so the starts are marked now
+            if (s_arrive[x] == 2u) s_arrive[x] = 3u;
+        }
+        __syncthreads();
+        for (uint32_t x = t; x < inside; x += kFitThreads) {
+            if (s_arrive[x] != 3u) continue;  // a climb arrives here
+            uint32_t cur = x;
+            for (int step = 0; step < 160; ++step) {
+                const uint32_t link = s_link[cur], par = s_par[cur];
+                if (link == kNone) break;  // the root
+                float lo[DIM], hi[DIM];
+#pragma unroll
+                for (int d = 0; d < DIM; ++d) {
+                    lo[d] = fminf(s_box[cur][0][d], s_box[cur][1][d]);
+                    hi[d] = fmaxf(s_box[cur][0][DIM + d], s_box[cur][1][DIM + d]);
+                }
+                set_child<DIM>(&recs[link >> 1], (int)(link & 1u), lo, hi, s_node[cur]);
+                if (par == kNone) break;
+                const uint32_t P = par >> 1;
+#pragma unroll
+                for (int d = 0; d < DIM; ++d) {
+                    s_box[P][par & 1u][d] = lo[d];
+                    s_box[P][par & 1u][DIM + d] = hi[d];
+                }
+                lds_fence();
+                if (atomicAdd(&s_arrive[P], 1u) == 0u) break;  // the sibling's climb goes on
+                lds_fence();
+                cur = P;
+            }
+        }
+        return;
+    }
+    for (uint32_t x = t; x < total; x += kFitThreads) {
+        int a = 0;
+#pragma unroll
+        for (int b = kFitGroup / 2; b > 0; b >>= 1)
+            if (s_off[a + b] <= x) a += b;
+        const uint32_t k = span[((g0 + a) << shift) + (x - s_off[a])];
+        const uint32_t klo = rlo[k], khi = rhi[k];
+        if ((uint64_t)klo >> up != (uint64_t)khi >> up) continue;    // listed above
+        if (fit_ready(klo, khi, k, shift) != 2u) continue;  // a climb arrives here
+        uint32_t cur = k;
+        for (int step = 0; step < 160; ++step) {
+            const uint32_t link = node_parent[cur];
+            if (link == kNone) break;  // the root
+            const uint32_t P = link >> 1;
+            const uint32_t plo = rlo[P], phi = rhi[P];
+            Child<DIM> c0, c1;
+            unpack<DIM>(recs[cur], c0, c1);
+            float lo[DIM], hi[DIM];
+#pragma unroll
+            for (int d = 0; d < DIM; ++d) {
+                lo[d] = fminf(c0.lo[d], c1.lo[d]);
+                hi[d] = fmaxf(c0.hi[d], c1.hi[d]);
+            }
+            set_child<DIM>(&recs[P], (int)(link & 1u), lo, hi, cur);
+            if ((uint64_t)plo >> up != (uint64_t)phi >> up) break;
+            __threadfence_block();
+            if (__hip_atomic_fetch_add(&arrive[P], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == 0u)
+                break;  // the sibling's climb goes on
+            __threadfence_block();
+            cur = P;
+        }
     }
 }
 
@@ -2716,20 +2872,40 @@ int sort_edges(emst_ctx* ctx, Bufs<DIM>& b, int64_t n, const uint32_t* slot_clou
     return EMST_OK;
 }
 
-// Hierarchy (bottom-up, exchange only) and the boxes of every node inside
-// a tile of kFitTile leaves.  The node records live in the cells' array,
-// the list of nodes across tile borders in the exchange words (both free
-// until the cells and the wave starts are made), its length in the sort's
-// histogram (free until the next sort).
+// Hierarchy (bottom-up, exchange only) and every box.  The node records live
+// in the cells' array; the first level's list of nodes across tile borders
+// and the arrival counts share the exchange words (both arrays are free
+// until the cells and the wave starts are made), the lists of the levels
+// above alternate between the sort's value buffers, and the counts of every
+// level lie one after another in the sort's histogram (free until the next
+// sort).  The control block names the root and the height once the
+// hierarchy kernel has run: with `mirror` its copy is queued right behind
+// that kernel and `ev` marks its arrival, so that the host reads it while
+// the boxes are fitted.
 template <int DIM>
-int build_hierarchy(emst_ctx* ctx, Bufs<DIM>& b, const uint64_t* codes, int64_t n, hipStream_t st) {
+int build_hierarchy(emst_ctx* ctx, Bufs<DIM>& b, const uint64_t* codes, int64_t n, hipStream_t st,
+                    Ctrl* mirror = nullptr, hipEvent_t ev = nullptr) {
     NodeInfo* info = reinterpret_cast<NodeInfo*>(b.up);
     k_build<DIM, false><<<grid_for(n), 256, 0, st>>>(codes, b.orig, n, b.recs, b.leaf_parent, info, b.exch, b.ctrl);
-    k_fill_u32<<<1, 64, 0, st>>>(b.hist, 1, 0u);
-    const unsigned tiles = (unsigned)((n + kFitTile - 1) / kFitTile);
-    k_fit_tiles<DIM><<<tiles, 256, 0, st>>>(b.spts, b.orig, b.leaf_parent, info, n, b.recs, b.rlo, b.rhi,
-                                              b.node_parent, b.height, reinterpret_cast<uint2*>(b.exch), b.hist,
-                                              b.ctrl);
+    if (mirror) {
+        HIP_TRY(hipMemcpyAsync(mirror, b.ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, st));
+        HIP_TRY(hipEventRecord(ev, st));
+    }
+    uint32_t* list = reinterpret_cast<uint32_t*>(b.exch);
+    uint32_t* arrive = list + (n - 1);
+    uint32_t* next[2] = {b.v0, b.v1};
+    uint32_t* counts = b.hist;
+    int64_t tiles = (n + kFitTile - 1) / kFitTile;
+    k_fit_tiles<DIM><<<(unsigned)tiles, 256, 0, st>>>(b.spts, b.orig, b.leaf_parent, info, n, b.recs, b.rlo, b.rhi,
+                                                      b.node_parent, list, counts, arrive, b.ctrl);
+    for (int shift = kFitShift, lvl = 0; tiles > 1; shift += kFitGroupShift, ++lvl) {
+        const int64_t groups = (tiles + kFitGroup - 1) / kFitGroup;
+        k_fit_group<DIM><<<(unsigned)groups, kFitThreads, 0, st>>>(list, counts, tiles, shift, next[lvl & 1], counts + tiles,
+                                                           arrive, b.rlo, b.rhi, b.node_parent, b.recs, b.ctrl);
+        list = next[lvl & 1];
+        counts += tiles;
+        tiles = groups;
+    }
     HIP_TRY(hipGetLastError());
     return EMST_OK;
 }
@@ -2741,30 +2917,15 @@ static int check_hierarchy(emst_ctx* ctx, const Ctrl* h, int64_t n) {
     return EMST_OK;
 }
 
-// The boxes of the nodes across tile borders, one launch per height below
-// the root H (after build_hierarchy, whose list they come from).
-template <int DIM>
-int fit_levels(emst_ctx* ctx, Bufs<DIM>& b, const uint64_t* codes, int64_t n, uint32_t H, hipStream_t st) {
-    (void)codes;
-    // at most 129 listed nodes per tile border (the grid only; the kernel
-    // reads the list's length)
-    const int64_t cap = ((n + kFitTile - 1) / kFitTile) * 129;
-    const unsigned grid = std::min<unsigned>(grid_for(cap), 1024);
-    for (uint32_t h = 1; h < H; ++h)
-        k_fit_span<DIM><<<grid, 256, 0, st>>>(reinterpret_cast<const uint2*>(b.exch), b.hist, n - 1, h,
-                                               b.node_parent, b.recs);
-    HIP_TRY(hipGetLastError());
-    return EMST_OK;
-}
-
-// Hierarchy and boxes in one go (reads the control block back for the root
-// and height).
+// Hierarchy and boxes, with the control block read back for the root and
+// height.
 template <int DIM>
 int build_tree(emst_ctx* ctx, Bufs<DIM>& b, const uint64_t* codes, int64_t n, hipStream_t st) {
-    if (int rc = build_hierarchy<DIM>(ctx, b, codes, n, st)) return rc;
-    if (int rc = read_ctrl(ctx, b.ctrl, st)) return rc;
-    if (int rc = check_hierarchy(ctx, ctx->h_ctrl, n)) return rc;
-    return fit_levels<DIM>(ctx, b, codes, n, ctx->h_ctrl->height, st);
+    if (int rc = build_hierarchy<DIM>(ctx, b, codes, n, st, ctx->h_ctrl, ctx->sev[0])) return rc;
+    HIP_TRY(hipEventSynchronize(ctx->sev[0]));
+    const int rc = check_hierarchy(ctx, ctx->h_ctrl, n);
+    if (rc) (void)hipStreamSynchronize(st);  // nothing stays queued on the caller's workspace
+    return rc;
 }
 
 void finish_stats(emst_ctx* ctx, emst_stats& S) {
@@ -2784,7 +2945,7 @@ void finish_stats(emst_ctx* ctx, emst_stats& S) {
 
 // One cloud's build as a resumable sequence of phases.  Each phase
 // enqueues its work and a copy of the control block into the job's pinned
-// host mirror; after the stream has drained, advance() reads the mirror and
+// host mirror; after it has arrived, advance() reads the mirror and
 // picks the next phase.  emst_build, emst_build_mreach and the one-round
 // test hook run one job to the end.
 //
@@ -2865,7 +3026,6 @@ int job_enqueue(emst_ctx* ctx, Job& j, hipStream_t st) {
     switch (j.phase) {
     case kPhTree: {  // validation + scene box, Morton codes, sort, hierarchy
         if (j.prof) HIP_TRY(hipEventRecord(E[0], st));
-        k_init_ctrl<<<1, 64, 0, st>>>(b.ctrl);
         HIP_TRY(launch_bbox<DIM>(j.pts, n, b.bpart, b.ctrl, st));
         // The codes take the box from the control block.  A cloud that fails
         // validation (read back after this phase) still yields codes of some
@@ -2874,11 +3034,9 @@ int job_enqueue(emst_ctx* ctx, Job& j, hipStream_t st) {
         const int shifts[8] = {0, 8, 16, 24, 32, 40, 48, 56};
         HIP_TRY(radix_sort_pairs(st, b.k0, b.v0, b.k1, b.v1, b.hist, n, shifts, 8, &j.codes_in1));
         const uint64_t* codes = j.codes_in1 ? b.k1 : b.k0;
-        k_count_dups<<<grid_for(n), 256, 0, st>>>(codes, n, b.ctrl);
         k_gather<DIM><<<grid_for(n), 256, 0, st>>>(j.pts, j.codes_in1 ? b.v1 : b.v0, n, b.spts, b.orig,
                                                    b.labels, b.exch);
-        if (int rc = build_hierarchy<DIM>(ctx, b, codes, n, st)) return rc;
-        break;
+        return build_hierarchy<DIM>(ctx, b, codes, n, st, j.h, ctx->sev[0]);
     }
     case kPhRank: {
         // many equal codes: rebuild on rank-space codes (the node records
@@ -2899,12 +3057,10 @@ int job_enqueue(emst_ctx* ctx, Job& j, hipStream_t st) {
         const uint64_t* codes = j.codes_in1 ? b.k1 : b.k0;
         k_gather<DIM><<<grid_for(n), 256, 0, st>>>(j.pts, j.codes_in1 ? b.v1 : b.v0, n, b.spts, b.orig,
                                                    b.labels, b.exch);
-        if (int rc = build_hierarchy<DIM>(ctx, b, codes, n, st)) return rc;
-        break;
+        return build_hierarchy<DIM>(ctx, b, codes, n, st, j.h, ctx->sev[0]);
     }
-    case kPhFit: {  // boxes, Morton cells, wave starts, core distances; then round 0
+    case kPhFit: {  // Morton cells, wave starts, core distances; then round 0
         const uint64_t* codes = j.codes_in1 ? b.k1 : b.k0;
-        if (int rc = fit_levels<DIM>(ctx, b, codes, n, (uint32_t)j.height, st)) return rc;
         k_cells<DIM><<<grid_for(n - 1), 256, 0, st>>>(codes, b.node_parent, n - 1, j.mp, j.ranks, b.up);
         k_wave_lca<<<grid_for((n + 63) / 64), 256, 0, st>>>(b.rlo, b.rhi, b.leaf_parent, b.node_parent, n,
                                                             reinterpret_cast<uint32_t*>(b.exch));
@@ -2975,7 +3131,7 @@ int job_advance(emst_ctx* ctx, Job& j) {
             j.mp = morton_params_of(*h, DIM);  // the parameters k_morton derived on the device
         }
         if (int rc = check_hierarchy(ctx, h, n)) return rc;
-        if (j.phase == kPhTree && (int64_t)h->dup_codes * 64 > n) {
+        if (j.phase == kPhTree && many_dups(h->dup_codes, n)) {
             j.ranks = true;
             j.phase = kPhRank;
         } else {
@@ -3076,10 +3232,15 @@ int job_run(emst_ctx* ctx, Job& j, hipStream_t st) {
             }
             continue;
         }
-        const hipError_t w = hipStreamSynchronize(st);
+        // the tree phases' control block arrives before their boxes are done
+        const bool tree = rc == EMST_OK && (j.phase == kPhTree || j.phase == kPhRank);
+        const hipError_t w = tree ? hipEventSynchronize(ctx->sev[0]) : hipStreamSynchronize(st);
         if (rc) return rc;
         if (w != hipSuccess) return fail(ctx, EMST_EHIP, hipGetErrorString(w));
-        if (int rc2 = job_advance<DIM>(ctx, j)) return rc2;
+        if (int rc2 = job_advance<DIM>(ctx, j)) {
+            if (tree) (void)hipStreamSynchronize(st);  // nothing stays queued on the caller's workspace
+            return rc2;
+        }
     }
     return EMST_OK;
 }
@@ -3484,9 +3645,7 @@ static int bjob_enqueue(emst_ctx* ctx, BJob& j, hipStream_t st, Ctrl* mirror, in
         j.wait = true;
         break;
     }
-    case kBFit: {  // boxes, every cloud's subtree root, the first round
-        const uint64_t* codes = j.codes_in1 ? b.k1 : b.k0;
-        if (int rc = fit_levels<3>(ctx, b, codes, n, (uint32_t)j.height, st)) return rc;
+    case kBFit: {  // every cloud's subtree root, the first round
         k_fill_u32<<<grid_for(j.B), 256, 0, st>>>(x.croot, j.B, kNone);
         k_cloud_roots<<<grid_for(n - 1), 256, 0, st>>>(b.rlo, b.rhi, x.cloud_sorted, x.cin, n - 1, x.croot);
         HIP_TRY(hipGetLastError());
@@ -4513,7 +4672,6 @@ extern "C" int emst_test_tree_boxes(emst_ctx* ctx, const float* d_points, int64_
     char* ws = (char*)d_workspace;
     const Layout L = make_layout(n, 3);
     Bufs<3> b = carve<3>(ws, L);
-    k_init_ctrl<<<1, 64, 0, st>>>(b.ctrl);
     HIP_TRY(launch_bbox<3>(d_points, n, b.bpart, b.ctrl, st));
     HIP_TRY(hipGetLastError());
     if (int rc = read_ctrl(ctx, b.ctrl, st)) return rc;
