@@ -287,7 +287,8 @@ typedef struct emst_stats {
     int32_t dim;
     int32_t rounds;                 /* Boruvka rounds */
     int64_t components[64];         /* components at the start of each round */
-    int32_t tree_height;            /* edges on the longest root-leaf path */
+    int32_t tree_height;            /* edges on the longest root-leaf path; 0 if
+                                       the cloud was solved without a tree */
     int32_t traversal_launches;     /* = rounds */
     double traversal_ms;            /* sum over rounds, traversal kernel only */
     double traversal_ms_round[64];  /* per round */
@@ -304,7 +305,10 @@ typedef struct emst_stats {
     int64_t leaf_tests_round[64];
     int64_t dist_evals;             /* leaf children outside the query's
                                        component: point distances computed */
-    int32_t traversal_variant;      /* the traversal variant that ran */
+    int32_t traversal_variant;      /* the traversal variant that ran; -1 if a
+                                       small cloud was solved without a tree
+                                       (emst_set_traversal -1, no table entry,
+                                       no counting: up to 16,384 points) */
     int32_t rank_codes;             /* 1 if the tree was built on rank-space
                                        codes (many points shared a Morton
                                        code), else 0 */
@@ -348,7 +352,9 @@ int emst_set_counting(emst_ctx *ctx, int on);
  *      its candidate if that is still outside its component, or "nothing"
  *      if it found nothing within a radius at least the new one (default)
  * -1 (the default) takes the variant from the context's autotune table
- * (emst_set_autotune) for the call's mode, dimension and size, else 13.
+ * (emst_set_autotune) for the call's mode, dimension and size, else 13, or
+ * for emst_build of up to 16,384 points a search without a tree (unless
+ * the table, emst_set_lds_depth or emst_set_counting ask for a traversal).
  * Batches (emst_build_batched) run 0, 5, 8 or 13 (with the start of 7) as
  * chosen and 7 for 10 and 11.
  * Returns EMST_EINVAL for any other value. */

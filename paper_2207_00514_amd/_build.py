@@ -9,7 +9,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 SO = os.path.join(PKG, "libemst.so")
 SOURCES = ["radix_sort.hip", "emst_build.hip", "tune_table.cpp"]
-HEADERS = ["emst_common.h", "emst_kernels.h", "radix_sort.h", "traverse.h", "tune_table.h"]
+HEADERS = ["emst_common.h", "flat.h", "emst_kernels.h", "radix_sort.h", "traverse.h", "tune_table.h"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",

@@ -20,6 +20,7 @@
 #include "../../include/emst.h"
 #include "../../include/emst_test.h"
 #include "emst_kernels.h"
+#include "flat.h"
 #include "radix_sort.h"
 #include "traverse.h"
 #include "tune_table.h"
@@ -101,6 +102,8 @@ __device__ __forceinline__ void init_ctrl(Ctrl* ctrl) {
     ctrl->key_or = 0ull; ctrl->key_and = ~0ull;
     ctrl->internal_tests = 0; ctrl->leaf_tests = 0; ctrl->dist_evals = 0; ctrl->touched = 0;
     ctrl->long_ties = 0; ctrl->dup_codes = 0; ctrl->done = 0; ctrl->rounds_run = 0;
+    ctrl->flat_bad = 0;
+    for (uint32_t& c : ctrl->flat_comps) c = 0;
 }
 
 __global__ void k_init_ctrl(Ctrl* ctrl) {
@@ -231,6 +234,86 @@ __global__ __launch_bounds__(256) void k_morton(const float* __restrict__ pts, i
         keys[i] = code;
         vals[i] = (uint32_t)i;
     }
+}
+
+// Codes of a cloud solved without a tree (flat.h): 48 bits (16 per axis in
+// 3D, 24 in 2D) above the point's 16-bit index.  Every workgroup folds the
+// partials of k_bbox itself (at most 64 of them, from L2), or without them
+// (kFlatOne points and fewer) reduces every point, which saves a launch;
+// the first one starts the control block with the box, the check
+// for non-finite coordinates and the check that the box's squared extent,
+// evaluated in the order of D, is finite.
+template <int DIM>
+__global__ __launch_bounds__(256) void k_flat_codes(const float* __restrict__ pts, int64_t n,
+                                                    const uint32_t* __restrict__ part, int nb, Ctrl* ctrl,
+                                                    uint64_t* __restrict__ keys) {
+    __shared__ uint32_t s[4][7];
+    uint32_t v[7] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0u, 0u, 0u, 0u};
+    if (!part) {
+        for (int64_t p = threadIdx.x; p < n; p += 256)
+#pragma unroll
+            for (int k = 0; k < DIM; ++k) {
+                const float x = pts[p * DIM + k];
+                v[6] |= !isfinite(x);
+                v[k] = min(v[k], ord_enc(x));
+                v[3 + k] = max(v[3 + k], ord_enc(x));
+            }
+        nb = 0;
+    }
+    for (int b = threadIdx.x; b < nb; b += 256) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            v[k] = min(v[k], part[8 * b + k]);
+            v[3 + k] = max(v[3 + k], part[8 * b + 3 + k]);
+        }
+        v[6] |= part[8 * b + 6];
+    }
+#pragma unroll
+    for (int k = 0; k < 7; ++k) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            const uint32_t o = (uint32_t)__shfl_xor((int)v[k], off);
+            v[k] = k < 3 ? min(v[k], o) : k < 6 ? max(v[k], o) : v[k] | o;
+        }
+        if (lane_id() == 0) s[threadIdx.x / 64][k] = v[k];
+    }
+    __syncthreads();
+    float lo[3] = {0.f, 0.f, 0.f}, hi[3] = {0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        v[k] = min(min(s[0][k], s[1][k]), min(s[2][k], s[3][k]));
+        v[3 + k] = max(max(s[0][3 + k], s[1][3 + k]), max(s[2][3 + k], s[3][3 + k]));
+        if (k < DIM) {
+            lo[k] = ord_dec(v[k]);
+            hi[k] = ord_dec(v[3 + k]);
+        }
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        init_ctrl(ctrl);
+        for (int k = 0; k < 3; ++k) {
+            ctrl->bb_min[k] = v[k];
+            ctrl->bb_max[k] = v[3 + k];
+        }
+        const bool nonfinite = (s[0][6] | s[1][6] | s[2][6] | s[3][6]) != 0u;
+        ctrl->nonfinite = nonfinite;
+        float e = (hi[0] - lo[0]) * (hi[0] - lo[0]);
+        for (int k = 1; k < DIM; ++k) e = e + (hi[k] - lo[k]) * (hi[k] - lo[k]);
+        ctrl->flat_bad = nonfinite ? 1u : (isfinite(e) ? 0u : 2u);
+    }
+    const MortonParams mp = morton_params(lo, hi, DIM, 48 / DIM);
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    uint64_t q[DIM];
+#pragma unroll
+    for (int k = 0; k < DIM; ++k) {
+        double t = ((double)pts[i * DIM + k] - mp.lo[k]) * mp.scale[k];
+        t = fmin(fmax(t, 0.0), mp.qmax);
+        q[k] = (uint64_t)t;
+    }
+    uint64_t code;
+    if (DIM == 3) code = (spread3(q[0]) << 2) | (spread3(q[1]) << 1) | spread3(q[2 % DIM]);
+    else code = (spread2(q[0]) << 1) | spread2(q[1]);
+    keys[i] = (code << 16) | (uint64_t)i;
 }
 
 // ---------------------------------------------------------------------------
@@ -433,13 +516,6 @@ constexpr int kFitTile = 1 << kFitShift;  // 256 and 1024 measured slower (LDS p
 __device__ __forceinline__ uint32_t fit_ready(uint32_t lo, uint32_t hi, uint32_t k, int shift) {
     return (uint32_t)((uint64_t)lo >> shift == (uint64_t)k >> shift) +
            (uint32_t)((uint64_t)(k + 1u) >> shift == (uint64_t)hi >> shift);
-}
-
-// Orders the LDS accesses of the workgroup's threads around it.  Unlike
-// __threadfence_block it does not wait for stores to memory, which nothing
-// in the launch reads back.
-__device__ __forceinline__ void lds_fence() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup", "local");
 }
 
 template <int DIM>
@@ -3245,9 +3321,112 @@ int job_run(emst_ctx* ctx, Job& j, hipStream_t st) {
     return EMST_OK;
 }
 
+// Rounds queued before the first look at the result: what uniform and
+// clustered clouds of n points take (6 at 1,000 points, 7 at 10,000).  A round too many costs its four empty launches (10 us), one too
+// few a wait of the host (20 us).
+static int flat_rounds(int64_t n) {
+    int r = 3;
+    for (int64_t m = n; m > 32; m /= 5) ++r;
+    return std::min(r, 16);
+}
+
+// One cloud of at most kFlatMax points without a tree (flat.h).
+template <int DIM>
+int flat_impl(emst_ctx* ctx, const float* pts, int64_t n, int32_t* edges, float* weights, float* d2, char* ws,
+              hipStream_t st) {
+    const bool prof = ctx->profiling && ctx->ev_ok;
+    hipEvent_t* E = ctx->ev;
+    const Layout L = make_layout(n, DIM);
+    Bufs<DIM> b = carve<DIM>(ws, L);
+    // whole tiles of points, in the sort's histogram (the smallest of which
+    // holds 65,600)
+    float4* spts = reinterpret_cast<float4*>(b.hist);
+    static_assert(kFlatMax * sizeof(float4) <= 4 * radix_hist_elems(), "the points fit");
+    float4* box = reinterpret_cast<float4*>(b.up);
+    FlatArgs a;
+    a.n = n;
+    a.tiles = (int)((n + kFlatTile - 1) / kFlatTile);
+    a.pts = spts;
+    a.inv = b.succ;
+    a.box = box;
+    a.labels = b.labels;
+    a.tile_label = b.leaf_parent;
+    a.cand_d = b.cand_d;
+    a.cand_p = b.cand_p;
+    a.compkey = b.compkey;
+    a.par = b.par;
+    a.ekeys = reinterpret_cast<uint64_t*>(b.eud);
+    a.ctrl = b.ctrl;
+    const unsigned grid = grid_for(n), tiles = (unsigned)a.tiles;
+
+    if (prof) HIP_TRY(hipEventRecord(E[0], st));
+    const bool own_box = n <= kFlatOne;
+    if (!own_box) k_bbox<DIM><<<grid, 256, 0, st>>>(pts, n, b.bpart);
+    k_flat_codes<DIM><<<grid, 256, 0, st>>>(pts, n, own_box ? nullptr : b.bpart, (int)grid, b.ctrl, b.k0);
+    k_flat_order<DIM><<<tiles, 1024, 0, st>>>(b.k0, pts, (int)n, spts, b.succ);
+    k_flat_tiles<DIM><<<grid, 256, 0, st>>>(a, spts, box);
+    HIP_TRY(hipGetLastError());
+    if (prof) HIP_TRY(hipEventRecord(E[1], st));
+
+    int next = 0;  // the next round to queue
+    auto queue = [&](int upto) -> int {
+        for (; next < upto; ++next) {
+            if (prof) HIP_TRY(hipEventRecord(E[8 + 2 * next], st));
+            k_flat_search<DIM><<<tiles, 64 * kFlatWaves, 0, st>>>(a, next);
+            if (prof) HIP_TRY(hipEventRecord(E[9 + 2 * next], st));
+            if (n <= kFlatOne) {
+                k_flat_merge<DIM><<<1, 1024, 0, st>>>(a, next);
+                continue;
+            }
+            k_flat_parent<<<grid, 256, 0, st>>>(a, next);
+            k_flat_jump<<<grid, 256, 0, st>>>(a, next);
+            k_flat_relabel<DIM><<<grid, 256, 0, st>>>(a, next);
+        }
+        HIP_TRY(hipGetLastError());
+        return EMST_OK;
+    };
+    const Ctrl* h = ctx->h_ctrl;
+    const int max_rounds = 17;
+    for (int upto = flat_rounds(n);; upto = std::min(next + 2, max_rounds)) {
+        if (int rc = queue(upto)) return rc;
+        if (prof) HIP_TRY(hipEventRecord(E[2], st));
+        k_flat_edges<<<tiles, 1024, 0, st>>>(a.ekeys, (int)n, b.ctrl, next - 1, edges, weights, d2);
+        HIP_TRY(hipGetLastError());
+        if (prof) HIP_TRY(hipEventRecord(E[3], st));
+        HIP_TRY(hipMemcpyAsync(ctx->h_ctrl, b.ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, st));
+        HIP_TRY(hipStreamSynchronize(st));
+        if (h->nonfinite) return fail(ctx, EMST_ENONFINITE, "non-finite coordinate");
+        if (h->flat_bad) return fail(ctx, EMST_ERANGE, "squared extent of the cloud overflows float32");
+        if (h->flat_comps[next - 1] <= 1u) break;
+        if (next == max_rounds) return fail(ctx, EMST_EINTERNAL, "too many rounds");
+    }
+    emst_stats S;
+    memset(&S, 0, sizeof(S));
+    S.n = n;
+    S.dim = DIM;
+    int64_t ncomp = n;
+    while (ncomp > 1) {
+        const int64_t left = S.rounds < next ? (int64_t)h->flat_comps[S.rounds] : 0;
+        if (left < 1 || left >= ncomp) return fail(ctx, EMST_EINTERNAL, "round made no progress");
+        S.components[S.rounds] = ncomp;
+        S.queries_round[S.rounds] = n;
+        ++S.rounds;
+        ncomp = left;
+    }
+    S.traversal_launches = S.rounds;
+    S.traversal_variant = -1;
+    finish_stats(ctx, S);
+    return EMST_OK;
+}
+
 template <int DIM>
 int build_impl(emst_ctx* ctx, const float* pts, int64_t n, int32_t* edges, float* weights, float* d2, char* ws,
                hipStream_t st, int k_pts = 0, float* core_out = nullptr, bool core_only = false) {
+    // a small cloud needs no tree, unless the caller asked for a traversal
+    // shape or for the traversal's counts
+    if (n <= kFlatMax && k_pts == 0 && !ctx->counting && ctx->traversal < 0 && ctx->lds_depth == 0 &&
+        !ctx->tune.pick(0, DIM, n))
+        return flat_impl<DIM>(ctx, pts, n, edges, weights, d2, ws, st);
     Job j = make_job(ctx, pts, n, DIM, ws, edges, weights, d2, k_pts, core_out, core_only, ctx->h_ctrl,
                      ctx->profiling && ctx->ev_ok);
     if (int rc = job_run<DIM>(ctx, j, st)) return rc;

@@ -147,6 +147,13 @@ __device__ __forceinline__ uint64_t load_relaxed64(const uint64_t* p) {
     return __hip_atomic_load(const_cast<uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Orders the LDS accesses of the workgroup's threads around it.  Unlike
+// __threadfence_block it does not wait for stores to memory, which nothing
+// in the launch reads back.
+__device__ __forceinline__ void lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup", "local");
+}
+
 __device__ __forceinline__ int lane_id() { return __lane_id(); }
 
 // gfx950 hands workgroups to its 8 XCDs round-robin (workgroup w runs on

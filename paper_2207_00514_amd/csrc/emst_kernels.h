@@ -27,8 +27,11 @@ struct Ctrl {
     uint32_t done;           // the round loop has reached its target: later round kernels return at once
     uint32_t qcount;         // length of this round's query list
     uint32_t rounds_run;     // rounds that ran before the loop reached its target
+    uint32_t flat_bad;       // clouds without a tree: 1 non-finite coordinate, 2 overflowing extent
+    uint32_t flat_comps[17]; // clouds without a tree: components each round left (0: it did not run)
     uint32_t pad;
 };
+static_assert(sizeof(Ctrl) <= 256, "the control block keeps its place in the workspace");
 
 // Search radius of a round from the second on (traversal variant 13): the
 // component bound, lowered to the shortest candidate already offered to the

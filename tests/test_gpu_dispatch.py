@@ -61,3 +61,105 @@ def test_boxes_of_nodes_across_tiles(ctx, n, kind):
     mn, mx = node_boxes(pts, left.cpu().numpy(), right.cpu().numpy(), root)
     np.testing.assert_array_equal(lo.cpu().numpy(), mn)
     np.testing.assert_array_equal(hi.cpu().numpy(), mx)
+
+
+def solve(ctx, pts):
+    e, w, d2 = ctx.build(torch.from_numpy(np.ascontiguousarray(pts, np.float32)).cuda())
+    torch.cuda.synchronize()
+    return e.cpu().numpy(), w.cpu().numpy(), d2.cpu().numpy()
+
+
+def assert_tree(got, ref, tag):
+    e, w, d2 = got
+    assert np.array_equal(e, ref.edges), f"{tag}: edges differ"
+    assert np.array_equal(d2.view(np.uint32), ref.d2.view(np.uint32)), f"{tag}: d2 differ"
+    assert np.array_equal(w.view(np.uint32), ref.w.view(np.uint32)), f"{tag}: weights differ"
+
+
+# Clouds solved without a tree: one tile of 64 points and its edges, several
+# tiles, the largest cloud merged by one workgroup and the first one merged
+# by many, the largest such cloud and the first one with a tree
+FLAT = [2, 3, 63, 64, 65, 129, 1000, 4095, 4096, 4097, 16383, 16384, 16385]
+
+
+@pytest.mark.parametrize("kind", ["uniform", "int", "dup", "outlier"])
+@pytest.mark.parametrize("n", FLAT)
+def test_clouds_without_a_tree(ctx, n, kind):
+    for dim in (2, 3):
+        pts = W.small_random(n, dim, n + dim, kind)
+        print(f"case flat n={n} dim={dim} {kind}", flush=True)
+        got = solve(ctx, pts)
+        assert (ctx.stats()["traversal_variant"] == -1) == (n <= 16384)
+        assert_tree(got, oracle.emst(pts, threads=8), f"{kind} n={n} dim={dim}")
+
+
+def growing_gaps(n):
+    """Every point's nearest neighbour is its predecessor: one chain of n
+    successors in the first merge."""
+    x = np.cumsum(1.0 + np.arange(n) * 1e-3)
+    return np.stack([x, np.zeros(n)], 1)[np.random.default_rng(1).permutation(n)].astype(np.float32)
+
+
+FLAT_FORMS = {
+    "identical": W.identical(1000), "grid2d": W.integer_grid(100, 2, seed=1), "grid3d": W.integer_grid(27, 3, seed=2),
+    "collinear": W.collinear(3000, 2, seed=3),
+    "growing gaps": growing_gaps(12_000), "growing gaps 4k": growing_gaps(4000), "two clusters": W.two_clusters(2000, 3, seed=5),
+    "skewed": W.make("skewed3d_2m", 10_000), "clustered": W.clustered3d(16_000, seed=6),
+    "cosmology": W.cosmology3d(15_000, seed=7),
+    "star": np.concatenate([np.zeros((1, 3)), np.eye(3), -np.eye(3)] * 2000).astype(np.float32),
+    "denormal": (np.random.default_rng(3).random((500, 3)) * 1e-19).astype(np.float32),
+    "large": (np.random.default_rng(4).random((500, 3)) * 1e18).astype(np.float32),
+}
+
+
+@pytest.mark.parametrize("name", sorted(FLAT_FORMS))
+def test_forms_without_a_tree(ctx, name):
+    pts = FLAT_FORMS[name]
+    print(f"case flat {name}", flush=True)
+    assert_tree(solve(ctx, pts), oracle.emst(pts, threads=8), name)
+
+
+@pytest.mark.parametrize("n", [100, 20_000])
+@pytest.mark.parametrize("bad", [np.nan, np.inf, 3e38])
+def test_refused_clouds_write_nothing(ctx, n, bad):
+    import paper_2207_00514_amd as emst
+    pts = W.small_random(n, 3, 1)
+    pts[n // 2, 1] = bad
+    pts[n // 3, 1] = -3e38 if np.isfinite(bad) else 0.0
+    out = (torch.full((n - 1, 2), 7, dtype=torch.int32, device="cuda"), torch.full((n - 1,), 7.0, device="cuda"),
+           torch.full((n - 1,), 7.0, device="cuda"))
+    with pytest.raises(emst.EmstError) as ei:
+        ctx.build(torch.from_numpy(pts).cuda(), out=out)
+    assert ei.value.name == ("EMST_ERANGE" if np.isfinite(bad) else "EMST_ENONFINITE")
+    assert all(bool((t == 7).all()) for t in out)
+    good = W.small_random(n, 3, 2)
+    assert_tree(solve(ctx, good), oracle.emst(good, threads=8), "after a refused cloud")
+
+
+def test_small_clouds_on_several_threads_and_streams():
+    """Four threads with a context and a stream each: their workgroups share
+    the device, so those of one search do not all run at once."""
+    import threading
+    import paper_2207_00514_amd as emst
+    clouds = [W.clustered3d(16_384, seed=s) for s in range(4)] + [W.uniform2d(9_000, seed=s) for s in range(4)]
+    refs = [oracle.emst(p, threads=8) for p in clouds]
+    wrong = []
+
+    def work(k):
+        ctx, st = emst.Context(0), torch.cuda.Stream()
+        with torch.cuda.stream(st):
+            dev = [torch.from_numpy(p).cuda() for p in clouds]
+            for rep in range(10):
+                c = (k + rep) % len(clouds)
+                e, w, d2 = ctx.build(dev[c], stream=st)
+                st.synchronize()
+                if not (np.array_equal(e.cpu().numpy(), refs[c].edges)
+                        and np.array_equal(d2.cpu().numpy().view(np.uint32), refs[c].d2.view(np.uint32))):
+                    wrong.append((k, rep, c))
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong
