@@ -15,6 +15,7 @@
 #include <mutex>
 #include <string>
 #include <thread>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/emst.h"
@@ -859,7 +860,7 @@ __global__ __launch_bounds__(256) void k_wave_lca(const uint32_t* __restrict__ r
 // and [k+1, hi]; the first shares one label exactly when the run of equal
 // labels containing k starts at or before lo, the second when the run
 // containing k+1 ends at or after hi.  Both tests are local to k once every
-// tile of kRunTile positions knows where the run crossing its left edge
+// tile of positions knows where the run crossing its left edge
 // starts and where the run crossing its right edge ends:
 //   - per tile, the last position where a run starts and the first where
 //     one ends (left by the previous round's relabel kernel, or by
@@ -871,16 +872,37 @@ __global__ __launch_bounds__(256) void k_wave_lca(const uint32_t* __restrict__ r
 //     Morton-neighbour bounds of Optimization 2.
 // No thread ever waits on another.
 
-constexpr int kRunPer = 8;                        // positions per thread
-constexpr int kRunTile = 256 * kRunPer;           // positions per tile (one workgroup)
-constexpr int kRunLds = kRunTile + kRunTile / 16 + 8;
+// A tile is one workgroup's 256 x PER positions.  Up to 2^21 points PER is
+// the smallest that keeps the tiles within kFoldTiles, above it 8: with few
+// tiles the kernels of a round are bound by the latency of one thread's
+// chain of loads, scans and atomics, which grows with PER.  k_round_prep per
+// launch at PER = 8 / at this rule's PER: 50,000 points 26.2 / 8.6 us (1),
+// 300,000 27.7 / 12.7 us (1), 2,000,000 43.2 / 37.4 us (4).
+constexpr int kRunPer = 8;                        // positions per thread, at most
+constexpr int kRunTile = 256 * kRunPer;           // positions per tile, at most
+constexpr int run_lds_words(int per) { return 256 * per + 16 * per + 8; }
 
-static inline int run_tiles(int64_t n) { return (int)((n + kRunTile - 1) / kRunTile); }
+// Up to this many tiles, a kernel that needs a scan over the per-tile
+// partials of the kernel before computes its own entry from all of them
+// (at most 2 x 2048 words from L2 per workgroup) instead of waiting for a
+// one-workgroup scan kernel, which saves that launch.
+constexpr int kFoldTiles = 2048;
 
-// LDS hash table of the bound pass (k_round_prep), in the run arrays
-constexpr int kBoundHashBits = 11;
-constexpr int kBoundHash = 1 << kBoundHashBits;
-static_assert(kBoundHash <= kRunLds, "the bound hash fits in the run arrays");
+static inline int run_per(int64_t n) {
+    int per = 1;
+    while (per < kRunPer && n > (int64_t)kFoldTiles * 256 * per) per *= 2;
+    return per;
+}
+static inline int run_tiles(int64_t n, int per) { return (int)((n + 256 * per - 1) / (256 * per)); }
+
+// Calls f with run_per(n) as a compile-time constant.
+template <typename F>
+static inline void with_run_per(int per, F f) {
+    if (per == 1) f(std::integral_constant<int, 1>());
+    else if (per == 2) f(std::integral_constant<int, 2>());
+    else if (per == 4) f(std::integral_constant<int, 4>());
+    else f(std::integral_constant<int, 8>());
+}
 
 // LDS slot of tile-local index x: one pad word per 16 keeps the
 // consecutive positions of one thread in distinct banks.
@@ -919,12 +941,6 @@ __device__ __forceinline__ void block_sum2_256(uint32_t& a, uint32_t& b, uint32_
     a = s_w[0] + s_w[1] + s_w[2] + s_w[3];
     b = s_w[4] + s_w[5] + s_w[6] + s_w[7];
 }
-
-// Up to this many tiles, a kernel that needs a scan over the per-tile
-// partials of the kernel before computes its own entry from all of them
-// (at most 2 x 1024 words from L2 per workgroup) instead of waiting for a
-// one-workgroup scan kernel, which saves that launch.
-constexpr int kFoldTiles = 1024;
 
 // Exclusive max-scan in thread order over the 256 threads (0 for thread 0).
 __device__ __forceinline__ uint32_t block_excl_max256(uint32_t x, uint32_t* s_w4) {
@@ -981,12 +997,13 @@ __device__ __forceinline__ uint32_t block_max_scan_incl(uint32_t x, uint32_t* s_
 // t where a run starts (p = 0 or labels[p-1] != labels[p]), 0 if none;
 // part[2t+1] = the first position where a run ends (p = n-1 or
 // labels[p] != labels[p+1]), kNone if none.
+template <int PER>
 __global__ __launch_bounds__(256) void k_run_partials(const uint32_t* __restrict__ labels, int64_t n,
                                                       uint32_t* __restrict__ part) {
     __shared__ uint32_t s_w[8];
-    const int64_t base = (int64_t)blockIdx.x * kRunTile;
+    const int64_t base = (int64_t)blockIdx.x * (256 * PER);
     uint32_t hmax = 0u, tmin = kNone;
-    for (int q = 0; q < kRunPer; ++q) {
+    for (int q = 0; q < PER; ++q) {
         const int64_t p = base + (int64_t)q * 256 + threadIdx.x;
         if (p >= n) break;
         const uint32_t l = labels[p];
@@ -1060,7 +1077,7 @@ struct KeepArgs {
     uint8_t* kept;
 };
 
-template <int DIM, bool FIRST, bool BOUNDS>
+template <int DIM, bool FIRST, bool BOUNDS, int PER>
 __global__ __launch_bounds__(256) void k_round_prep(const uint32_t* __restrict__ labels,
                                                     const uint32_t* __restrict__ carry,
                                                     const uint32_t* __restrict__ rlo,
@@ -1070,23 +1087,25 @@ __global__ __launch_bounds__(256) void k_round_prep(const uint32_t* __restrict__
                                                     const float* __restrict__ core_s, int64_t n, uint32_t* ub,
                                                     Ctrl* ctrl, const uint32_t* __restrict__ fold_part, int nt,
                                                     KeepArgs keep, uint32_t* __restrict__ succ) {
+    constexpr int kHashBits = PER == 8 ? 11 : PER == 4 ? 10 : PER == 2 ? 9 : 8;
+    constexpr int kBoundHash = 1 << kHashBits;  // one entry per position of the tile
     if (ctrl->done) return;
-    __shared__ uint32_t s_lab[kRunLds];               // labels of positions base-1 .. base+kRunTile
-    __shared__ uint32_t s_rs[FIRST ? 1 : kRunLds];    // start of the run containing each position
-    __shared__ uint32_t s_re[FIRST ? 1 : kRunLds];    // end of the run containing each position
+    __shared__ uint32_t s_lab[run_lds_words(PER)];               // labels of positions base-1 .. base+(256 * PER)
+    __shared__ uint32_t s_rs[FIRST ? 1 : run_lds_words(PER)];    // start of the run containing each position
+    __shared__ uint32_t s_re[FIRST ? 1 : run_lds_words(PER)];    // end of the run containing each position
     __shared__ uint32_t s_w[8];
     const int tid = threadIdx.x;
-    const int64_t base = (int64_t)blockIdx.x * kRunTile;
+    const int64_t base = (int64_t)blockIdx.x * (256 * PER);
     // the leaf ranges of the tile's records, loaded before the label scans
     // so that their latency overlaps the scans
-    uint32_t rl[kRunPer], rh[kRunPer];
+    uint32_t rl[PER], rh[PER];
 #pragma unroll
-    for (int q = 0; q < kRunPer; ++q) {
+    for (int q = 0; q < PER; ++q) {
         const int64_t k = base + q * 256 + tid;
         rl[q] = k < n - 1 ? rlo[k] : 0u;
         rh[q] = k < n - 1 ? rhi[k] : 0u;
     }
-    for (int x = tid; x < kRunTile + 2; x += 256) {
+    for (int x = tid; x < (256 * PER) + 2; x += 256) {
         int64_t p = base + x - 1;
         p = p < 0 ? 0 : (p >= n ? n - 1 : p);
         s_lab[run_lds(x)] = FIRST ? (uint32_t)p : labels[p];  // first round: a point's label is its position
@@ -1108,11 +1127,11 @@ __global__ __launch_bounds__(256) void k_round_prep(const uint32_t* __restrict__
     }
     __syncthreads();
     if (!FIRST) {
-        // thread tid owns the local positions [kRunPer tid, kRunPer (tid + 1))
-        const int x0 = tid * kRunPer;
+        // thread tid owns the local positions [PER tid, PER (tid + 1))
+        const int x0 = tid * PER;
         uint32_t agg_h = 0u, agg_t = kNone;
 #pragma unroll
-        for (int j = 0; j < kRunPer; ++j) {
+        for (int j = 0; j < PER; ++j) {
             const int x = x0 + j;
             const int64_t p = base + x;
             if (p < n) {
@@ -1124,7 +1143,7 @@ __global__ __launch_bounds__(256) void k_round_prep(const uint32_t* __restrict__
         uint32_t cur = max(block_excl_max256(agg_h, s_w), carry_l);
         const uint32_t cr = min(block_excl_min256_rev(agg_t, s_w + 4), carry_r);
 #pragma unroll
-        for (int j = 0; j < kRunPer; ++j) {
+        for (int j = 0; j < PER; ++j) {
             const int x = x0 + j;
             const int64_t p = base + x;
             if (p < n && (p == 0 || s_lab[run_lds(x)] != s_lab[run_lds(x + 1)])) cur = (uint32_t)p;
@@ -1132,7 +1151,7 @@ __global__ __launch_bounds__(256) void k_round_prep(const uint32_t* __restrict__
         }
         cur = cr;
 #pragma unroll
-        for (int j = kRunPer - 1; j >= 0; --j) {
+        for (int j = PER - 1; j >= 0; --j) {
             const int x = x0 + j;
             const int64_t p = base + x;
             if (p < n && (p == n - 1 || s_lab[run_lds(x + 2)] != s_lab[run_lds(x + 1)])) cur = (uint32_t)p;
@@ -1142,7 +1161,7 @@ __global__ __launch_bounds__(256) void k_round_prep(const uint32_t* __restrict__
     }
     // record labels; record k has the children [rlo[k], k] and [k+1, rhi[k]]
 #pragma unroll
-    for (int q = 0; q < kRunPer; ++q) {
+    for (int q = 0; q < PER; ++q) {
         const int x = q * 256 + tid;
         const int64_t k = base + x;
         if (k < n - 1) {
@@ -1153,7 +1172,7 @@ __global__ __launch_bounds__(256) void k_round_prep(const uint32_t* __restrict__
                 right = hi == (uint32_t)(k + 1);
             } else {
                 left = s_rs[run_lds(x)] <= lo;
-                right = (x + 1 < kRunTile ? s_re[run_lds(x + 1)] : carry_r) >= hi;
+                right = (x + 1 < (256 * PER) ? s_re[run_lds(x + 1)] : carry_r) >= hi;
             }
             lab2[k] = make_uint2(left ? s_lab[run_lds(x + 1)] : kInvalid,
                                  right ? s_lab[run_lds(x + 2)] : kInvalid);
@@ -1163,21 +1182,21 @@ __global__ __launch_bounds__(256) void k_round_prep(const uint32_t* __restrict__
         if (!FIRST && succ && k < n && s_lab[run_lds(x + 1)] == (uint32_t)k) succ[k] = (uint32_t)k;
     }
     if (!FIRST && keep.kept) {
-        uint32_t pj[kRunPer], other[kRunPer];
+        uint32_t pj[PER], other[PER];
 #pragma unroll
-        for (int q = 0; q < kRunPer; ++q) {
+        for (int q = 0; q < PER; ++q) {
             const int64_t k = base + q * 256 + tid;
             pj[q] = k < n ? keep.cand_j[k] : kNone;
         }
 #pragma unroll
-        for (int q = 0; q < kRunPer; ++q) {
+        for (int q = 0; q < PER; ++q) {
             const int64_t k = base + q * 256 + tid;
             other[q] = pj[q] != kNone ? keep.cand_p[k] : 0u;
         }
 #pragma unroll
-        for (int q = 0; q < kRunPer; ++q) other[q] = pj[q] != kNone ? labels[other[q]] : kNone;
+        for (int q = 0; q < PER; ++q) other[q] = pj[q] != kNone ? labels[other[q]] : kNone;
 #pragma unroll
-        for (int q = 0; q < kRunPer; ++q) {
+        for (int q = 0; q < PER; ++q) {
             const int x = q * 256 + tid;
             const int64_t k = base + x;
             const bool valid = k < n;
@@ -1195,9 +1214,9 @@ __global__ __launch_bounds__(256) void k_round_prep(const uint32_t* __restrict__
         }
     }
     if (!BOUNDS) return;
-    uint32_t v[kRunPer];
+    uint32_t v[PER];
 #pragma unroll
-    for (int q = 0; q < kRunPer; ++q) {
+    for (int q = 0; q < PER; ++q) {
         const int x = q * 256 + tid;
         const int64_t k = base + x;
         v[q] = kInfBits;
@@ -1230,7 +1249,7 @@ __global__ __launch_bounds__(256) void k_round_prep(const uint32_t* __restrict__
     }
     if constexpr (FIRST) {
 #pragma unroll
-        for (int q = 0; q < kRunPer; ++q) {
+        for (int q = 0; q < PER; ++q) {
             const int64_t k = base + q * 256 + tid;
             if (k < n) ub[k] = v[q];
         }
@@ -1244,7 +1263,7 @@ __global__ __launch_bounds__(256) void k_round_prep(const uint32_t* __restrict__
         uint32_t* h_val = s_re;
         bool some = false;
 #pragma unroll
-        for (int q = 0; q < kRunPer; ++q) some |= v[q] != kInfBits;
+        for (int q = 0; q < PER; ++q) some |= v[q] != kInfBits;
         // a tile without a component boundary (most tiles of late rounds)
         // has no bound to give
         if (!__syncthreads_or(some)) return;
@@ -1254,7 +1273,7 @@ __global__ __launch_bounds__(256) void k_round_prep(const uint32_t* __restrict__
         }
         __syncthreads();
 #pragma unroll
-        for (int q = 0; q < kRunPer; ++q) {
+        for (int q = 0; q < PER; ++q) {
             const int x = q * 256 + tid;
             const int64_t k = base + x;
             // uniform over the workgroup; a wave without a bound skips its scan
@@ -1263,7 +1282,7 @@ __global__ __launch_bounds__(256) void k_round_prep(const uint32_t* __restrict__
                 bool run_end;
                 const uint32_t m = wave_seg_min<uint32_t>(lab, v[q], &run_end);
                 if (k < n && run_end && m != kInfBits) {
-                    uint32_t h = (lab * 2654435761u) >> (32 - kBoundHashBits);
+                    uint32_t h = (lab * 2654435761u) >> (32 - kHashBits);
                     bool placed = false;
                     for (int probe = 0; probe < 8; ++probe) {
                         const uint32_t old = atomicCAS(&h_lab[h], kNone, lab);
@@ -1294,7 +1313,7 @@ __global__ __launch_bounds__(256) void k_round_prep(const uint32_t* __restrict__
 // run full.  A point whose last result still holds (see k_traverse_fast,
 // REUSE) offers its kept candidate to its component here instead.
 
-// Per tile of kRunTile positions: qflag[i] = 1 for a point that must
+// Per tile of 256 PER positions: qflag[i] = 1 for a point that must
 // search, qcnt[t] = their number.  On entry qflag holds the kept flags of
 // k_round_prep, whose offers are complete by now, so the radius of every
 // component is known: its bound, lowered to the shortest kept candidate
@@ -1303,6 +1322,7 @@ __global__ __launch_bounds__(256) void k_round_prep(const uint32_t* __restrict__
 // that nothing outside its component lies within that radius: an absorbed
 // candidate at D = pd (every point now outside was outside then, so none
 // is nearer), or a search that found nothing within R.
+template <int PER>
 __global__ __launch_bounds__(256) void k_reuse_mark(const uint32_t* __restrict__ labels,
                                                     const uint32_t* __restrict__ ub,
                                                     const uint64_t* __restrict__ compkey,
@@ -1311,10 +1331,10 @@ __global__ __launch_bounds__(256) void k_reuse_mark(const uint32_t* __restrict__
                                                     int64_t n, const Ctrl* ctrl) {
     if (ctrl->done) return;
     __shared__ uint32_t s_w[4];
-    const int64_t base = (int64_t)blockIdx.x * kRunTile;
-    uint32_t c[kRunPer], pj[kRunPer], pd[kRunPer], kp[kRunPer], radius[kRunPer];
+    const int64_t base = (int64_t)blockIdx.x * (256 * PER);
+    uint32_t c[PER], pj[PER], pd[PER], kp[PER], radius[PER];
 #pragma unroll
-    for (int q = 0; q < kRunPer; ++q) {
+    for (int q = 0; q < PER; ++q) {
         const int64_t i = base + q * 256 + threadIdx.x;
         const bool valid = i < n;
         c[q] = valid ? labels[i] : kNone;
@@ -1324,7 +1344,7 @@ __global__ __launch_bounds__(256) void k_reuse_mark(const uint32_t* __restrict__
     }
     const bool tight = tight_radius(ctrl, n);
 #pragma unroll
-    for (int q = 0; q < kRunPer; ++q) {
+    for (int q = 0; q < PER; ++q) {
         radius[q] = 0u;
         if (c[q] != kNone && !kp[q]) {
             const uint64_t ck = tight ? compkey[c[q]] : kKeyMax;
@@ -1333,7 +1353,7 @@ __global__ __launch_bounds__(256) void k_reuse_mark(const uint32_t* __restrict__
     }
     uint32_t cnt = 0;
 #pragma unroll
-    for (int q = 0; q < kRunPer; ++q) {
+    for (int q = 0; q < PER; ++q) {
         const int64_t i = base + q * 256 + threadIdx.x;
         if (i >= n) continue;
         bool need = false;
@@ -1391,6 +1411,7 @@ __global__ __launch_bounds__(1024) void k_qlist_scan(const uint32_t* __restrict_
 // qlist[qoff[t] + k] = the k-th flagged position of tile t, in order.  With
 // fold_cnt, a workgroup sums the tile counts before its own tile itself
 // (qoff unused), and workgroup 0 stores the total in ctrl->qcount.
+template <int PER>
 __global__ __launch_bounds__(256) void k_qlist_write(const uint8_t* __restrict__ qflag,
                                                      const uint32_t* __restrict__ qoff, int64_t n,
                                                      uint32_t* __restrict__ qlist, Ctrl* ctrl,
@@ -1412,12 +1433,12 @@ __global__ __launch_bounds__(256) void k_qlist_write(const uint8_t* __restrict__
     } else {
         off = qoff[blockIdx.x];
     }
-    const int64_t base = (int64_t)blockIdx.x * kRunTile;
-    const int64_t x0 = base + (int64_t)threadIdx.x * kRunPer;  // this thread's kRunPer consecutive positions
-    uint32_t f[kRunPer];
+    const int64_t base = (int64_t)blockIdx.x * (256 * PER);
+    const int64_t x0 = base + (int64_t)threadIdx.x * PER;  // this thread's PER consecutive positions
+    uint32_t f[PER];
     uint32_t cnt = 0;
 #pragma unroll
-    for (int j = 0; j < kRunPer; ++j) {
+    for (int j = 0; j < PER; ++j) {
         f[j] = x0 + j < n ? qflag[x0 + j] : 0u;
         cnt += f[j];
     }
@@ -1434,7 +1455,7 @@ __global__ __launch_bounds__(256) void k_qlist_write(const uint8_t* __restrict__
     uint32_t at = off + inc - cnt;
     for (int k = 0; k < w; ++k) at += s_w[k];
 #pragma unroll
-    for (int j = 0; j < kRunPer; ++j)
+    for (int j = 0; j < PER; ++j)
         if (f[j]) qlist[at++] = (uint32_t)(x0 + j);
 }
 
@@ -1632,11 +1653,12 @@ __global__ __launch_bounds__(256) void k_merge_jump(const uint32_t* __restrict__
 // so that every kernel of a round already queued behind this one returns
 // at once (this kernel itself always runs: on a finished loop it rewrites
 // the same labels).
+template <int PER>
 __global__ __launch_bounds__(256) void k_relabel(uint32_t* labels, const uint32_t* __restrict__ par, int64_t n,
                                                  int steps, uint32_t* __restrict__ tile_part,
                                                  const uint2* __restrict__ part, int nparts, Ctrl* ctrl,
                                                  int64_t target) {
-    __shared__ uint32_t s_new[kRunLds];
+    __shared__ uint32_t s_new[run_lds_words(PER)];
     __shared__ uint32_t s_w[8];
     const int tid = threadIdx.x;
     if (blockIdx.x == 0) {
@@ -1665,31 +1687,31 @@ __global__ __launch_bounds__(256) void k_relabel(uint32_t* labels, const uint32_
         }
         __syncthreads();
     }
-    const int64_t base = (int64_t)blockIdx.x * kRunTile;
-    // thread 0 also follows position base-1, thread 1 position base+kRunTile
-    const int64_t hp = tid == 0 ? base - 1 : (tid == 1 ? base + kRunTile : -1);
+    const int64_t base = (int64_t)blockIdx.x * (256 * PER);
+    // thread 0 also follows position base-1, thread 1 position base+(256 * PER)
+    const int64_t hp = tid == 0 ? base - 1 : (tid == 1 ? base + (256 * PER) : -1);
     const bool halo = hp >= 0 && hp < n;
-    uint32_t r[kRunPer];
+    uint32_t r[PER];
     uint32_t h = halo ? labels[hp] : 0u;
 #pragma unroll
-    for (int q = 0; q < kRunPer; ++q) {
+    for (int q = 0; q < PER; ++q) {
         const int64_t p = base + (int64_t)q * 256 + tid;
         r[q] = p < n ? labels[p] : 0u;
     }
 #pragma unroll
-    for (int q = 0; q < kRunPer; ++q)
+    for (int q = 0; q < PER; ++q)
         if (base + (int64_t)q * 256 + tid < n) r[q] = par[r[q]];
     if (halo) h = par[h];
     // finish the chains in lockstep: one batch of independent loads per hop
     bool more = true;
     for (int it = 0; it < steps && more; ++it) {
         more = false;
-        uint32_t rr[kRunPer];
+        uint32_t rr[PER];
 #pragma unroll
-        for (int q = 0; q < kRunPer; ++q) rr[q] = (base + (int64_t)q * 256 + tid < n) ? par[r[q]] : r[q];
+        for (int q = 0; q < PER; ++q) rr[q] = (base + (int64_t)q * 256 + tid < n) ? par[r[q]] : r[q];
         const uint32_t hh = halo ? par[h] : h;
 #pragma unroll
-        for (int q = 0; q < kRunPer; ++q) {
+        for (int q = 0; q < PER; ++q) {
             more |= rr[q] != r[q];
             r[q] = rr[q];
         }
@@ -1698,17 +1720,17 @@ __global__ __launch_bounds__(256) void k_relabel(uint32_t* labels, const uint32_
     }
     if (more) atomicOr(&ctrl->error, kErrJump);
 #pragma unroll
-    for (int q = 0; q < kRunPer; ++q) {
+    for (int q = 0; q < PER; ++q) {
         const int x = q * 256 + tid;
         if (base + x < n) labels[base + x] = r[q];
         s_new[run_lds(x + 1)] = r[q];
     }
     if (tid == 0) s_new[run_lds(0)] = h;
-    if (tid == 1) s_new[run_lds(kRunTile + 1)] = h;
+    if (tid == 1) s_new[run_lds((256 * PER) + 1)] = h;
     __syncthreads();
     uint32_t hmax = 0u, tmin = kNone;
 #pragma unroll
-    for (int q = 0; q < kRunPer; ++q) {
+    for (int q = 0; q < PER; ++q) {
         const int x = q * 256 + tid;
         const int64_t p = base + x;
         if (p < n) {
@@ -2472,10 +2494,10 @@ bool extent_ok(const float* lo, const float* hi, int dim) {
 // The record labels of arbitrary labels (no bounds).
 hipError_t propagate_labels(const uint32_t* labels, uint32_t* run_part, uint32_t* run_carry, const uint32_t* rlo,
                             const uint32_t* rhi, uint2* lab2, int64_t n, Ctrl* ctrl, hipStream_t st) {
-    const int nb = run_tiles(n);
-    k_run_partials<<<nb, 256, 0, st>>>(labels, n, run_part);
+    const int nb = run_tiles(n, kRunPer);
+    k_run_partials<kRunPer><<<nb, 256, 0, st>>>(labels, n, run_part);
     k_tile_carries<<<1, 1024, 0, st>>>(run_part, nb, run_carry, ctrl);
-    k_round_prep<3, false, false><<<nb, 256, 0, st>>>(labels, run_carry, rlo, rhi, lab2, nullptr, nullptr, nullptr,
+    k_round_prep<3, false, false, kRunPer><<<nb, 256, 0, st>>>(labels, run_carry, rlo, rhi, lab2, nullptr, nullptr, nullptr,
                                                       n, nullptr, ctrl, nullptr, nb, KeepArgs{}, nullptr);
     return hipGetLastError();
 }
@@ -2505,7 +2527,7 @@ struct Bufs {
 };
 
 template <int DIM>
-Bufs<DIM> carve(char* ws, const Layout& L) {
+Bufs<DIM> carve(char* ws, const Layout& L, int64_t n) {
     Bufs<DIM> b;
     b.ctrl = reinterpret_cast<Ctrl*>(ws + L.ctrl);
     b.bpart = reinterpret_cast<uint32_t*>(ws + L.bpart);
@@ -2530,6 +2552,12 @@ Bufs<DIM> carve(char* ws, const Layout& L) {
     b.run_carry = reinterpret_cast<uint32_t*>(ws + L.run_carry);
     b.qcnt = reinterpret_cast<uint32_t*>(ws + L.qcnt);
     b.qoff = reinterpret_cast<uint32_t*>(ws + L.qoff);
+    if (run_per(n) < kRunPer) {
+        // more tiles than these arrays have room for: the sort's histogram is
+        // free during the rounds (no scan kernel runs, so no carries either)
+        b.run_part = b.hist;
+        b.qcnt = b.hist + 2 * kFoldTiles;
+    }
     b.qflag = reinterpret_cast<uint8_t*>(ws + L.qflag);
     b.qlist = reinterpret_cast<uint32_t*>(ws + L.qlist);
     b.labels = reinterpret_cast<uint32_t*>(ws + L.labels);
@@ -2630,23 +2658,24 @@ int enqueue_round(emst_ctx* ctx, Bufs<DIM>& b, TraverseArgs<DIM>& ta, int64_t n,
     hipEvent_t* E = ctx->ev;
     // record labels and bounds; the run partials of round r > 0 come from
     // the relabel kernel of round r - 1
-    const int nt = run_tiles(n);
+    const int per = run_per(n), nt = run_tiles(n, per);
     const bool fold = nt <= kFoldTiles;  // scans folded into their consumers
     // variant 13 from the third round on: kept candidates are offered here
     // (in round 1 none is kept: every point joined its candidate's
     // component in round 0)
     const bool keep = variant == 13 && round >= 2;
     const KeepArgs ka = keep ? KeepArgs{b.cand_d, b.cand_j, b.cand_p, b.orig, b.compkey, b.qflag} : KeepArgs{};
-    if (round == 0) {
-        k_round_prep<DIM, true, true><<<nt, 256, 0, st>>>(b.labels, b.run_carry, b.rlo, b.rhi, b.lab2, b.spts,
-                                                          cloud_of, ta.core_s, n, b.ub, b.ctrl, nullptr, nt, ka,
-                                                          b.succ);
-    } else {
-        if (!fold) k_tile_carries<<<1, 1024, 0, st>>>(b.run_part, nt, b.run_carry, b.ctrl);
-        k_round_prep<DIM, false, true><<<nt, 256, 0, st>>>(b.labels, b.run_carry, b.rlo, b.rhi, b.lab2, b.spts,
-                                                           cloud_of, ta.core_s, n, b.ub, b.ctrl,
-                                                           fold ? b.run_part : nullptr, nt, ka, b.succ);
-    }
+    if (round > 0 && !fold) k_tile_carries<<<1, 1024, 0, st>>>(b.run_part, nt, b.run_carry, b.ctrl);
+    with_run_per(per, [&](auto P) {
+        if (round == 0)
+            k_round_prep<DIM, true, true, P.value><<<nt, 256, 0, st>>>(b.labels, b.run_carry, b.rlo, b.rhi, b.lab2,
+                                                                       b.spts, cloud_of, ta.core_s, n, b.ub, b.ctrl,
+                                                                       nullptr, nt, ka, b.succ);
+        else
+            k_round_prep<DIM, false, true, P.value><<<nt, 256, 0, st>>>(
+                b.labels, b.run_carry, b.rlo, b.rhi, b.lab2, b.spts, cloud_of, ta.core_s, n, b.ub, b.ctrl,
+                fold ? b.run_part : nullptr, nt, ka, b.succ);
+    });
     ta.first = round == 0;
     ta.all_absorbed = round == 1;
     ta.kept = keep ? b.qflag : nullptr;
@@ -2654,10 +2683,13 @@ int enqueue_round(emst_ctx* ctx, Bufs<DIM>& b, TraverseArgs<DIM>& ta, int64_t n,
     ta.qlist = nullptr;
     if (uses_qlist(variant, round, n)) {
         ta.kept = nullptr;
-        k_reuse_mark<<<nt, 256, 0, st>>>(b.labels, b.ub, b.compkey, b.cand_d, b.cand_j, b.qflag, b.qcnt, n,
-                                         b.ctrl);
-        if (!fold) k_qlist_scan<<<1, 1024, 0, st>>>(b.qcnt, nt, b.qoff, b.ctrl);
-        k_qlist_write<<<nt, 256, 0, st>>>(b.qflag, b.qoff, n, b.qlist, b.ctrl, fold ? b.qcnt : nullptr, nt);
+        with_run_per(per, [&](auto P) {
+            k_reuse_mark<P.value><<<nt, 256, 0, st>>>(b.labels, b.ub, b.compkey, b.cand_d, b.cand_j, b.qflag, b.qcnt,
+                                                      n, b.ctrl);
+            if (!fold) k_qlist_scan<<<1, 1024, 0, st>>>(b.qcnt, nt, b.qoff, b.ctrl);
+            k_qlist_write<P.value><<<nt, 256, 0, st>>>(b.qflag, b.qoff, n, b.qlist, b.ctrl, fold ? b.qcnt : nullptr,
+                                                       nt);
+        });
         HIP_TRY(hipGetLastError());
         ta.qlist = b.qlist;
     }
@@ -2701,8 +2733,10 @@ int enqueue_round(emst_ctx* ctx, Bufs<DIM>& b, TraverseArgs<DIM>& ta, int64_t n,
                                               cloud_of != nullptr);
     HIP_TRY(hipGetLastError());
     k_merge_jump<<<merge_grid, 256, 0, st>>>(b.labels, b.par, n, 1024, b.ctrl, first, rl);
-    k_relabel<<<nt, 256, 0, st>>>(b.labels, b.par, n, 4096, b.run_part, reinterpret_cast<const uint2*>(b.bpart),
-                                  mp_blocks, b.ctrl, target);
+    with_run_per(per, [&](auto P) {
+        k_relabel<P.value><<<nt, 256, 0, st>>>(b.labels, b.par, n, 4096, b.run_part,
+                                               reinterpret_cast<const uint2*>(b.bpart), mp_blocks, b.ctrl, target);
+    });
     HIP_TRY(hipGetLastError());
     return EMST_OK;
 }
@@ -3097,7 +3131,7 @@ template <int DIM>
 int job_enqueue(emst_ctx* ctx, Job& j, hipStream_t st) {
     const int64_t n = j.n;
     const Layout L = make_layout(n, DIM);
-    Bufs<DIM> b = carve<DIM>(j.ws, L);
+    Bufs<DIM> b = carve<DIM>(j.ws, L, j.n);
     hipEvent_t* E = ctx->ev;  // E[0..3] phases, E[8 + 2r], E[9 + 2r] traversal of round r
     switch (j.phase) {
     case kPhTree: {  // validation + scene box, Morton codes, sort, hierarchy
@@ -3259,7 +3293,7 @@ int job_rounds(emst_ctx* ctx, Job& j, hipStream_t st) {
     Ctrl* mirror[2] = {ctx->h_ctrl, ctx->h_ctrl + 1};
     HIP_TRY(hipEventRecord(ctx->sev[0], st));
     const Layout L = make_layout(j.n, DIM);
-    Bufs<DIM> b = carve<DIM>(j.ws, L);
+    Bufs<DIM> b = carve<DIM>(j.ws, L, j.n);
     TraverseArgs<DIM> ta = job_args<DIM>(j, b);
     auto queue = [&](int r) -> int {
         if (int rc = enqueue_round<DIM>(ctx, b, ta, j.n, r, j.height, j.variant, nullptr, 1, j.prof, st)) return rc;
@@ -3337,7 +3371,7 @@ int flat_impl(emst_ctx* ctx, const float* pts, int64_t n, int32_t* edges, float*
     const bool prof = ctx->profiling && ctx->ev_ok;
     hipEvent_t* E = ctx->ev;
     const Layout L = make_layout(n, DIM);
-    Bufs<DIM> b = carve<DIM>(ws, L);
+    Bufs<DIM> b = carve<DIM>(ws, L, n);
     // whole tiles of points, in the sort's histogram (the smallest of which
     // holds 65,600)
     float4* spts = reinterpret_cast<float4*>(b.hist);
@@ -3439,7 +3473,7 @@ int batched_impl(emst_ctx* ctx, const float* pts, const int64_t* h_offsets, cons
                  int32_t* edges, float* weights, float* d2, int64_t* h_edge_offsets, char* ws, hipStream_t st) {
     const int64_t n = h_offsets[B];
     const BatchLayout BL = make_batch_layout(n, B);
-    Bufs<3> b = carve<3>(ws, BL.base);
+    Bufs<3> b = carve<3>(ws, BL.base, n);
     float* pts3 = reinterpret_cast<float*>(ws + BL.pts3);
     uint32_t* cloud_of = reinterpret_cast<uint32_t*>(ws + BL.cloud_of);
     uint32_t* cloud_sorted = reinterpret_cast<uint32_t*>(ws + BL.cloud_sorted);
@@ -3714,7 +3748,7 @@ struct BatchBufs {
 static BatchBufs batch_bufs(char* ws, int64_t n, int32_t B) {
     const BatchLayout BL = make_batch_layout(n, B);
     BatchBufs x;
-    x.b = carve<3>(ws, BL.base);
+    x.b = carve<3>(ws, BL.base, n);
     x.pts3 = reinterpret_cast<float*>(ws + BL.pts3);
     x.cloud_of = reinterpret_cast<uint32_t*>(ws + BL.cloud_of);
     x.cloud_sorted = reinterpret_cast<uint32_t*>(ws + BL.cloud_sorted);
@@ -4652,13 +4686,16 @@ int test_round(emst_ctx* ctx, const float* pts, int64_t n, const int32_t* comp, 
     j.variant = variant;
     if (int rc = job_run<DIM>(ctx, j, st)) return rc;
     const Layout L = make_layout(n, DIM);
-    Bufs<DIM> b = carve<DIM>(ws, L);
+    Bufs<DIM> b = carve<DIM>(ws, L, n);
     TraverseArgs<DIM> ta = job_args<DIM>(j, b);
     k_fill_u32<<<grid_for(n), 256, 0, st>>>(b.succ, n, kNone);
     k_test_reps<<<grid_for(n), 256, 0, st>>>(comp, b.orig, n, b.succ);
     k_test_labels<<<grid_for(n), 256, 0, st>>>(comp, b.orig, b.succ, n, b.labels, b.ub, b.compkey, b.compmax,
                                                b.cand_d, b.cand_j, b.cand_p);
-    k_run_partials<<<run_tiles(n), 256, 0, st>>>(b.labels, n, b.run_part);
+    const int per = run_per(n);
+    with_run_per(per, [&](auto P) {
+        k_run_partials<P.value><<<run_tiles(n, per), 256, 0, st>>>(b.labels, n, b.run_part);
+    });
     RootList rl;
     uint32_t* lists[2] = {reinterpret_cast<uint32_t*>(b.k0), reinterpret_cast<uint32_t*>(b.k1)};
     uint32_t* counts = b.bpart + 4 * kPartBlocks;
@@ -4850,7 +4887,7 @@ extern "C" int emst_test_tree_boxes(emst_ctx* ctx, const float* d_points, int64_
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     char* ws = (char*)d_workspace;
     const Layout L = make_layout(n, 3);
-    Bufs<3> b = carve<3>(ws, L);
+    Bufs<3> b = carve<3>(ws, L, n);
     HIP_TRY(launch_bbox<3>(d_points, n, b.bpart, b.ctrl, st));
     HIP_TRY(hipGetLastError());
     if (int rc = read_ctrl(ctx, b.ctrl, st)) return rc;
