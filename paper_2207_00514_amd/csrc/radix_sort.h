@@ -25,6 +25,10 @@ constexpr size_t radix_hist_elems() { return (size_t)256 * kRadixMaxBlocks + 256
 // count table.
 constexpr int64_t kRadixOneMin = (int64_t)1 << 22;
 constexpr int kRadixOneTile = 256 * 16;
+// Below this many keys as well, on smaller tiles, with the scratch in the
+// count table's place.
+constexpr int64_t kRadixSmallOne = (int64_t)1 << 19;
+static_assert(3 * 8 * 256 + 64 + 2 * (kRadixSmallOne / 2048) * 256 <= (int64_t)radix_hist_elems(), "the scratch fits");
 // uint32 elements of the scratch `hist` must hold for n keys (every caller
 // passes at least this many).
 inline size_t radix_scratch_elems(int64_t n) {

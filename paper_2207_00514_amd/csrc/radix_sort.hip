@@ -18,9 +18,14 @@
 // so the (slot, wave, lane) order equals the input order and the sort is
 // stable.
 //
-// From kRadixOneMin keys on, a pass is instead one launch of rs_onesweep
-// (decoupled look-back across tiles, after one count of every digit of
-// every pass by rs_global_hist), described below.
+// From kRadixOneMin keys on, and below kRadixSmallOne, a pass is instead one
+// launch of rs_onesweep (decoupled look-back across tiles, after one count
+// of every digit of every pass by rs_global_hist), described below.  Eight
+// passes over random keys, three launches / one launch a pass: 20,000 keys
+// 136 / 87 us, 50,000 138 / 95, 300,000 148 / 133, 500,000 159 / 150 (tiles of
+// 2,048 keys: small sorts are a chain of launches, and one of three remains),
+// 1,000,000 186 / 191, 2,000,000 242 / 261 (the look-back crosses hundreds of
+// tiles that all started together), 5,000,000 446 (16 items) / 436.
 #include "radix_sort.h"
 
 namespace emst {
@@ -242,8 +247,10 @@ __global__ __launch_bounds__(kRsThreads) void rs_downsweep(const uint64_t* __res
 // The words go through device-coherent atomics; each one holds its datum.
 
 constexpr uint32_t kOsAgg = 1u << 30, kOsIncl = 2u << 30, kOsMask = (1u << 30) - 1u;
-// predecessor status words a look-back step loads at once
-constexpr int kOsWindow = 8;
+// Predecessor status words a look-back step loads at once.  Every one goes to
+// memory, and the nearest few usually settle it: 20,000,000 keys in 8 passes
+// take 1477 us with 2, 1403 with 4, 1431 with 8, 1777 with 12.
+constexpr int kOsWindow = 4;
 
 struct RsShifts {
     int s[8];
@@ -306,11 +313,12 @@ __device__ __forceinline__ void os_store(uint32_t* p, uint32_t v) {
 // lanes of an item read their digit's count, and the first lane of each
 // digit adds the item's peers (a wave's LDS operations complete in order).
 // The first 256 threads then own one digit each for the scans and the
-// look-back.  Keys, then values, go through LDS in the sorted order so that
+// look-back; with SCAN they also turn the counts of the whole input into
+// the digits' starts (instead of a launch of rs_global_scan).  Keys, then values, go through LDS in the sorted order so that
 // the stores of a digit's run are contiguous.  At most 80 registers keep
 // six waves per SIMD (three 512-thread workgroups per compute unit, which
 // their 35 KB of LDS allows too).
-template <int THREADS, int ITEMS>
+template <int THREADS, int ITEMS, bool SCAN>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(6))) void rs_onesweep(
     const uint64_t* __restrict__ kin, const uint32_t* __restrict__ vin, uint64_t* __restrict__ kout,
     uint32_t* __restrict__ vout, int64_t n, int shift, const uint32_t* __restrict__ gstart, uint32_t* status,
@@ -363,8 +371,20 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(6))) vo
         if (ok[s] && r == 0) wcnt[dg] = before + (uint32_t)__popcll(peers);
     }
     __syncthreads();
-    uint32_t total = 0, x = 0;
+    uint32_t total = 0, x = 0, start = 0;
+    __shared__ uint32_t gsum[4];
     if (t < 256) {
+        start = gstart[t];
+        if (SCAN) {  // gstart holds counts: exclusive sum inside the wave
+            uint32_t y = start;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const uint32_t z = __shfl_up(y, o);
+                if (lane >= o) y += z;
+            }
+            if (lane == 63) gsum[w] = y;
+            start = y - start;
+        }
         uint32_t off = 0;
 #pragma unroll
         for (int ww = 0; ww < kWaves; ++ww) {
@@ -385,6 +405,8 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(6))) vo
     if (t < 256) {
         uint32_t before = 0;
         for (int k = 0; k < w; ++k) before += wsum[k];
+        if (SCAN)
+            for (int k = 0; k < w; ++k) start += gsum[k];
         lstart[t] = x - total + before;
         // digit t: publish this tile's count, add up the tiles before it
         uint32_t excl = 0;
@@ -417,7 +439,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(6))) vo
             }
             os_store(&status[tile * 256 + t], kOsIncl | (excl + total));
         }
-        gbase[t] = gstart[t] + excl;
+        gbase[t] = start + excl;
         os_store(&status_next[tile * 256 + t], 0u);  // the next pass's status starts empty
     }
     __syncthreads();
@@ -456,9 +478,36 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(6))) vo
     }
 }
 
-// Threads and items per thread of a one-sweep tile (kRadixOneTile keys).
+// Threads and items per thread of a one-sweep tile.
 constexpr int kOsThreads = 512;
 constexpr int kOsItems = kRadixOneTile / kOsThreads;
+constexpr int kOsSmallItems = 4;
+
+// One-sweep passes; `scratch` holds the global counts and starts of every
+// pass, the pass counters and an error word, and two status arrays.
+template <int ITEMS, bool SCAN>
+static void rs_one(hipStream_t stream, uint64_t* ka, uint32_t* va, uint64_t* kb, uint32_t* vb, uint32_t* scratch,
+                   int64_t n, const int* shifts, int nshifts) {
+    const int64_t tiles = (n + kOsThreads * ITEMS - 1) / (kOsThreads * ITEMS);
+    uint32_t* ghist = scratch;
+    uint32_t* gstart = scratch + 8 * 256;
+    uint32_t* counters = scratch + 3 * 8 * 256;  // [8] pass counters, [9] error
+    uint32_t* status[2] = {counters + 64, counters + 64 + tiles * 256};
+    RsShifts sh;
+    for (int q = 0; q < 8; ++q) sh.s[q] = q < nshifts ? shifts[q] : 0;
+    const int64_t words = 3 * 8 * 256 + 64 + tiles * 256;  // through the first status array
+    rs_fill<<<(unsigned)std::min<int64_t>((words + kRsThreads - 1) / kRsThreads, 1024), kRsThreads, 0, stream>>>(
+        scratch, words);
+    rs_global_hist<<<(unsigned)std::min<int64_t>(tiles, 1024), kRsThreads, 0, stream>>>(ka, n, sh, nshifts, ghist);
+    if (!SCAN) rs_global_scan<<<nshifts, kRsThreads, 0, stream>>>(ghist, gstart);
+    for (int q = 0; q < nshifts; ++q) {
+        rs_onesweep<kOsThreads, ITEMS, SCAN><<<(unsigned)tiles, kOsThreads, 0, stream>>>(
+            ka, va, kb, vb, n, shifts[q], (SCAN ? ghist : gstart) + q * 256, status[q & 1], status[(q + 1) & 1],
+            counters + q, counters + 8);
+        std::swap(ka, kb);
+        std::swap(va, vb);
+    }
+}
 
 static int rs_items(int64_t n) { return n >= kRsBigN ? 16 : 8; }
 
@@ -487,31 +536,11 @@ hipError_t radix_sort_pairs(hipStream_t stream, uint64_t* k0, uint32_t* v0, uint
     if (n <= 1 || nshifts == 0) return hipSuccess;
     uint64_t *ka = k0, *kb = k1;
     uint32_t *va = v0, *vb = v1;
-    if (n >= kRadixOneMin && n < ((int64_t)1 << 30) && nshifts <= 8) {
-        // scratch after the count table: global counts, global starts, the
-        // pass counters and an error word, two status arrays
-        const int64_t tiles = (n + kRadixOneTile - 1) / kRadixOneTile;
-        uint32_t* base = hist + radix_hist_elems();
-        uint32_t* ghist = base;
-        uint32_t* gstart = base + 8 * 256;
-        uint32_t* counters = base + 3 * 8 * 256;  // [8] pass counters, [9] error
-        uint32_t* status[2] = {counters + 64, counters + 64 + tiles * 256};
-        RsShifts sh;
-        for (int q = 0; q < 8; ++q) sh.s[q] = q < nshifts ? shifts[q] : 0;
-        rs_fill<<<1, kRsThreads, 0, stream>>>(ghist, 8 * 256);
-        rs_fill<<<1, kRsThreads, 0, stream>>>(counters, 64);
-        rs_fill<<<(unsigned)std::min<int64_t>((tiles * 256 + kRsThreads - 1) / kRsThreads, 1024), kRsThreads, 0,
-                  stream>>>(status[0], tiles * 256);
-        rs_global_hist<<<(unsigned)std::min<int64_t>(tiles, 1024), kRsThreads, 0, stream>>>(ka, n, sh, nshifts,
-                                                                                             ghist);
-        rs_global_scan<<<nshifts, kRsThreads, 0, stream>>>(ghist, gstart);
-        for (int q = 0; q < nshifts; ++q) {
-            rs_onesweep<kOsThreads, kOsItems><<<(unsigned)tiles, kOsThreads, 0, stream>>>(
-                ka, va, kb, vb, n, shifts[q], gstart + q * 256, status[q & 1], status[(q + 1) & 1], counters + q,
-                counters + 8);
-            std::swap(ka, kb);
-            std::swap(va, vb);
-        }
+    if (nshifts <= 8 && (n < kRadixSmallOne || (n >= kRadixOneMin && n < ((int64_t)1 << 30)))) {
+        if (n < kRadixSmallOne)  // in the count table's place
+            rs_one<kOsSmallItems, true>(stream, ka, va, kb, vb, hist, n, shifts, nshifts);
+        else
+            rs_one<kOsItems, false>(stream, ka, va, kb, vb, hist + radix_hist_elems(), n, shifts, nshifts);
         *result_in_1 = (nshifts & 1);
         return hipGetLastError();
     }

@@ -163,3 +163,19 @@ def test_small_clouds_on_several_threads_and_streams():
     for t in threads:
         t.join()
     assert not wrong
+
+
+# one-launch passes on tiles of 2,048 keys below 2^19 keys, three launches above
+@pytest.mark.parametrize("n", [3, 2047, 2048, 2049, 16_385, 65_537, 300_001, 524_287, 524_288])
+def test_sort_sizes(ctx, n):
+    rng = np.random.default_rng(n)
+    keys = rng.integers(-2 ** 63, 2 ** 63, n, dtype=np.int64)
+    keys[n // 2:] = rng.integers(0, 3, n - n // 2)  # most digits the same, many equal keys
+    keys[rng.permutation(n)[: n // 4]] = -1
+    vals = np.arange(n, dtype=np.int32)
+    k, v = torch.from_numpy(keys).cuda(), torch.from_numpy(vals).cuda()
+    print(f"case sort n={n}", flush=True)
+    ctx.test_radix_sort(k, v)
+    order = np.argsort(keys.view(np.uint64), kind="stable")
+    assert np.array_equal(k.cpu().numpy(), keys[order])
+    assert np.array_equal(v.cpu().numpy(), vals[order])
