@@ -2167,7 +2167,7 @@ __global__ __launch_bounds__(256) void k_batch_edge_write(const uint4* __restric
 // workspace layout
 
 struct Layout {
-    size_t ctrl, bpart, k0, k1, v0, v1, hist, spts, orig, cand_p, recs, lab2, height, node_parent, leaf_parent, up, exch, rlo, rhi, run_part, run_carry, qcnt, qoff, qflag, qlist, labels, ub, compkey, compmax, succ, par, cand_d, cand_j, eud, core_s, core_o, total;
+    size_t ctrl, bpart, k0, k1, v0, v1, hist, spts, orig, cand_p, recs, lab2, height, node_parent, leaf_parent, up, exch, rlo, rhi, run_part, run_carry, qcnt, qoff, qflag, qlist, labels, ub, compkey, compmax, succ, par, cand_d, cand_j, eud, core_s, spare, total;
 };
 
 static size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -2233,7 +2233,7 @@ static Layout make_layout(int64_t n, int dim) {
     L.cand_j = take(4 * N);
     L.eud = take(16 * N);
     L.core_s = take(4 * N);
-    L.core_o = take(4 * N);
+    L.spare = take(4 * N);  // (keeps emst_workspace_bytes what it was)
     L.total = o;
     return L;
 }
@@ -2523,7 +2523,7 @@ struct Bufs {
     uint64_t* compkey;
     uint32_t *compmax, *succ, *par, *cand_d, *cand_j;
     uint4* eud;
-    float *core_s, *core_o;
+    float* core_s;
 };
 
 template <int DIM>
@@ -2570,7 +2570,6 @@ Bufs<DIM> carve(char* ws, const Layout& L, int64_t n) {
     b.cand_j = reinterpret_cast<uint32_t*>(ws + L.cand_j);
     b.eud = reinterpret_cast<uint4*>(ws + L.eud);
     b.core_s = reinterpret_cast<float*>(ws + L.core_s);
-    b.core_o = reinterpret_cast<float*>(ws + L.core_o);
     return b;
 }
 
@@ -2583,7 +2582,6 @@ TraverseArgs<DIM> traverse_args(const Bufs<DIM>& b, int64_t n, uint32_t root) {
     ta.cloud_of = nullptr; ta.cloud_root = nullptr; ta.lab2 = b.lab2;
     ta.wave_lca = reinterpret_cast<const uint32_t*>(b.exch);  // the build's exchange words are free by now
     ta.core_s = nullptr;
-    ta.core_o = nullptr;
     ta.cand_p = b.cand_p;
     ta.succ = b.succ;
     ta.qlist = nullptr;
@@ -3121,7 +3119,6 @@ static TraverseArgs<DIM> job_args(const Job& j, const Bufs<DIM>& b) {
     ta.lds_depth = j.lds_depth;
     if (j.k_pts >= 2) {
         ta.core_s = b.core_s;
-        ta.core_o = b.core_o;
     }
     return ta;
 }
@@ -3177,7 +3174,7 @@ int job_enqueue(emst_ctx* ctx, Job& j, hipStream_t st) {
         HIP_TRY(hipGetLastError());
         TraverseArgs<DIM> ta = job_args<DIM>(j, b);
         if (j.k_pts >= 2) {
-            HIP_TRY(launch_core<DIM>(ta, j.height, j.k_pts, b.core_s, b.core_o, j.core_out, st));
+            HIP_TRY(launch_core<DIM>(ta, j.height, j.k_pts, b.core_s, j.core_out, st));
         } else if (j.k_pts == 1 && j.core_out) {
             k_fill_u32<<<grid_for(n), 256, 0, st>>>(reinterpret_cast<uint32_t*>(j.core_out), n, 0u);
             HIP_TRY(hipGetLastError());

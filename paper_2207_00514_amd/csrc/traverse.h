@@ -45,10 +45,9 @@ struct TraverseArgs {
     // per wave of 64 Morton-consecutive queries: the lowest common ancestor
     // of their leaves (one cloud only)
     const uint32_t* wave_lca;
-    // mutual reachability: squared core distances by sorted position and by
-    // original index (null for the Euclidean tree)
+    // mutual reachability: squared core distances by sorted position (null
+    // for the Euclidean tree)
     const float* core_s;
-    const float* core_o;
     // each point's candidate: its sorted position (the leaf children of
     // record k are positions k and k + 1), written with cand_d / cand_j
     uint32_t* cand_p;
@@ -420,9 +419,8 @@ __global__ __launch_bounds__(256) void k_traverse_fast(TraverseArgs<DIM> a) {
             if ((in0 & l0) | (in1 & l1)) {
                 float m0 = d0, m1 = d1;
                 if (MREACH) {  // a leaf box is its point, so d0 / d1 are the exact D
-                    const uint32_t j0 = c0.ref & ~kLeafFlag, j1 = c1.ref & ~kLeafFlag;
-                    const float q0 = (in0 & l0 & (d0 <= radius)) ? a.core_o[j0] : 0.f;
-                    const float q1 = (in1 & l1 & (d1 <= radius)) ? a.core_o[j1] : 0.f;
+                    const float q0 = (in0 & l0 & (d0 <= radius)) ? a.core_s[node] : 0.f;
+                    const float q1 = (in1 & l1 & (d1 <= radius)) ? a.core_s[node + 1u] : 0.f;
                     m0 = fmaxf(fmaxf(core_p, q0), d0);
                     m1 = fmaxf(fmaxf(core_p, q1), d1);
                 }
@@ -494,31 +492,31 @@ __global__ __launch_bounds__(256) void k_traverse_fast(TraverseArgs<DIM> a) {
 // ---------------------------------------------------------------------------
 // Core distances (Section 4, "Mutual reachability distance"): for every
 // sorted position i the k-th smallest D(i, j) over all j, the point itself
-// (D = 0) included.  The k-th smallest D to the sorted positions within k-1
-// of i (at least k points) bounds it from above; the search then keeps the
-// K smallest D of every leaf it reaches in registers (K >= k, only the
-// first k matter), prunes boxes farther than the running k-th value, and
-// starts every wave below the root as variant 10 does.
+// (D = 0) included.  K registers (K >= k) hold the smallest D so far in
+// ascending order; the first K - k start at -inf and stay there, so that the
+// last one always is the k-th smallest.  The sorted positions within k - 1
+// of i (at least k points) come first; the search then takes every other
+// leaf it reaches, prunes boxes farther than the running k-th value, and
+// starts every wave below the root as variant 10 does.  The loop is the one
+// of k_traverse_fast; the insertions, 2 K selects and compares each, run only
+// when some lane meets a leaf within its radius.  Keeping the window's
+// distances instead of finding them again in the search, and the k-th value
+// in a fixed register instead of a select over K every step, took the launch
+// at 2M clustered points from 1466 to 710 us (k = 8), and a whole call from
+// 13.6 to 2.3 ms (k = 30).  Now bound by the record gathers, as
+// k_traverse_fast.
 
+// Inserts d, which must be below best[K - 1], into the ascending list.
 template <int K>
 __device__ __forceinline__ void knn_insert(float (&best)[K], float d) {
-    if (!(d < best[K - 1])) return;
 #pragma unroll
-    for (int q = K - 1; q > 0; --q) best[q] = (d < best[q - 1]) ? best[q - 1] : ((d < best[q]) ? d : best[q]);
-    best[0] = (d < best[0]) ? d : best[0];
-}
-
-template <int K>
-__device__ __forceinline__ float knn_kth(const float (&best)[K], int k) {
-    float r = best[0];
-#pragma unroll
-    for (int q = 1; q < K; ++q) r = (q == k - 1) ? best[q] : r;
-    return r;
+    for (int q = K - 1; q > 0; --q) best[q] = __builtin_amdgcn_fmed3f(best[q - 1], best[q], d);
+    best[0] = fminf(best[0], d);
 }
 
 template <int DIM, int STACK, int K>
 __global__ __launch_bounds__(256) void k_core_dist(TraverseArgs<DIM> a, int k, float* __restrict__ core_s,
-                                                   float* __restrict__ core_o, float* __restrict__ core_out) {
+                                                   float* __restrict__ core_out) {
     constexpr int kDepth = 8;
     __shared__ uint2 lds[kDepth][256];
     const int t = threadIdx.x;
@@ -529,20 +527,18 @@ __global__ __launch_bounds__(256) void k_core_dist(TraverseArgs<DIM> a, int k, f
     for (int c = 0; c < DIM; ++c) p[c] = a.spts[i * DIM + c];
     float best[K];
 #pragma unroll
-    for (int q = 0; q < K; ++q) best[q] = INFINITY;
-    {
-        const int64_t w0 = i - (k - 1) > 0 ? i - (k - 1) : 0;
-        const int64_t w1 = i + (k - 1) < a.n - 1 ? i + (k - 1) : a.n - 1;
-        for (int64_t q = w0; q <= w1; ++q) {
-            float o[DIM];
+    for (int q = 0; q < K; ++q) best[q] = q < K - k ? -INFINITY : INFINITY;
+    // the window [w0, w0 + span], clipped to the cloud
+    const uint32_t w0 = (uint32_t)(i - (k - 1) > 0 ? i - (k - 1) : 0);
+    const uint32_t span = (uint32_t)(i + (k - 1) < a.n - 1 ? i + (k - 1) : a.n - 1) - w0;
+    for (uint32_t q = 0; q <= span; ++q) {
+        float o[DIM];
 #pragma unroll
-            for (int c = 0; c < DIM; ++c) o[c] = a.spts[q * DIM + c];
-            knn_insert<K>(best, sqdist<DIM>(p, o));
-        }
+        for (int c = 0; c < DIM; ++c) o[c] = a.spts[(int64_t)(w0 + q) * DIM + c];
+        const float d = sqdist<DIM>(p, o);
+        if (d < best[K - 1]) knn_insert<K>(best, d);
     }
-    float radius = knn_kth<K>(best, k);
-#pragma unroll
-    for (int q = 0; q < K; ++q) best[q] = INFINITY;
+    float radius = best[K - 1];
     uint32_t node = a.root;
     {  // wave-uniform climb from the wave's leaf LCA (lanes past the end take no part)
         const float rr = widen(radius);
@@ -557,44 +553,55 @@ __global__ __launch_bounds__(256) void k_core_dist(TraverseArgs<DIM> a, int k, f
     }
     uint2 spill[STACK];
     int sp = 0, base = 0;
+    bool have = true;
     for (int64_t guard = 0;; ++guard) {
-        if (guard > 2 * a.n + 256) {
+        if (guard > 4 * a.n + 256) {
             atomicOr(&a.ctrl->error, kErrStack);
             break;
         }
-        const Rec<DIM> r = a.recs[node];
-        Child<DIM> c0, c1;
-        unpack<DIM>(r, c0, c1);
-        const float d0 = boxdist<DIM>(p, c0.lo, c0.hi);
-        const float d1 = boxdist<DIM>(p, c1.lo, c1.hi);
-        const bool l0 = (c0.ref & kLeafFlag) != 0u, l1 = (c1.ref & kLeafFlag) != 0u;
-        if (l0 && d0 <= radius) knn_insert<K>(best, d0);
-        if (l1 && d1 <= radius) knn_insert<K>(best, d1);
-        radius = fminf(radius, knn_kth<K>(best, k));
-        const bool go0 = !l0 && d0 <= radius;
-        const bool go1 = !l1 && d1 <= radius;
-        if (go0 && go1) {
+        if (have) {
+            const Rec<DIM> r = a.recs[node];
+            Child<DIM> c0, c1;
+            unpack<DIM>(r, c0, c1);
+            const float d0 = boxdist<DIM>(p, c0.lo, c0.hi);
+            const float d1 = boxdist<DIM>(p, c1.lo, c1.hi);
+            const bool l0 = (c0.ref & kLeafFlag) != 0u, l1 = (c1.ref & kLeafFlag) != 0u;
+            // the leaf children of record k are sorted positions k and k + 1;
+            // those of the window are in the list already
+            const bool b0 = l0 & (d0 < radius) & (node - w0 > span);
+            const bool b1 = l1 & (d1 < radius) & (node + 1u - w0 > span);
+            if (b0 | b1) {
+                if (b0) knn_insert<K>(best, d0);
+                if (b1 & (d1 < best[K - 1])) knn_insert<K>(best, d1);
+                radius = best[K - 1];
+            }
+            // (a box at the radius holds nothing nearer)
+            const bool go0 = !l0 && d0 < radius;
+            const bool go1 = !l1 && d1 < radius;
+            const bool both = go0 && go1;
             const bool near1 = d1 < d0;
             const uint2 far = make_uint2(near1 ? c0.ref : c1.ref, fbits(near1 ? d0 : d1));
-            node = near1 ? c1.ref : c0.ref;
-            if (sp - base == kDepth) {
-                if (base >= STACK) {
-                    atomicOr(&a.ctrl->error, kErrStack);
-                    break;
+            node = both ? (near1 ? c1.ref : c0.ref) : (go0 ? c0.ref : c1.ref);
+            have = go0 || go1;
+            if (both) {
+                if (sp - base == kDepth) {  // ring full: move its oldest entry out
+                    if (base < STACK) {
+                        spill[base] = lds[(unsigned)base % kDepth][t];
+                        ++base;
+                    } else {  // (cannot happen: the stack holds a tree's height) end the search
+                        atomicOr(&a.ctrl->error, kErrStack);
+                        have = false;
+                        sp = base = 0;
+                    }
                 }
-                spill[base] = lds[(unsigned)base % kDepth][t];
-                ++base;
+                if (have) {
+                    lds[(unsigned)sp % kDepth][t] = far;
+                    ++sp;
+                }
             }
-            lds[(unsigned)sp % kDepth][t] = far;
-            ++sp;
-            continue;
         }
-        if (go0 || go1) {
-            node = go0 ? c0.ref : c1.ref;
-            continue;
-        }
-        bool found = false;
-        while (sp > 0) {
+        if (!have) {
+            if (sp == 0) break;
             if (sp == base) {  // as in k_traverse_fast
                 const int back = base < kDepth ? base : kDepth;
                 for (int q = 1; q <= back; ++q) lds[(unsigned)(base - q) % kDepth][t] = spill[base - q];
@@ -602,39 +609,33 @@ __global__ __launch_bounds__(256) void k_core_dist(TraverseArgs<DIM> a, int k, f
             }
             --sp;
             const uint2 e = lds[(unsigned)sp % kDepth][t];
-            if (bitsf(e.y) <= radius) {
-                node = e.x;
-                found = true;
-                break;
-            }
+            have = bitsf(e.y) < radius;
+            node = have ? e.x : node;
         }
-        if (!found) break;
     }
-    const float core = knn_kth<K>(best, k);
-    const uint32_t oi = a.orig[i];
+    const float core = best[K - 1];
     core_s[i] = core;
-    core_o[oi] = core;
-    if (core_out) core_out[oi] = core;
+    if (core_out) core_out[a.orig[i]] = core;
 }
 
 template <int DIM, int STACK>
-hipError_t launch_core_s(const TraverseArgs<DIM>& a, int k, float* core_s, float* core_o, float* core_out,
+hipError_t launch_core_s(const TraverseArgs<DIM>& a, int k, float* core_s, float* core_out,
                          hipStream_t st) {
     const unsigned grid = (unsigned)(((a.n + 255) / 256 + kXcds - 1) / kXcds * kXcds);
-    if (k <= 4) k_core_dist<DIM, STACK, 4><<<grid, 256, 0, st>>>(a, k, core_s, core_o, core_out);
-    else if (k <= 8) k_core_dist<DIM, STACK, 8><<<grid, 256, 0, st>>>(a, k, core_s, core_o, core_out);
-    else if (k <= 16) k_core_dist<DIM, STACK, 16><<<grid, 256, 0, st>>>(a, k, core_s, core_o, core_out);
-    else if (k <= 32) k_core_dist<DIM, STACK, 32><<<grid, 256, 0, st>>>(a, k, core_s, core_o, core_out);
-    else k_core_dist<DIM, STACK, 64><<<grid, 256, 0, st>>>(a, k, core_s, core_o, core_out);
+    if (k <= 4) k_core_dist<DIM, STACK, 4><<<grid, 256, 0, st>>>(a, k, core_s, core_out);
+    else if (k <= 8) k_core_dist<DIM, STACK, 8><<<grid, 256, 0, st>>>(a, k, core_s, core_out);
+    else if (k <= 16) k_core_dist<DIM, STACK, 16><<<grid, 256, 0, st>>>(a, k, core_s, core_out);
+    else if (k <= 32) k_core_dist<DIM, STACK, 32><<<grid, 256, 0, st>>>(a, k, core_s, core_out);
+    else k_core_dist<DIM, STACK, 64><<<grid, 256, 0, st>>>(a, k, core_s, core_out);
     return hipGetLastError();
 }
 
 template <int DIM>
-hipError_t launch_core(const TraverseArgs<DIM>& a, int height, int k, float* core_s, float* core_o, float* core_out,
+hipError_t launch_core(const TraverseArgs<DIM>& a, int height, int k, float* core_s, float* core_out,
                        hipStream_t st) {
-    if (height <= 32) return launch_core_s<DIM, 32>(a, k, core_s, core_o, core_out, st);
-    if (height <= 64) return launch_core_s<DIM, 64>(a, k, core_s, core_o, core_out, st);
-    return launch_core_s<DIM, 96>(a, k, core_s, core_o, core_out, st);
+    if (height <= 32) return launch_core_s<DIM, 32>(a, k, core_s, core_out, st);
+    if (height <= 64) return launch_core_s<DIM, 64>(a, k, core_s, core_out, st);
+    return launch_core_s<DIM, 96>(a, k, core_s, core_out, st);
 }
 
 // ---------------------------------------------------------------------------

@@ -179,3 +179,28 @@ def test_sort_sizes(ctx, n):
     order = np.argsort(keys.view(np.uint64), kind="stable")
     assert np.array_equal(k.cpu().numpy(), keys[order])
     assert np.array_equal(v.cpu().numpy(), vals[order])
+
+
+def core_reference(pts, k):
+    """The k-th smallest D(i, j) over all j, float32 in the kernels' order."""
+    n, out = len(pts), np.empty(len(pts), np.float32)
+    for a in range(0, n, 256):
+        s = np.zeros((min(256, n - a), n), np.float32)
+        for c in range(pts.shape[1]):
+            d = pts[a:a + 256, c][:, None] - pts[None, :, c]
+            s = d * d if c == 0 else s + d * d
+        out[a:a + 256] = np.partition(s, k - 1, axis=1)[:, k - 1]
+    return out
+
+
+# every list length (4, 8, 16, 32, 64) full and not, windows clipped at both
+# ends of the cloud, duplicates, and denormal distances
+@pytest.mark.parametrize("k", [2, 4, 5, 8, 9, 16, 17, 31, 32, 33, 64])
+def test_core_distances_of_every_list_length(ctx, k):
+    clouds = [W.small_random(max(k, 65), 3, 1), W.small_random(k, 2, 2), W.small_random(2500, 3, 3, "dup"),
+              W.small_random(2500, 2, 4, "int"), W.clustered3d(3000, seed=5),
+              (np.random.default_rng(6).random((1500, 3)) * 1e-20).astype(np.float32)]
+    for n, pts in enumerate(clouds):
+        print(f"case core k={k} cloud {n}", flush=True)
+        got = ctx.core_distances(torch.from_numpy(pts).cuda(), k).cpu().numpy()
+        assert np.array_equal(got.view(np.uint32), core_reference(pts, k).view(np.uint32)), f"cloud {n}"
