@@ -24,7 +24,7 @@ Prints one JSON line:
                 per launch (FIFO) and the round-granular solver, p50/p99
 
 Bytes per unit (3D; 2D in brackets):
-  node record      64 [48] B, plus 8 B of child labels after the first round
+  node record      64 [48] B (two boxes, two references, two labels)
   per query        4*dim + 16 B  (own coordinates, label, bound, candidate)
   logical: internal child 8*dim + 8 B, leaf child 4*dim + 8 B
 """
@@ -102,9 +102,8 @@ def logical_bytes(dim: int, queries: int, internal: int, leaf: int) -> int:
     return internal * (8 * dim + 8) + leaf * (4 * dim + 8) + queries * (4 * dim + 16)
 
 
-def unique_bytes(dim: int, rnd: int, queries: int, touched: int) -> int:
-    rec = (64 if dim == 3 else 48) + (0 if rnd == 0 else 8)  # the first round derives labels
-    return touched * rec + queries * (4 * dim + 16)
+def unique_bytes(dim: int, queries: int, touched: int) -> int:
+    return touched * (64 if dim == 3 else 48) + queries * (4 * dim + 16)
 
 
 def log(msg: str) -> None:
@@ -265,7 +264,7 @@ def bench_single(args) -> int:
 
     rounds = cst["rounds"]
     q_round, t_round = cst["queries_round"], cst["records_touched_round"]
-    uniq = [unique_bytes(dim, r, q, t) for r, (q, t) in enumerate(zip(q_round, t_round))]
+    uniq = [unique_bytes(dim, q, t) for q, t in zip(q_round, t_round)]
     logi = [logical_bytes(dim, q, ci, li)
             for q, ci, li in zip(q_round, cst["child_tests_round"], cst["leaf_tests_round"])]
     avg_launch_ms = trav_ms / max(launches, 1)
@@ -275,6 +274,8 @@ def bench_single(args) -> int:
     achieved = uniq_launch / sec_launch / 1e9 if avg_launch_ms > 0 else 0.0
     logical_rate = logi_launch / sec_launch / 1e9 if avg_launch_ms > 0 else 0.0
     variant_ran = int(st["traversal_variant"])
+    if variant_ran < 0:
+        log("the timed steps solved the cloud without a tree; the counts are those of a traversal of its tree")
     src_hash = traversal_source_hash()
     key = (args.workload, variant_ran, src_hash)
     meas = None if args.n is not None else MEASURED_TRAFFIC.get(key)
@@ -290,14 +291,14 @@ def bench_single(args) -> int:
         "frac": round(achieved / HBM_PEAK_GBS, 4),
         "traffic": traffic,
         "traffic_frac": None if traffic is None else round(traffic / sec_launch / 1e9 / HBM_PEAK_GBS, 4),
-        "kernel": "k_traverse_lane" if variant_ran == 0 else "k_traverse_fast",
+        "kernel": {0: "k_traverse_lane", -1: "k_flat_search"}.get(variant_ran, "k_traverse_fast"),
         "variant": variant_ran,
         "source_hash": src_hash,
         "avg_launch_ms": round(avg_launch_ms, 4),
         "launches_per_step": rounds,
         "algorithmic_bytes_per_launch": int(uniq_launch),
-        "algorithmic_bytes": "node records loaded in the launch, each once (64 B + 8 B of child labels after "
-                             "the first round), plus 4*dim + 16 B per query",
+        "algorithmic_bytes": "node records loaded in the launch, each once (64 B, 48 B in 2D), plus "
+                             "4*dim + 16 B per query",
         "records_touched_per_launch": int(sum(t_round) / max(rounds, 1)),
         "logical": {"bytes_per_launch": int(logi_launch), "rate_gbs": round(logical_rate, 1),
                     "rate_frac": round(logical_rate / HBM_PEAK_GBS, 4),

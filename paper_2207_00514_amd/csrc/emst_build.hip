@@ -416,7 +416,7 @@ __host__ __device__ inline bool many_dups(uint32_t dups, int64_t n) { return (in
 
 template <int DIM, bool REFS>
 __global__ __launch_bounds__(256) void k_build(const uint64_t* __restrict__ codes,
-                                               const uint32_t* __restrict__ orig, int64_t n, Rec<DIM>* recs,
+                                               const uint32_t* __restrict__ orig, int64_t n, uint4* meta,
                                                uint32_t* __restrict__ leaf_parent, NodeInfo* __restrict__ info,
                                                uint64_t* exch, Ctrl* ctrl) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -444,7 +444,7 @@ __global__ __launch_bounds__(256) void k_build(const uint64_t* __restrict__ code
         const uint32_t parent = (uint32_t)(left_child ? r : l - 1);
         const int side = left_child ? 0 : 1;
         const uint32_t link = (parent << 1) | (uint32_t)side;
-        if (REFS) set_child_ref<DIM>(&recs[parent], side, self_ref);
+        if (REFS) set_child_ref(meta, parent, side, self_ref);
         if (leaf) leaf_parent[i] = link;
         else info[self] = NodeInfo{(uint32_t)l, (uint32_t)r, link, h};  // self's range and height
         // Two sibling leaves: node k holds leaves k and k+1 exactly when
@@ -523,7 +523,7 @@ template <int DIM>
 __global__ __launch_bounds__(256) void k_fit_tiles(const float* __restrict__ spts, const uint32_t* __restrict__ orig,
                                                    const uint32_t* __restrict__ leaf_parent,
                                                    const NodeInfo* __restrict__ info, int64_t n, Rec<DIM>* recs,
-                                                   uint32_t* __restrict__ rlo, uint32_t* __restrict__ rhi,
+                                                   uint4* meta, uint32_t* __restrict__ rlo, uint32_t* __restrict__ rhi,
                                                    uint32_t* __restrict__ node_parent, uint32_t* __restrict__ span,
                                                    uint32_t* __restrict__ span_count, uint32_t* __restrict__ arrive,
                                                    Ctrl* ctrl) {
@@ -571,7 +571,7 @@ __global__ __launch_bounds__(256) void k_fit_tiles(const float* __restrict__ spt
                 atomicOr(&ctrl->error, kErrStack);
                 break;
             }
-            set_child<DIM>(&recs[P], side, lo, hi, ref);
+            set_child<DIM>(recs, meta, P, side, lo, hi, ref);
             const int64_t ps = (int64_t)P - t0;
             if (ps < 0 || ps >= kFitTile) break;                    // P spans the tile's border
             if (s_lo[ps] < lo_in || s_hi[ps] > hi_in) break;         // likewise
@@ -626,7 +626,7 @@ __global__ __launch_bounds__(kFitThreads) void k_fit_group(const uint32_t* __res
                                                    uint32_t* arrive, const uint32_t* __restrict__ rlo,
                                                    const uint32_t* __restrict__ rhi,
                                                    const uint32_t* __restrict__ node_parent, Rec<DIM>* recs,
-                                                   const Ctrl* ctrl) {
+                                                   uint4* meta, const Ctrl* ctrl) {
     if (ctrl->error) return;
     __shared__ uint32_t s_off[kFitGroup + 1];
     __shared__ uint32_t s_out, s_in;
@@ -714,7 +714,7 @@ __global__ __launch_bounds__(kFitThreads) void k_fit_group(const uint32_t* __res
                     lo[d] = fminf(s_box[cur][0][d], s_box[cur][1][d]);
                     hi[d] = fmaxf(s_box[cur][0][DIM + d], s_box[cur][1][DIM + d]);
                 }
-                set_child<DIM>(&recs[link >> 1], (int)(link & 1u), lo, hi, s_node[cur]);
+                set_child<DIM>(recs, meta, link >> 1, (int)(link & 1u), lo, hi, s_node[cur]);
                 if (par == kNone) break;
                 const uint32_t P = par >> 1;
 #pragma unroll
@@ -753,7 +753,7 @@ __global__ __launch_bounds__(kFitThreads) void k_fit_group(const uint32_t* __res
                 lo[d] = fminf(c0.lo[d], c1.lo[d]);
                 hi[d] = fmaxf(c0.hi[d], c1.hi[d]);
             }
-            set_child<DIM>(&recs[P], (int)(link & 1u), lo, hi, cur);
+            set_child<DIM>(recs, meta, P, (int)(link & 1u), lo, hi, cur);
             if ((uint64_t)plo >> up != (uint64_t)phi >> up) break;
             __threadfence_block();
             if (__hip_atomic_fetch_add(&arrive[P], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == 0u)
@@ -783,9 +783,19 @@ __device__ __forceinline__ uint32_t compact2(uint64_t x) {
     return (uint32_t)x;
 }
 
-// Morton cell of every internal node.  A node that splits on a code bit t
-// holds exactly the points whose codes agree with its leaves above bit t, so
-// its cell is the box of quantised coordinates with those bits fixed.  In
+// Where the searches of a wave of 64 Morton-consecutive queries start: the
+// lowest node over their leaves, and the Morton cells on the way up from it.
+//
+// wave_lca[w]: the node over the leaves 64w .. 64w + 63 is the one among the
+// 63 (or fewer) splits between them with the highest split bit, which one
+// wave finds by reading their codes in order (climbing to it from a leaf,
+// one thread per wave of queries, took 301 us at 37M points).  Written over
+// the exchange words of the build, which are dead once the hierarchy exists.
+//
+// up[k], for every node a climb can pass, that is over 64 leaves or more or
+// over the last leaf: its link and its cell.  A node that splits on a code
+// bit t holds exactly the points whose codes agree with its leaves above bit
+// t, so its cell is the box of quantised coordinates with those bits fixed.  In
 // real coordinates the cell is [lo + Q/scale, lo + (Q + 2^m)/scale) per
 // axis (m = free low bits of that axis); the stored box is shrunk by a
 // margin far above every rounding in the quantisation, so any point inside
@@ -793,12 +803,32 @@ __device__ __forceinline__ uint32_t compact2(uint64_t x) {
 // stay open, nodes that split equal codes get an empty cell.
 // With rank-space codes (`ranks`) a cell is not a box of coordinates: every
 // cell is left empty, so the climbs run to the top.
+//
+// Bound by streaming codes and leaf ranges (16 B a point); cells of every
+// node wrote 32 B a point more and took 341 us at 37M points; both
+// together now take 362 us, and at
+// 2M points 24 instead of 44 us.
 template <int DIM>
-__global__ __launch_bounds__(256) void k_cells(const uint64_t* __restrict__ codes,
-                                               const uint32_t* __restrict__ node_parent, int64_t m,
-                                               MortonParams mp, bool ranks, Up* __restrict__ up) {
+__global__ __launch_bounds__(256) void k_starts(const uint64_t* __restrict__ codes,
+                                                const uint32_t* __restrict__ rlo, const uint32_t* __restrict__ rhi,
+                                                const uint32_t* __restrict__ node_parent, int64_t n,
+                                                MortonParams mp, bool ranks, uint32_t* __restrict__ wave_lca,
+                                                Up* __restrict__ up) {
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t m = n - 1;
+    const int lane = lane_id();
+    {
+        // highest split among the wave's pairs (k, k + 1), k < 64w + 63; a
+        // wave of one leaf (the last) starts at the split before it
+        uint32_t best = 0u;
+        if (lane < 63 && k < m) best = ((uint32_t)split_bit(codes, k) + 1u) << 6 | (uint32_t)lane;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) best = max(best, (uint32_t)__shfl_xor((int)best, off));
+        if (lane == 0 && k < n) wave_lca[k / 64] = best ? (uint32_t)(k + (best & 63u)) : (uint32_t)(k - 1);
+    }
     if (k >= m) return;
+    const uint32_t lo = rlo[k], hi = rhi[k];
+    if (hi - lo < 63u && hi != (uint32_t)m) return;
     float clo[3] = {INFINITY, INFINITY, INFINITY}, chi[3] = {-INFINITY, -INFINITY, -INFINITY};
     const uint64_t x = codes[k] ^ codes[k + 1];
     if (x && !ranks) {
@@ -826,28 +856,6 @@ __global__ __launch_bounds__(256) void k_cells(const uint64_t* __restrict__ code
     u.a = make_float4(clo[0], clo[1], clo[2], __uint_as_float(node_parent[k]));
     u.b = make_float4(chi[0], chi[1], chi[2], 0.f);
     up[k] = u;
-}
-
-// For every wave of 64 Morton-consecutive queries [64w, 64w + 63]: the
-// lowest node whose leaf range covers them, found by climbing from the first
-// leaf.  Written over the exchange words of the build, which are dead once
-// the hierarchy exists.
-__global__ __launch_bounds__(256) void k_wave_lca(const uint32_t* __restrict__ rlo, const uint32_t* __restrict__ rhi,
-                                                  const uint32_t* __restrict__ leaf_parent,
-                                                  const uint32_t* __restrict__ node_parent, int64_t n,
-                                                  uint32_t* __restrict__ wave_lca) {
-    const int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t i0 = 64 * w;
-    if (i0 >= n) return;
-    const uint32_t i1 = (uint32_t)min<int64_t>(i0 + 63, n - 1);
-    uint32_t s = leaf_parent[i0] >> 1;
-    for (int h = 0; h < 160; ++h) {
-        if (rlo[s] <= (uint32_t)i0 && rhi[s] >= i1) break;
-        const uint32_t link = node_parent[s];
-        if (link == kNone) break;
-        s = link >> 1;
-    }
-    wave_lca[w] = s;
 }
 
 // ===========================================================================
@@ -1050,7 +1058,8 @@ __global__ __launch_bounds__(1024) void k_tile_carries(const uint32_t* __restric
     tiles_excl_scan<true>(part, carry, nb, s_w, s_incl);
 }
 
-// Per tile: the record labels lab2[k] of every record k in the tile and,
+// Per tile: the record labels (meta[k].zw) of every record k in the tile
+// (unless meta is null: the first round's searches derive them) and,
 // with BOUNDS, the Morton-neighbour bound of every component (Optimization
 // 2): a Morton-adjacent pair with different labels bounds the shortest
 // outgoing edge of both components by its D.  Every position takes the
@@ -1081,7 +1090,7 @@ template <int DIM, bool FIRST, bool BOUNDS, int PER>
 __global__ __launch_bounds__(256) void k_round_prep(const uint32_t* __restrict__ labels,
                                                     const uint32_t* __restrict__ carry,
                                                     const uint32_t* __restrict__ rlo,
-                                                    const uint32_t* __restrict__ rhi, uint2* __restrict__ lab2,
+                                                    const uint32_t* __restrict__ rhi, uint4* __restrict__ meta,
                                                     const float* __restrict__ spts,
                                                     const uint32_t* __restrict__ cloud_of,
                                                     const float* __restrict__ core_s, int64_t n, uint32_t* ub,
@@ -1102,8 +1111,8 @@ __global__ __launch_bounds__(256) void k_round_prep(const uint32_t* __restrict__
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
         const int64_t k = base + q * 256 + tid;
-        rl[q] = k < n - 1 ? rlo[k] : 0u;
-        rh[q] = k < n - 1 ? rhi[k] : 0u;
+        rl[q] = k < n - 1 && meta ? rlo[k] : 0u;
+        rh[q] = k < n - 1 && meta ? rhi[k] : 0u;
     }
     for (int x = tid; x < (256 * PER) + 2; x += 256) {
         int64_t p = base + x - 1;
@@ -1164,7 +1173,7 @@ __global__ __launch_bounds__(256) void k_round_prep(const uint32_t* __restrict__
     for (int q = 0; q < PER; ++q) {
         const int x = q * 256 + tid;
         const int64_t k = base + x;
-        if (k < n - 1) {
+        if (k < n - 1 && meta) {
             const uint32_t lo = rl[q], hi = rh[q];
             bool left, right;
             if (FIRST) {
@@ -1174,8 +1183,8 @@ __global__ __launch_bounds__(256) void k_round_prep(const uint32_t* __restrict__
                 left = s_rs[run_lds(x)] <= lo;
                 right = (x + 1 < (256 * PER) ? s_re[run_lds(x + 1)] : carry_r) >= hi;
             }
-            lab2[k] = make_uint2(left ? s_lab[run_lds(x + 1)] : kInvalid,
-                                 right ? s_lab[run_lds(x + 2)] : kInvalid);
+            reinterpret_cast<uint2*>(meta + k)[1] = make_uint2(left ? s_lab[run_lds(x + 1)] : kInvalid,
+                                                               right ? s_lab[run_lds(x + 2)] : kInvalid);
         }
         // a component's successor is itself until stage B finds its edge
         // (the first round's traversal writes every successor itself)
@@ -2167,7 +2176,7 @@ __global__ __launch_bounds__(256) void k_batch_edge_write(const uint4* __restric
 // workspace layout
 
 struct Layout {
-    size_t ctrl, bpart, k0, k1, v0, v1, hist, spts, orig, cand_p, recs, lab2, height, node_parent, leaf_parent, up, exch, rlo, rhi, run_part, run_carry, qcnt, qoff, qflag, qlist, labels, ub, compkey, compmax, succ, par, cand_d, cand_j, eud, core_s, spare, total;
+    size_t ctrl, bpart, k0, k1, v0, v1, hist, spts, orig, cand_p, recs, meta, height, node_parent, leaf_parent, up, exch, rlo, rhi, run_part, run_carry, qcnt, qoff, qflag, qlist, labels, ub, compkey, compmax, succ, par, cand_d, cand_j, eud, core_s, spare, total;
 };
 
 static size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -2209,7 +2218,7 @@ static Layout make_layout(int64_t n, int dim) {
     L.orig = take(4 * N);
     L.cand_p = take(4 * N);
     L.recs = take(M * (dim == 3 ? sizeof(Rec<3>) : sizeof(Rec<2>)));
-    L.lab2 = take(8 * M);
+    L.meta = take(16 * M);
     L.height = take(M);
     L.node_parent = take(4 * M);
     L.leaf_parent = take(4 * N);
@@ -2233,7 +2242,7 @@ static Layout make_layout(int64_t n, int dim) {
     L.cand_j = take(4 * N);
     L.eud = take(16 * N);
     L.core_s = take(4 * N);
-    L.spare = take(4 * N);  // (keeps emst_workspace_bytes what it was)
+    L.spare = take(12 * N);  // (keeps emst_workspace_bytes what it was)
     L.total = o;
     return L;
 }
@@ -2493,11 +2502,11 @@ bool extent_ok(const float* lo, const float* hi, int dim) {
 
 // The record labels of arbitrary labels (no bounds).
 hipError_t propagate_labels(const uint32_t* labels, uint32_t* run_part, uint32_t* run_carry, const uint32_t* rlo,
-                            const uint32_t* rhi, uint2* lab2, int64_t n, Ctrl* ctrl, hipStream_t st) {
+                            const uint32_t* rhi, uint4* meta, int64_t n, Ctrl* ctrl, hipStream_t st) {
     const int nb = run_tiles(n, kRunPer);
     k_run_partials<kRunPer><<<nb, 256, 0, st>>>(labels, n, run_part);
     k_tile_carries<<<1, 1024, 0, st>>>(run_part, nb, run_carry, ctrl);
-    k_round_prep<3, false, false, kRunPer><<<nb, 256, 0, st>>>(labels, run_carry, rlo, rhi, lab2, nullptr, nullptr, nullptr,
+    k_round_prep<3, false, false, kRunPer><<<nb, 256, 0, st>>>(labels, run_carry, rlo, rhi, meta, nullptr, nullptr, nullptr,
                                                       n, nullptr, ctrl, nullptr, nb, KeepArgs{}, nullptr);
     return hipGetLastError();
 }
@@ -2512,7 +2521,7 @@ struct Bufs {
     float* spts;
     uint32_t *orig, *cand_p;
     Rec<DIM>* recs;
-    uint2* lab2;
+    uint4* meta;
     uint8_t* height;
     uint32_t *node_parent, *leaf_parent;
     Up* up;
@@ -2540,7 +2549,7 @@ Bufs<DIM> carve(char* ws, const Layout& L, int64_t n) {
     b.orig = reinterpret_cast<uint32_t*>(ws + L.orig);
     b.cand_p = reinterpret_cast<uint32_t*>(ws + L.cand_p);
     b.recs = reinterpret_cast<Rec<DIM>*>(ws + L.recs);
-    b.lab2 = reinterpret_cast<uint2*>(ws + L.lab2);
+    b.meta = reinterpret_cast<uint4*>(ws + L.meta);
     b.height = reinterpret_cast<uint8_t*>(ws + L.height);
     b.node_parent = reinterpret_cast<uint32_t*>(ws + L.node_parent);
     b.leaf_parent = reinterpret_cast<uint32_t*>(ws + L.leaf_parent);
@@ -2579,7 +2588,7 @@ TraverseArgs<DIM> traverse_args(const Bufs<DIM>& b, int64_t n, uint32_t root) {
     ta.spts = b.spts; ta.labels = b.labels; ta.orig = b.orig; ta.ub = b.ub; ta.recs = b.recs; ta.root = root;
     ta.n = n; ta.cand_d = b.cand_d; ta.cand_j = b.cand_j; ta.compkey = b.compkey; ta.compmax = b.compmax;
     ta.ctrl = b.ctrl; ta.first = true; ta.up = b.up;
-    ta.cloud_of = nullptr; ta.cloud_root = nullptr; ta.lab2 = b.lab2;
+    ta.cloud_of = nullptr; ta.cloud_root = nullptr; ta.meta = b.meta;
     ta.wave_lca = reinterpret_cast<const uint32_t*>(b.exch);  // the build's exchange words are free by now
     ta.core_s = nullptr;
     ta.cand_p = b.cand_p;
@@ -2666,12 +2675,12 @@ int enqueue_round(emst_ctx* ctx, Bufs<DIM>& b, TraverseArgs<DIM>& ta, int64_t n,
     if (round > 0 && !fold) k_tile_carries<<<1, 1024, 0, st>>>(b.run_part, nt, b.run_carry, b.ctrl);
     with_run_per(per, [&](auto P) {
         if (round == 0)
-            k_round_prep<DIM, true, true, P.value><<<nt, 256, 0, st>>>(b.labels, b.run_carry, b.rlo, b.rhi, b.lab2,
-                                                                       b.spts, cloud_of, ta.core_s, n, b.ub, b.ctrl,
+            k_round_prep<DIM, true, true, P.value><<<nt, 256, 0, st>>>(b.labels, b.run_carry, b.rlo, b.rhi,
+                                                                       variant == 0 ? b.meta : nullptr, b.spts, cloud_of, ta.core_s, n, b.ub, b.ctrl,
                                                                        nullptr, nt, ka, b.succ);
         else
             k_round_prep<DIM, false, true, P.value><<<nt, 256, 0, st>>>(
-                b.labels, b.run_carry, b.rlo, b.rhi, b.lab2, b.spts, cloud_of, ta.core_s, n, b.ub, b.ctrl,
+                b.labels, b.run_carry, b.rlo, b.rhi, b.meta, b.spts, cloud_of, ta.core_s, n, b.ub, b.ctrl,
                 fold ? b.run_part : nullptr, nt, ka, b.succ);
     });
     ta.first = round == 0;
@@ -2994,7 +3003,7 @@ template <int DIM>
 int build_hierarchy(emst_ctx* ctx, Bufs<DIM>& b, const uint64_t* codes, int64_t n, hipStream_t st,
                     Ctrl* mirror = nullptr, hipEvent_t ev = nullptr) {
     NodeInfo* info = reinterpret_cast<NodeInfo*>(b.up);
-    k_build<DIM, false><<<grid_for(n), 256, 0, st>>>(codes, b.orig, n, b.recs, b.leaf_parent, info, b.exch, b.ctrl);
+    k_build<DIM, false><<<grid_for(n), 256, 0, st>>>(codes, b.orig, n, b.meta, b.leaf_parent, info, b.exch, b.ctrl);
     if (mirror) {
         HIP_TRY(hipMemcpyAsync(mirror, b.ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, st));
         HIP_TRY(hipEventRecord(ev, st));
@@ -3004,12 +3013,12 @@ int build_hierarchy(emst_ctx* ctx, Bufs<DIM>& b, const uint64_t* codes, int64_t 
     uint32_t* next[2] = {b.v0, b.v1};
     uint32_t* counts = b.hist;
     int64_t tiles = (n + kFitTile - 1) / kFitTile;
-    k_fit_tiles<DIM><<<(unsigned)tiles, 256, 0, st>>>(b.spts, b.orig, b.leaf_parent, info, n, b.recs, b.rlo, b.rhi,
-                                                      b.node_parent, list, counts, arrive, b.ctrl);
+    k_fit_tiles<DIM><<<(unsigned)tiles, 256, 0, st>>>(b.spts, b.orig, b.leaf_parent, info, n, b.recs, b.meta, b.rlo,
+                                                      b.rhi, b.node_parent, list, counts, arrive, b.ctrl);
     for (int shift = kFitShift, lvl = 0; tiles > 1; shift += kFitGroupShift, ++lvl) {
         const int64_t groups = (tiles + kFitGroup - 1) / kFitGroup;
         k_fit_group<DIM><<<(unsigned)groups, kFitThreads, 0, st>>>(list, counts, tiles, shift, next[lvl & 1], counts + tiles,
-                                                           arrive, b.rlo, b.rhi, b.node_parent, b.recs, b.ctrl);
+                                                           arrive, b.rlo, b.rhi, b.node_parent, b.recs, b.meta, b.ctrl);
         list = next[lvl & 1];
         counts += tiles;
         tiles = groups;
@@ -3168,9 +3177,8 @@ int job_enqueue(emst_ctx* ctx, Job& j, hipStream_t st) {
     }
     case kPhFit: {  // Morton cells, wave starts, core distances; then round 0
         const uint64_t* codes = j.codes_in1 ? b.k1 : b.k0;
-        k_cells<DIM><<<grid_for(n - 1), 256, 0, st>>>(codes, b.node_parent, n - 1, j.mp, j.ranks, b.up);
-        k_wave_lca<<<grid_for((n + 63) / 64), 256, 0, st>>>(b.rlo, b.rhi, b.leaf_parent, b.node_parent, n,
-                                                            reinterpret_cast<uint32_t*>(b.exch));
+        k_starts<DIM><<<grid_for(n), 256, 0, st>>>(codes, b.rlo, b.rhi, b.node_parent, n, j.mp, j.ranks,
+                                                   reinterpret_cast<uint32_t*>(b.exch), b.up);
         HIP_TRY(hipGetLastError());
         TraverseArgs<DIM> ta = job_args<DIM>(j, b);
         if (j.k_pts >= 2) {
@@ -4573,35 +4581,35 @@ __global__ __launch_bounds__(256) void k_test_prep(const uint32_t* __restrict__ 
     if (i + 1 < n) exch[i] = ~0ull;
 }
 
-__global__ __launch_bounds__(256) void k_test_extract(const Rec<3>* __restrict__ recs, const uint2* __restrict__ lab2,
+__global__ __launch_bounds__(256) void k_test_extract(const uint4* __restrict__ meta,
                                                       const uint32_t* __restrict__ node_parent, int64_t m,
                                                       int32_t* __restrict__ left, int32_t* __restrict__ right,
                                                       uint32_t* __restrict__ label) {
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= m) return;
-    Child<3> c0, c1;
-    unpack<3>(recs[k], c0, c1);
-    left[k] = (c0.ref & kLeafFlag) ? -(int32_t)(c0.ref & ~kLeafFlag) - 1 : (int32_t)c0.ref;
-    right[k] = (c1.ref & kLeafFlag) ? -(int32_t)(c1.ref & ~kLeafFlag) - 1 : (int32_t)c1.ref;
+    const uint4 M = meta[k];
+    left[k] = (M.x & kLeafFlag) ? -(int32_t)(M.x & ~kLeafFlag) - 1 : (int32_t)M.x;
+    right[k] = (M.y & kLeafFlag) ? -(int32_t)(M.y & ~kLeafFlag) - 1 : (int32_t)M.y;
     const uint32_t link = node_parent[k];
     if (link == kNone) {
-        const uint2 L = lab2[k];
-        label[k] = (L.x == L.y) ? L.x : kInvalid;
+        label[k] = (M.z == M.w) ? M.z : kInvalid;
     } else {
-        const uint2 L = lab2[link >> 1];
-        label[k] = (link & 1u) ? L.y : L.x;
+        const uint4 P = meta[link >> 1];
+        label[k] = (link & 1u) ? P.w : P.z;
     }
 }
 
-__global__ __launch_bounds__(256) void k_test_boxes(const Rec<3>* __restrict__ recs, int64_t m,
+__global__ __launch_bounds__(256) void k_test_boxes(const Rec<3>* __restrict__ recs,
+                                                    const uint4* __restrict__ meta, int64_t m,
                                                     int32_t* __restrict__ left, int32_t* __restrict__ right,
                                                     float* __restrict__ lo, float* __restrict__ hi) {
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= m) return;
+    const uint4 M = meta[k];
+    left[k] = (M.x & kLeafFlag) ? -(int32_t)(M.x & ~kLeafFlag) - 1 : (int32_t)M.x;
+    right[k] = (M.y & kLeafFlag) ? -(int32_t)(M.y & ~kLeafFlag) - 1 : (int32_t)M.y;
     Child<3> c0, c1;
     unpack<3>(recs[k], c0, c1);
-    left[k] = (c0.ref & kLeafFlag) ? -(int32_t)(c0.ref & ~kLeafFlag) - 1 : (int32_t)c0.ref;
-    right[k] = (c1.ref & kLeafFlag) ? -(int32_t)(c1.ref & ~kLeafFlag) - 1 : (int32_t)c1.ref;
     for (int d = 0; d < 3; ++d) {
         lo[3 * k + d] = fminf(c0.lo[d], c1.lo[d]);
         hi[3 * k + d] = fmaxf(c0.hi[d], c1.hi[d]);
@@ -4822,18 +4830,17 @@ extern "C" int emst_test_tree_from_codes(emst_ctx* ctx, const uint64_t* d_codes,
     uint32_t* rhi = reinterpret_cast<uint32_t*>(ws + L.rhi);
     uint32_t* run_part = reinterpret_cast<uint32_t*>(ws + L.run_part);
     uint32_t* run_carry = reinterpret_cast<uint32_t*>(ws + L.run_carry);
-    Rec<3>* recs = reinterpret_cast<Rec<3>*>(ws + L.recs);
-    uint2* lab2 = reinterpret_cast<uint2*>(ws + L.lab2);
+    uint4* meta = reinterpret_cast<uint4*>(ws + L.meta);
     uint32_t* node_parent = reinterpret_cast<uint32_t*>(ws + L.node_parent);
     uint32_t* leaf_parent = reinterpret_cast<uint32_t*>(ws + L.leaf_parent);
     k_init_ctrl<<<1, 64, 0, st>>>(ctrl);
     k_test_prep<<<grid_for(n), 256, 0, st>>>(d_leaf_labels, n, spts, orig, labels, exch);
     uint8_t* height = reinterpret_cast<uint8_t*>(ws + L.height);
     NodeInfo* info = reinterpret_cast<NodeInfo*>(ws + L.up);
-    k_build<3, true><<<grid_for(n), 256, 0, st>>>(d_codes, orig, n, recs, leaf_parent, info, exch, ctrl);
+    k_build<3, true><<<grid_for(n), 256, 0, st>>>(d_codes, orig, n, meta, leaf_parent, info, exch, ctrl);
     k_unpack_nodes<<<grid_for(n - 1), 256, 0, st>>>(info, n - 1, rlo, rhi, node_parent, height);
-    HIP_TRY(propagate_labels(labels, run_part, run_carry, rlo, rhi, lab2, n, ctrl, st));
-    k_test_extract<<<grid_for(n - 1), 256, 0, st>>>(recs, lab2, node_parent, n - 1, d_left, d_right, d_label);
+    HIP_TRY(propagate_labels(labels, run_part, run_carry, rlo, rhi, meta, n, ctrl, st));
+    k_test_extract<<<grid_for(n - 1), 256, 0, st>>>(meta, node_parent, n - 1, d_left, d_right, d_label);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipMemcpyAsync(ctx->h_ctrl, ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
@@ -4901,7 +4908,7 @@ extern "C" int emst_test_tree_boxes(emst_ctx* ctx, const float* d_points, int64_
     const uint32_t* perm = in1 ? b.v1 : b.v0;
     k_gather<3><<<grid_for(n), 256, 0, st>>>(d_points, perm, n, b.spts, b.orig, b.labels, b.exch);
     if (int rc = build_tree<3>(ctx, b, codes, n, st)) return rc;
-    k_test_boxes<<<grid_for(n - 1), 256, 0, st>>>(b.recs, n - 1, d_left, d_right, d_lo, d_hi);
+    k_test_boxes<<<grid_for(n - 1), 256, 0, st>>>(b.recs, b.meta, n - 1, d_left, d_right, d_lo, d_hi);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipStreamSynchronize(st));
     *root_out = (int32_t)ctx->h_ctrl->root;

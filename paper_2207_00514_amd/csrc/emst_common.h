@@ -15,30 +15,34 @@ constexpr int kWave = 64;
 
 // ---------------------------------------------------------------------------
 // Node record of the binary LBVH.  One record per internal node holds
-// everything a traversal needs about BOTH children, so testing the two
-// children of a node is one contiguous read: per child its bounding box and
-// its reference (internal node index, or kLeafFlag | original point index).
-// With one point per leaf a leaf child's box is the point itself.  The
-// component labels of the children change every round and live in a
-// separate 8-byte entry per record; the record's label slots stay unused.
+// everything a traversal needs about BOTH children, in two parts: the two
+// boxes (48 bytes in 3D, 32 in 2D), which never change after the build, and
+// one 16-byte entry with each child's reference (internal node index, or
+// kLeafFlag | original point index) and component label, the labels
+// rewritten every round.  With one point per leaf a leaf child's box is the
+// point itself.  A node visit is one 16-byte gather per 16 bytes: the
+// traversal is bound by the number of gather instructions (the texture
+// addresser takes 19 to 20 cycles for one, whatever its width, and was busy
+// 88 % of the second round at 2M points), so labels in an array of their own
+// cost it a fifth gather: all rounds' traversals of 37M points took 30.4 ms
+// that way and take 28.4, of 2M points 1.83 and 1.64 ms; k_round_prep, which
+// writes the labels into 16-byte entries, takes 615 instead of 540 us a launch
+// at 37M points.
 //
-//   3D, 64 B:  child c at [32c, 32c+32): float4(lo.x, lo.y, lo.z, unused)
-//                                        float4(hi.x, hi.y, hi.z, ref)
-//   2D, 48 B:  float4(lo0.x, lo0.y, hi0.x, hi0.y)
-//              float4(lo1.x, lo1.y, hi1.x, hi1.y)
-//              uint4 (unused, ref0, unused, ref1)
+//   3D: child c at floats [6c, 6c + 6): lo.x, lo.y, lo.z, hi.x, hi.y, hi.z
+//   2D: child c at floats [4c, 4c + 4): lo.x, lo.y, hi.x, hi.y
+//   entry: ref of child 0, ref of child 1, label of child 0, label of child 1
 template <int DIM> struct Rec;
 
-template <> struct alignas(64) Rec<3> {
-    float4 a0, b0, a1, b1;
+template <> struct alignas(16) Rec<3> {
+    float4 a, b, c;
 };
 template <> struct alignas(16) Rec<2> {
     float4 box0, box1;
-    uint4 meta;
 };
 
-static_assert(sizeof(Rec<3>) == 64, "3D record is 64 bytes");
-static_assert(sizeof(Rec<2>) == 48, "2D record is 48 bytes");
+static_assert(sizeof(Rec<3>) == 48, "3D boxes are 48 bytes");
+static_assert(sizeof(Rec<2>) == 32, "2D boxes are 32 bytes");
 
 // Upward-walk metadata of an internal node (32 B): the node's Morton cell
 // shrunk by a safety margin (every point whose coordinates lie inside it is
@@ -52,49 +56,48 @@ struct alignas(16) Up {
 
 template <int DIM> struct Child {
     float lo[DIM], hi[DIM];
-    uint32_t lab, ref;  // label (from the per-round entry), reference
+    uint32_t lab, ref;  // label, reference (from the entry)
 };
 
 __device__ __forceinline__ uint32_t fbits(float f) { return __float_as_uint(f); }
 __device__ __forceinline__ float bitsf(uint32_t u) { return __uint_as_float(u); }
 
+// The boxes of both children.
 template <int DIM>
 __device__ __forceinline__ void unpack(const Rec<DIM>& r, Child<DIM>& c0, Child<DIM>& c1);
 
 template <>
 __device__ __forceinline__ void unpack<3>(const Rec<3>& r, Child<3>& c0, Child<3>& c1) {
-    c0.lo[0] = r.a0.x; c0.lo[1] = r.a0.y; c0.lo[2] = r.a0.z; c0.lab = kInvalid;
-    c0.hi[0] = r.b0.x; c0.hi[1] = r.b0.y; c0.hi[2] = r.b0.z; c0.ref = fbits(r.b0.w);
-    c1.lo[0] = r.a1.x; c1.lo[1] = r.a1.y; c1.lo[2] = r.a1.z; c1.lab = kInvalid;
-    c1.hi[0] = r.b1.x; c1.hi[1] = r.b1.y; c1.hi[2] = r.b1.z; c1.ref = fbits(r.b1.w);
+    c0.lo[0] = r.a.x; c0.lo[1] = r.a.y; c0.lo[2] = r.a.z;
+    c0.hi[0] = r.a.w; c0.hi[1] = r.b.x; c0.hi[2] = r.b.y;
+    c1.lo[0] = r.b.z; c1.lo[1] = r.b.w; c1.lo[2] = r.c.x;
+    c1.hi[0] = r.c.y; c1.hi[1] = r.c.z; c1.hi[2] = r.c.w;
 }
 
 template <>
 __device__ __forceinline__ void unpack<2>(const Rec<2>& r, Child<2>& c0, Child<2>& c1) {
     c0.lo[0] = r.box0.x; c0.lo[1] = r.box0.y; c0.hi[0] = r.box0.z; c0.hi[1] = r.box0.w;
     c1.lo[0] = r.box1.x; c1.lo[1] = r.box1.y; c1.hi[0] = r.box1.z; c1.hi[1] = r.box1.w;
-    c0.lab = kInvalid; c0.ref = r.meta.y; c1.lab = kInvalid; c1.ref = r.meta.w;
 }
 
-// Write the reference of child `side` of record r.
-template <int DIM>
-__device__ __forceinline__ void set_child_ref(Rec<DIM>* r, int side, uint32_t ref) {
-    if (DIM == 3) reinterpret_cast<uint32_t*>(r)[8 * side + 7] = ref;
-    else reinterpret_cast<uint32_t*>(r)[8 + 2 * side + 1] = ref;
+// Write the reference of child `side` of node k.
+__device__ __forceinline__ void set_child_ref(uint4* meta, uint32_t k, int side, uint32_t ref) {
+    reinterpret_cast<uint32_t*>(meta + k)[side] = ref;
 }
 
-// Box and reference of child `side` in one go (3D: the whole 32-byte half
-// of the record, two 16-byte stores).
+// Box and reference of child `side` of node k.
 template <int DIM>
-__device__ __forceinline__ void set_child(Rec<DIM>* r, int side, const float* lo, const float* hi, uint32_t ref) {
+__device__ __forceinline__ void set_child(Rec<DIM>* recs, uint4* meta, uint32_t k, int side, const float* lo,
+                                          const float* hi, uint32_t ref) {
     if constexpr (DIM == 3) {
-        float4* f = reinterpret_cast<float4*>(r) + 2 * side;
-        f[0] = make_float4(lo[0], lo[1], lo[2], 0.f);
-        f[1] = make_float4(hi[0], hi[1], hi[2], __uint_as_float(ref));
+        float2* f = reinterpret_cast<float2*>(recs + k) + 3 * side;
+        f[0] = make_float2(lo[0], lo[1]);
+        f[1] = make_float2(lo[2], hi[0]);
+        f[2] = make_float2(hi[1], hi[2]);
     } else {
-        reinterpret_cast<float4*>(r)[side] = make_float4(lo[0], lo[1], hi[0], hi[1]);
-        reinterpret_cast<uint32_t*>(r)[8 + 2 * side + 1] = ref;
+        reinterpret_cast<float4*>(recs + k)[side] = make_float4(lo[0], lo[1], hi[0], hi[1]);
     }
+    set_child_ref(meta, k, side, ref);
 }
 
 // ---------------------------------------------------------------------------
@@ -167,22 +170,45 @@ __device__ __forceinline__ int64_t xcd_block(int64_t hw, int64_t grid) {
     return (hw % kXcds) * per + hw / kXcds;
 }
 
+// Lane moves inside the vector unit (no LDS): the value of the lane CTRL
+// names, or the lane's own value where there is none.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_move(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, CTRL, ROWS, 0xF, false);
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint64_t dpp_move(uint64_t x) {
+    return ((uint64_t)dpp_move<CTRL, ROWS>((uint32_t)(x >> 32)) << 32) | dpp_move<CTRL, ROWS>((uint32_t)x);
+}
+
 // Segmented inclusive min-scan over the lanes of a wave, segments = runs of
 // equal `lab` in lane order.  Lanes only ever combine values carrying the
 // same label, and the last lane of a run ends up with the minimum of the
 // whole run; *run_end tells whether this lane is that last lane.  Every lane
-// of the wave must call it.
+// of the wave must call it.  The six steps move values by DPP (1, 2, 4 and 8
+// lanes inside a row of 16, then the last lane of a row to the next rows); a
+// lane takes part in a step if its run reaches back to the lanes it gets
+// values from.  (Through LDS, two or three
+// ds_bpermute a step, k_round_prep took 621 instead of 615 us a launch at 37M
+// points and 39.6 instead of 37.8 us at 2M.)
 template <typename T>
 __device__ __forceinline__ T wave_seg_min(uint32_t lab, T v, bool* run_end) {
     const int lane = lane_id();
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t ol = __shfl_up(lab, off);
-        const T ov = __shfl_up(v, off);
-        if (lane >= off && ol == lab && ov < v) v = ov;
-    }
-    const uint32_t next = __shfl_down(lab, 1);
-    *run_end = (lane == 63) || (next != lab);
+    const uint64_t heads = __ballot(lane == 0 || (uint32_t)__shfl_up((int)lab, 1) != lab);
+    const int start = 63 - __clzll(heads & (~0ull >> (63 - lane)));  // first lane of the run
+    T o = dpp_move<0x111, 0xF>(v);  // row_shr:1
+    if (lane - 1 >= start && o < v) v = o;
+    o = dpp_move<0x112, 0xF>(v);
+    if (lane - 2 >= start && o < v) v = o;
+    o = dpp_move<0x114, 0xF>(v);
+    if (lane - 4 >= start && o < v) v = o;
+    o = dpp_move<0x118, 0xF>(v);
+    if (lane - 8 >= start && o < v) v = o;
+    o = dpp_move<0x142, 0xA>(v);  // row_bcast:15 to rows 1 and 3
+    if ((lane & ~15) > start && o < v) v = o;
+    o = dpp_move<0x143, 0xC>(v);  // row_bcast:31 to rows 2 and 3
+    if (start < 32 && o < v) v = o;
+    *run_end = lane == 63 || ((heads >> (lane + 1)) & 1ull);
     return v;
 }
 

@@ -41,7 +41,7 @@ struct TraverseArgs {
     // cloud (kNone for a cloud of one point); null for one cloud
     const uint32_t* cloud_of;
     const uint32_t* cloud_root;
-    const uint2* lab2;  // per record: component labels of its two children (rewritten every round)
+    const uint4* meta;  // per node: references and component labels of its two children
     // per wave of 64 Morton-consecutive queries: the lowest common ancestor
     // of their leaves (one cloud only)
     const uint32_t* wave_lca;
@@ -158,9 +158,11 @@ __device__ __forceinline__ void descend(const TraverseArgs<DIM>& a, uint32_t nod
         Child<DIM> ch[2];
         unpack<DIM>(r, ch[0], ch[1]);
         {
-            const uint2 L = a.lab2[node];
-            ch[0].lab = L.x;
-            ch[1].lab = L.y;
+            const uint4 M = a.meta[node];
+            ch[0].ref = M.x;
+            ch[1].ref = M.y;
+            ch[0].lab = M.z;
+            ch[1].lab = M.w;
         }
         bool go[2] = {false, false};
         float dd[2] = {0.f, 0.f};
@@ -390,17 +392,14 @@ __global__ __launch_bounds__(256) void k_traverse_fast(TraverseArgs<DIM> a) {
             if (COUNT) a.touched[node] = 1;
             Child<DIM> c0, c1;
             unpack<DIM>(r, c0, c1);
-            if (a.first) {
-                // first round: every leaf is its own component, labelled by
-                // its sorted position (the left leaf of record k is k, the
-                // right one k + 1), and every internal node holds several
-                c0.lab = (c0.ref & kLeafFlag) ? node : kInvalid;
-                c1.lab = (c1.ref & kLeafFlag) ? node + 1u : kInvalid;
-            } else {
-                const uint2 L = a.lab2[node];
-                c0.lab = L.x;
-                c1.lab = L.y;
-            }
+            const uint4 M = a.meta[node];
+            c0.ref = M.x;
+            c1.ref = M.y;
+            // first round: every leaf is its own component, labelled by its
+            // sorted position (the left leaf of record k is k, the right one
+            // k + 1), and every internal node holds several
+            c0.lab = a.first ? ((M.x & kLeafFlag) ? node : kInvalid) : M.z;
+            c1.lab = a.first ? ((M.y & kLeafFlag) ? node + 1u : kInvalid) : M.w;
             if (SHARED) radius = fminf(radius, bitsf(load_relaxed(&a.ub[c])));
             const float d0 = boxdist<DIM>(p, c0.lo, c0.hi);
             const float d1 = boxdist<DIM>(p, c1.lo, c1.hi);
@@ -563,6 +562,9 @@ __global__ __launch_bounds__(256) void k_core_dist(TraverseArgs<DIM> a, int k, f
             const Rec<DIM> r = a.recs[node];
             Child<DIM> c0, c1;
             unpack<DIM>(r, c0, c1);
+            const uint2 R = *reinterpret_cast<const uint2*>(a.meta + node);
+            c0.ref = R.x;
+            c1.ref = R.y;
             const float d0 = boxdist<DIM>(p, c0.lo, c0.hi);
             const float d1 = boxdist<DIM>(p, c1.lo, c1.hi);
             const bool l0 = (c0.ref & kLeafFlag) != 0u, l1 = (c1.ref & kLeafFlag) != 0u;
