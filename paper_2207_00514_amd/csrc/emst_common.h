@@ -194,7 +194,9 @@ __device__ __forceinline__ uint64_t dpp_move(uint64_t x) {
 template <typename T>
 __device__ __forceinline__ T wave_seg_min(uint32_t lab, T v, bool* run_end) {
     const int lane = lane_id();
-    const uint64_t heads = __ballot(lane == 0 || (uint32_t)__shfl_up((int)lab, 1) != lab);
+    // (every lane moves its label: a lane left out would give its neighbour 0)
+    const uint32_t before = (uint32_t)__shfl_up((int)lab, 1);
+    const uint64_t heads = __ballot((lane == 0) | (before != lab));
     const int start = 63 - __clzll(heads & (~0ull >> (63 - lane)));  // first lane of the run
     T o = dpp_move<0x111, 0xF>(v);  // row_shr:1
     if (lane - 1 >= start && o < v) v = o;

@@ -204,3 +204,29 @@ def test_core_distances_of_every_list_length(ctx, k):
         print(f"case core k={k} cloud {n}", flush=True)
         got = ctx.core_distances(torch.from_numpy(pts).cuda(), k).cpu().numpy()
         assert np.array_equal(got.view(np.uint32), core_reference(pts, k).view(np.uint32)), f"cloud {n}"
+
+
+def test_runs_of_component_zero_beside_another(ctx):
+    """The component labelled 0 with a run that starts at lane 1 of a wave
+    (and at lanes 16, 32 and 63 of others): the offers and bounds of the lane
+    before stay that lane's own."""
+    n = 1000
+    rng = np.random.default_rng(12)
+    x = np.cumsum(1.0 + rng.random(n))
+    zero = [0, 65, 66, 144, 145, 224, 319]  # sorted positions, the order along the line
+    for p in zero[1:]:
+        x[p - 1:] -= 0.9 * (x[p - 1] - x[p - 2])  # the lane before has the shortest edges around
+    comp = np.arange(n)
+    comp[zero] = 0
+    pts = np.stack([x, np.zeros(n)], 1).astype(np.float32)
+    d = (pts[1:, 0] - pts[:-1, 0]) ** 2
+    nearest = np.full(n, np.inf, np.float32)  # per component: a point's nearest other-component point is a neighbour
+    for k in range(n - 1):
+        if comp[k] != comp[k + 1]:
+            for c in (comp[k], comp[k + 1]):
+                nearest[c] = min(nearest[c], d[k])
+    for variant in (7, 13):
+        print(f"case runs of component 0, variant {variant}", flush=True)
+        r = ctx.test_round(torch.from_numpy(pts).cuda(), torch.from_numpy(comp.astype(np.int32)).cuda(), 1, variant)
+        for name in ("comp_d2", "bound"):
+            assert np.array_equal(r[name].cpu().numpy(), nearest[comp]), f"variant {variant}: {name}"
