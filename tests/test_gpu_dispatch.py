@@ -230,3 +230,38 @@ def test_runs_of_component_zero_beside_another(ctx):
         r = ctx.test_round(torch.from_numpy(pts).cuda(), torch.from_numpy(comp.astype(np.int32)).cuda(), 1, variant)
         for name in ("comp_d2", "bound"):
             assert np.array_equal(r[name].cpu().numpy(), nearest[comp]), f"variant {variant}: {name}"
+
+
+def check_batch(ctx, clouds):
+    res = ctx.build_batched([torch.from_numpy(c).cuda() for c in clouds])
+    torch.cuda.synchronize()
+    for k, (c, (e, w, d2)) in enumerate(zip(clouds, res)):
+        assert_tree((e.cpu().numpy(), w.cpu().numpy(), d2.cpu().numpy()), oracle.emst(c, threads=8), f"cloud {k}")
+
+
+# waves of 64 points inside one cloud, across clouds and past the end; 2D and
+# 3D; ties that need the in-place order and those that need the full one
+@pytest.mark.parametrize("sizes", [[64, 64, 64], [1, 63, 64, 65, 2, 0, 127, 1], [1000, 1, 200, 5000, 64, 129],
+                                   [40_000, 3, 30_000], [20_001]])
+@pytest.mark.parametrize("kind", ["uniform", "int", "dup", "outlier"])
+def test_batch_edge_order(ctx, sizes, kind):
+    print(f"case batch {sizes} {kind}", flush=True)
+    check_batch(ctx, [W.small_random(n, 2 + k % 2, 7 * k + n, kind) for k, n in enumerate(sizes)])
+
+
+def test_batch_whose_order_needs_more_than_64_bits(ctx):
+    """70,000 clouds (17 bits) with one of 70,000 points (17 bits): with the
+    31 bits of D one more than a key holds, so the slots are sorted by cloud."""
+    rng = np.random.default_rng(9)
+    big = W.clustered3d(70_000, seed=9)
+    pairs = rng.random((69_999, 2, 2)).astype(np.float32)
+    clouds = [torch.from_numpy(big).cuda()] + list(torch.from_numpy(pairs).cuda())
+    res = ctx.build_batched(clouds)
+    torch.cuda.synchronize()
+    e, w, d2 = (t.cpu().numpy() for t in res[0])
+    assert_tree((e, w, d2), oracle.emst(big, threads=8), "the large cloud")
+    edges = torch.cat([r[0] for r in res[1:]]).cpu().numpy()
+    got = torch.cat([r[2] for r in res[1:]]).cpu().numpy()
+    dx, dy = (pairs[:, 0] - pairs[:, 1]).T
+    assert np.array_equal(edges, np.tile(np.array([[0, 1]], np.int32), (69_999, 1)))
+    assert np.array_equal(got.view(np.uint32), (dx * dx + dy * dy).view(np.uint32))
