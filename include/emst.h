@@ -348,15 +348,15 @@ int emst_set_counting(emst_ctx *ctx, int on);
  *  11  as 10 with the component bound shared while the round runs (every
  *      improved candidate lowers it with an atomicMin, every node visit
  *      re-reads it)
- *  13  as 10, and a point keeps last round's result where it still holds:
+ *  13  as 7, and a point keeps last round's result where it still holds:
  *      its candidate if that is still outside its component, or "nothing"
  *      if it found nothing within a radius at least the new one (default)
  * -1 (the default) takes the variant from the context's autotune table
  * (emst_set_autotune) for the call's mode, dimension and size, else 13, or
  * for emst_build of up to 16,384 points a search without a tree (unless
  * the table, emst_set_lds_depth or emst_set_counting ask for a traversal).
- * Batches (emst_build_batched) run 0, 5, 8 or 13 (with the start of 7) as
- * chosen and 7 for 10 and 11.
+ * Batches (emst_build_batched) run 0, 5, 8 or 13 as chosen and 7
+ * for 10 and 11; emst_build_mreach runs 7 for all but 13.
  * Returns EMST_EINVAL for any other value. */
 int emst_set_traversal(emst_ctx *ctx, int variant);
 

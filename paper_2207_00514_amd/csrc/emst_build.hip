@@ -783,8 +783,9 @@ __device__ __forceinline__ uint32_t compact2(uint64_t x) {
     return (uint32_t)x;
 }
 
-// Where the searches of a wave of 64 Morton-consecutive queries start: the
-// lowest node over their leaves, and the Morton cells on the way up from it.
+// Where the searches of a wave of 64 Morton-consecutive queries start in the
+// variants that start below the root (10 and 11): the lowest node over their
+// leaves, and the Morton cells on the way up from it.
 //
 // wave_lca[w]: the node over the leaves 64w .. 64w + 63 is the one among the
 // 63 (or fewer) splits between them with the highest split bit, which one
@@ -2633,7 +2634,7 @@ TraverseArgs<DIM> traverse_args(const Bufs<DIM>& b, int64_t n, uint32_t root) {
     ta.n = n; ta.cand_d = b.cand_d; ta.cand_j = b.cand_j; ta.compkey = b.compkey; ta.compmax = b.compmax;
     ta.ctrl = b.ctrl; ta.first = true; ta.up = b.up;
     ta.cloud_of = nullptr; ta.cloud_root = nullptr; ta.meta = b.meta;
-    ta.wave_lca = reinterpret_cast<const uint32_t*>(b.exch);  // the build's exchange words are free by now
+    ta.wave_lca = nullptr;
     ta.core_s = nullptr;
     ta.cand_p = b.cand_p;
     ta.succ = b.succ;
@@ -3196,13 +3197,16 @@ static Job make_job(emst_ctx* ctx, const float* pts, int64_t n, int dim, char* w
     return j;
 }
 
+// Variants whose waves start below the root (the others' searches start there,
+// see k_traverse_fast).
+static bool wave_starts(const Job& j) { return j.k_pts < 2 && (j.variant == 10 || j.variant == 11); }
+
 template <int DIM>
 static TraverseArgs<DIM> job_args(const Job& j, const Bufs<DIM>& b) {
     TraverseArgs<DIM> ta = traverse_args<DIM>(b, j.n, j.root);
     ta.lds_depth = j.lds_depth;
-    if (j.k_pts >= 2) {
-        ta.core_s = b.core_s;
-    }
+    if (wave_starts(j)) ta.wave_lca = reinterpret_cast<const uint32_t*>(b.exch);  // (free once the tree is built)
+    if (j.k_pts >= 2) ta.core_s = b.core_s;
     return ta;
 }
 
@@ -3249,11 +3253,12 @@ int job_enqueue(emst_ctx* ctx, Job& j, hipStream_t st) {
                                                    b.labels, b.exch);
         return build_hierarchy<DIM>(ctx, b, codes, n, st, j.h, ctx->sev[0]);
     }
-    case kPhFit: {  // Morton cells, wave starts, core distances; then round 0
-        const uint64_t* codes = j.codes_in1 ? b.k1 : b.k0;
-        k_starts<DIM><<<grid_for(n), 256, 0, st>>>(codes, b.rlo, b.rhi, b.node_parent, n, j.mp, j.ranks,
-                                                   reinterpret_cast<uint32_t*>(b.exch), b.up);
-        HIP_TRY(hipGetLastError());
+    case kPhFit: {  // wave starts and their Morton cells, core distances; then round 0
+        if (wave_starts(j)) {
+            k_starts<DIM><<<grid_for(n), 256, 0, st>>>(j.codes_in1 ? b.k1 : b.k0, b.rlo, b.rhi, b.node_parent, n, j.mp,
+                                                       j.ranks, reinterpret_cast<uint32_t*>(b.exch), b.up);
+            HIP_TRY(hipGetLastError());
+        }
         TraverseArgs<DIM> ta = job_args<DIM>(j, b);
         if (j.k_pts >= 2) {
             HIP_TRY(launch_core<DIM>(ta, j.height, j.k_pts, b.core_s, j.core_out, st));
@@ -3657,8 +3662,7 @@ int batched_impl(emst_ctx* ctx, const float* pts, const int64_t* h_offsets, cons
     TraverseArgs<3> ta = traverse_args<3>(b, n, ctx->h_ctrl->root);
     ta.cloud_of = cloud_sorted;
     ta.cloud_root = d_croot;
-    // variants 1-4 start every lane at one root and 6, 9-12 need the Morton
-    // cells of one cloud: a batch runs them as 7 (and 13 with the start of 7)
+    // (10 and 11 need the Morton cells of one cloud: a batch runs them as 7)
     int t = 13, depth = 8;
     pick_shape(ctx, 1, 3, n, &t, &depth);
     const int variant = (t == 0 || t == 5 || t == 8 || t == 13) ? t : 7;

@@ -42,8 +42,8 @@ struct TraverseArgs {
     const uint32_t* cloud_of;
     const uint32_t* cloud_root;
     const uint4* meta;  // per node: references and component labels of its two children
-    // per wave of 64 Morton-consecutive queries: the lowest common ancestor
-    // of their leaves (one cloud only)
+    // variants 10 and 11: per wave of 64 Morton-consecutive queries, the
+    // lowest common ancestor of their leaves (one cloud only)
     const uint32_t* wave_lca;
     // mutual reachability: squared core distances by sorted position (null
     // for the Euclidean tree)
@@ -294,11 +294,18 @@ __device__ __forceinline__ float widen(float radius) { return sqrtf(radius) * 1.
 // shortest candidate already offered to the component while components
 // are small (tight_radius).  With LIST the
 // lanes take the points of the query list, which holds exactly the points
-// that must search (k_reuse_mark), so waves run full.  A wave of the list
-// spans more than 64 positions; its climb starts at the start node of the
-// 64 positions around its first point, an ancestor of that point's leaf,
-// and the climb's stopping rule (every lane's ball inside the cell) still
-// puts every lane's search region below the node it stops at.
+// that must search (k_reuse_mark), so waves run full.
+//
+// REUSE searches start at the root, although starting a wave below it (WSTART)
+// saves its lanes the shared descent: that descent reads records that every
+// wave reads, and the climb to the start is a chain of dependent loads in
+// front of it.  Rounds 0 and 1 from the root and from below it, us:
+// 2M clustered points 1,555 and 1,590, 16M 6,472 and 6,478, 16M uniform 6,126 and
+// 6,319, 16M uniform in 2D 2,801 and 2,908; only large cosmology clouds gain
+// from the climb (30M: 12,184 and 11,673, of 43,000 in all), which is less than
+// finding the starts and cells (362 us at 37M points) and the climbs of the
+// listed waves, which span far more than 64 positions, cost them: list rounds
+// took 13.9 with and 13.6 ms without at 37M, 1.41 and 1.25 ms at 5M in 2D.
 template <int DIM, int STACK, bool COUNT, int kLdsDepth = 16, bool WSTART = false, bool MREACH = false,
           bool SHARED = false, bool REUSE = false, bool LIST = false>
 __global__ __launch_bounds__(256) void k_traverse_fast(TraverseArgs<DIM> a) {
@@ -306,7 +313,6 @@ __global__ __launch_bounds__(256) void k_traverse_fast(TraverseArgs<DIM> a) {
     __shared__ uint2 lds[kLdsDepth][256];
     const int t = threadIdx.x;
     int64_t i;
-    uint32_t first = 0;  // LIST: the wave's first point (its lane 0 holds the smallest position)
     if (LIST) {
         // the grid covers every point; only the blocks the list needs run
         const int64_t cnt = a.ctrl->qcount;
@@ -314,7 +320,6 @@ __global__ __launch_bounds__(256) void k_traverse_fast(TraverseArgs<DIM> a) {
         if ((int64_t)blockIdx.x >= active) return;
         const int64_t li = xcd_block(blockIdx.x, active) * blockDim.x + t;
         i = li < cnt ? (int64_t)a.qlist[li] : a.n;
-        first = __builtin_amdgcn_readfirstlane((uint32_t)i);
     } else {
         i = xcd_block(blockIdx.x, gridDim.x) * blockDim.x + t;
     }
@@ -368,7 +373,7 @@ __global__ __launch_bounds__(256) void k_traverse_fast(TraverseArgs<DIM> a) {
         if (WSTART && mask) {
             // wave-uniform climb; lanes past the end take no part
             const float rr = widen(radius);
-            uint32_t s = a.wave_lca[(LIST ? (int64_t)first : i) >> 6];
+            uint32_t s = a.wave_lca[i >> 6];
             for (int h = 0; h < 160 && s != node; ++h) {
                 const Up cu = a.up[s];
                 if (__all(ball_in_cell<DIM>(p, rr, cu))) break;
@@ -494,9 +499,9 @@ __global__ __launch_bounds__(256) void k_traverse_fast(TraverseArgs<DIM> a) {
 // (D = 0) included.  K registers (K >= k) hold the smallest D so far in
 // ascending order; the first K - k start at -inf and stay there, so that the
 // last one always is the k-th smallest.  The sorted positions within k - 1
-// of i (at least k points) come first; the search then takes every other
-// leaf it reaches, prunes boxes farther than the running k-th value, and
-// starts every wave below the root as variant 10 does.  The loop is the one
+// of i (at least k points) come first; the search from the root then takes
+// every other leaf it reaches and prunes boxes farther than the running k-th
+// value.  The loop is the one
 // of k_traverse_fast; the insertions, 2 K selects and compares each, run only
 // when some lane meets a leaf within its radius.  Keeping the window's
 // distances instead of finding them again in the search, and the k-th value
@@ -539,17 +544,6 @@ __global__ __launch_bounds__(256) void k_core_dist(TraverseArgs<DIM> a, int k, f
     }
     float radius = best[K - 1];
     uint32_t node = a.root;
-    {  // wave-uniform climb from the wave's leaf LCA (lanes past the end take no part)
-        const float rr = widen(radius);
-        uint32_t s = a.wave_lca[i >> 6];
-        for (int h = 0; h < 160 && s != node; ++h) {
-            const Up cu = a.up[s];
-            if (__all(ball_in_cell<DIM>(p, rr, cu))) break;
-            const uint32_t link = fbits(cu.a.w);
-            s = link == kNone ? node : link >> 1;
-        }
-        node = s;
-    }
     uint2 spill[STACK];
     int sp = 0, base = 0;
     bool have = true;
@@ -652,10 +646,10 @@ hipError_t launch_traverse_s(const TraverseArgs<DIM>& a, int variant, bool count
         else k_traverse_fast<DIM, STACK, false, __VA_ARGS__><<<grid, 256, 0, st>>>(a);       \
     } while (0)
     //            kLdsDepth, WSTART, MREACH, SHARED, REUSE, LIST
-    if (a.core_s) {  // mutual reachability: the loop and start of variant 10 (with the reuse of 13)
-        if (variant == 13 && a.qlist) EMST_FAST(8, true, true, false, true, true);
-        else if (variant == 13) EMST_FAST(8, true, true, false, true, false);
-        else EMST_FAST(8, true, true);
+    if (a.core_s) {  // mutual reachability: the loop of variant 7 (with the reuse of 13)
+        if (variant == 13 && a.qlist) EMST_FAST(8, false, true, false, true, true);
+        else if (variant == 13) EMST_FAST(8, false, true, false, true, false);
+        else EMST_FAST(8, false, true);
     } else if (variant == 5) {
         EMST_FAST(16);
     } else if (variant == 7) {
@@ -666,8 +660,7 @@ hipError_t launch_traverse_s(const TraverseArgs<DIM>& a, int variant, bool count
         EMST_FAST(8, true);
     } else if (variant == 11) {
         EMST_FAST(8, true, false, true);
-    } else if (variant == 13 && a.cloud_of) {
-        // batches: the start of variant 7 (each cloud's root) with the reuse
+    } else if (variant == 13) {
         if (a.lds_depth == 4) {
             if (a.qlist) EMST_FAST(4, false, false, false, true, true);
             else EMST_FAST(4, false, false, false, true, false);
@@ -677,17 +670,6 @@ hipError_t launch_traverse_s(const TraverseArgs<DIM>& a, int variant, bool count
         } else {
             if (a.qlist) EMST_FAST(8, false, false, false, true, true);
             else EMST_FAST(8, false, false, false, true, false);
-        }
-    } else if (variant == 13) {
-        if (a.lds_depth == 4) {
-            if (a.qlist) EMST_FAST(4, true, false, false, true, true);
-            else EMST_FAST(4, true, false, false, true, false);
-        } else if (a.lds_depth == 16) {
-            if (a.qlist) EMST_FAST(16, true, false, false, true, true);
-            else EMST_FAST(16, true, false, false, true, false);
-        } else {
-            if (a.qlist) EMST_FAST(8, true, false, false, true, true);
-            else EMST_FAST(8, true, false, false, true, false);
         }
     } else {
         if (count) k_traverse_lane<DIM, STACK, true><<<grid, 256, 0, st>>>(a);
