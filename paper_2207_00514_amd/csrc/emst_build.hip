@@ -388,129 +388,43 @@ __device__ __forceinline__ int split_bit(const uint64_t* __restrict__ codes, int
 
 // Bottom-up construction of the binary radix tree over the sorted codes
 // (the agglomerative scheme of Apetrei 2014, one of the two constructions
-// the paper's BVH follows).  Internal node k is the node that splits
-// between leaves k and k+1.  A node spanning leaves [l, r] becomes the left
-// child of node r if its right neighbour pair (r, r+1) shares a longer
-// prefix than its left neighbour pair (l-1, l), else the right child of
-// node l-1.  The first of the two children to reach a parent parks its range
-// end and its height there and stops; the second learns both from that
-// exchange and continues upwards.  Only the 64-bit atomic exchange crosses
-// between threads (agent-scope acquire/release would write back and
-// invalidate the per-XCD L2 caches at every step); every other store is read
-// by later kernels only.  The boxes are fitted afterwards (k_fit_tiles,
-// k_fit_group).  A node's leaf range, height and parent link go out together
-// in one 16-byte NodeInfo once its parent is known (the fit, or
-// k_unpack_nodes, spreads them into their arrays): the stores of the climb
-// land at scattered nodes, and four separate stores per node each cost a
-// whole memory sector.  The child references are written with the boxes by
-// the fit (REFS: here as well, for the test hook that reads the hierarchy
-// without fitting it).  It also counts the positions that repeat the
-// previous code (ctrl->dup_codes).
-struct alignas(16) NodeInfo {
-    uint32_t lo, hi, link, height;
-};
+// the paper's BVH follows), with its boxes, in levels of tiles.  Internal
+// node k is the node that splits between leaves k and k+1.  A node spanning
+// leaves [l, r] becomes the left child of node r if its right neighbour pair
+// (r, r+1) shares a longer prefix than its left neighbour pair (l-1, l), else
+// the right child of node l-1.
+//
+// The first level has one workgroup per tile of kFitTile consecutive leaves.
+// Every leaf's thread climbs while the parent is one of the tile's nodes: it
+// leaves its box, reference, range end and height at the parent in LDS; the
+// first of the two children stops there, the second forms the union and climbs
+// on.  So the subtrees inside the tile are complete after one pass over LDS, and
+// their records, ranges and links go out in order.
+// What is left are the few nodes whose range crosses a tile border (about 11
+// of a tile's 512 of uniform points).  Their ranges come from the
+// threads whose climbs ended below them, which go on through one 64-bit
+// exchange word per node in memory in the same manner: only that exchange
+// crosses between workgroups (agent-scope acquire/release would write back and
+// invalidate the per-XCD L2 caches at every step), and every other store is
+// read by later kernels only.  Their boxes come from the next levels
+// (k_fit_group), which take them from the list that each tile leaves.  The
+// copy of a record whose child crosses the border carries nothing for
+// that child; k_fit_group writes it.  Only the last node of a tile has a child
+// in the next tile, whose workgroup writes that half.
+//
+// Also counts the positions that repeat the previous code (ctrl->dup_codes).
+//
+// Bound by the latency of the climbs (one thread per leaf, 32 waves a CU) and the
+// records' stores.  Two kernels, the hierarchy through the exchange words of
+// every node and the boxes through LDS, took 46 us at 50,000 points, 188 at 2M and
+// 3,519 at 37M; this one takes 31, 123 and 2,576.
 
 // Sorted positions that repeat the previous code, from which the tree is
 // rebuilt on rank-space codes.
 __host__ __device__ inline bool many_dups(uint32_t dups, int64_t n) { return (int64_t)dups * 64 > n; }
 
-template <int DIM, bool REFS>
-__global__ __launch_bounds__(256) void k_build(const uint64_t* __restrict__ codes,
-                                               const uint32_t* __restrict__ orig, int64_t n, uint4* meta,
-                                               uint32_t* __restrict__ leaf_parent, NodeInfo* __restrict__ info,
-                                               uint64_t* exch, Ctrl* ctrl) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int dups = __syncthreads_count(i > 0 && i < n && codes[i] == codes[i - 1]);
-    // (past the threshold nobody needs the exact count, and thousands of
-    // additions to one address would take tens of microseconds)
-    if (threadIdx.x == 0 && dups && !many_dups(load_relaxed(&ctrl->dup_codes), n))
-        atomicAdd(&ctrl->dup_codes, (uint32_t)dups);
-    if (i >= n) return;
-    int64_t l = i, r = i;
-    uint32_t h = 0;
-    uint32_t self = (uint32_t)i, self_ref = orig[i] | kLeafFlag;
-    bool leaf = true;
-    // every step climbs one level; a radix tree over 95-bit augmented keys
-    // has height <= 96
-    for (int step = 0;; ++step) {
-        if (step > 128) {
-            atomicOr(&ctrl->error, kErrStack);
-            return;
-        }
-        bool left_child;
-        if (l == 0) left_child = true;
-        else if (r == n - 1) left_child = false;
-        else left_child = split_bit(codes, r) < split_bit(codes, l - 1);
-        const uint32_t parent = (uint32_t)(left_child ? r : l - 1);
-        const int side = left_child ? 0 : 1;
-        const uint32_t link = (parent << 1) | (uint32_t)side;
-        if (REFS) set_child_ref(meta, parent, side, self_ref);
-        if (leaf) leaf_parent[i] = link;
-        else info[self] = NodeInfo{(uint32_t)l, (uint32_t)r, link, h};  // self's range and height
-        // Two sibling leaves: node k holds leaves k and k+1 exactly when
-        // leaf k is a left child and leaf k+1 a right child.  Both leaf
-        // threads see this from the split bits of adjacent pairs (which
-        // always differ), so the left one continues and the right one stops
-        // with no exchange.
-        bool pair = false;
-        if (leaf) {
-            if (left_child) pair = (i + 1 == n - 1) || split_bit(codes, i + 1) > split_bit(codes, i);
-            else pair = (i - 1 == 0) || split_bit(codes, i - 1) < split_bit(codes, i - 2);
-            if (pair && !left_child) return;
-        }
-        if (pair) {
-            r = i + 1;
-            h = 1u;
-        } else {
-            const uint64_t mine = ((uint64_t)(left_child ? l : r) << 32) | h;
-            const uint64_t other = atomicExch((unsigned long long*)&exch[parent], (unsigned long long)mine);
-            if (other == ~0ull) return;
-            const int64_t oend = (int64_t)(other >> 32);
-            if (left_child) r = oend;
-            else l = oend;
-            h = max(h, (uint32_t)(other & 0xFFFFFFFFu)) + 1u;
-        }
-        self = parent;
-        self_ref = parent;
-        leaf = false;
-        if (l == 0 && r == n - 1) {
-            ctrl->root = parent;
-            ctrl->height = h;
-            info[parent] = NodeInfo{(uint32_t)l, (uint32_t)r, kNone, h};
-            return;
-        }
-    }
-}
-
-__global__ __launch_bounds__(256) void k_unpack_nodes(const NodeInfo* __restrict__ info, int64_t m,
-                                                      uint32_t* __restrict__ rlo, uint32_t* __restrict__ rhi,
-                                                      uint32_t* __restrict__ node_parent,
-                                                      uint8_t* __restrict__ height) {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= m) return;
-    const NodeInfo x = info[k];
-    rlo[k] = x.lo;
-    rhi[k] = x.hi;
-    node_parent[k] = x.link;
-    height[k] = (uint8_t)x.height;
-}
-
-// Boxes, bottom-up, in levels of tiles.  The first level has one workgroup
-// per tile of kFitTile consecutive leaves, which fits every node whose leaf
-// range lies inside its tile: each leaf's thread
-// stores the leaf's box (its point) and reference into the parent's record
-// and climbs while the parent lies inside the tile; at each such node the
-// first child to arrive parks its box in LDS and stops, the second forms the
-// union, stores it with the node's reference into the node's parent's record
-// and climbs on.  Only LDS and one workgroup take part, so no thread waits
-// on another and no cross-XCD ordering is needed.  The same pass spreads the
-// tile's node records (range, parent link) into their arrays and
-// lists the tile's nodes whose range crosses a tile border, which the next
-// levels fit (k_fit_group).  The fences order LDS accesses only: waiting
-// for the record stores at every step of a climb (__threadfence_block)
-// took 85 us instead of 70 us at 2M points.
 constexpr int kFitShift = 9;
-constexpr int kFitTile = 1 << kFitShift;  // 256 and 1024 measured slower (LDS per workgroup vs nodes across borders)
+constexpr int kFitTile = 1 << kFitShift;
 
 // The children of node k, with the leaf ranges [lo, k] and [k + 1, hi], that
 // lie inside one tile of 2^shift leaves.
@@ -520,77 +434,150 @@ __device__ __forceinline__ uint32_t fit_ready(uint32_t lo, uint32_t hi, uint32_t
 }
 
 template <int DIM>
-__global__ __launch_bounds__(256) void k_fit_tiles(const float* __restrict__ spts, const uint32_t* __restrict__ orig,
-                                                   const uint32_t* __restrict__ leaf_parent,
-                                                   const NodeInfo* __restrict__ info, int64_t n, Rec<DIM>* recs,
-                                                   uint4* meta, uint32_t* __restrict__ rlo, uint32_t* __restrict__ rhi,
-                                                   uint32_t* __restrict__ node_parent, uint32_t* __restrict__ span,
-                                                   uint32_t* __restrict__ span_count, uint32_t* __restrict__ arrive,
-                                                   Ctrl* ctrl) {
-    if (ctrl->error) return;  // the build failed: its records are incomplete
-    __shared__ uint32_t s_arrive[kFitTile];
-    __shared__ float s_box[kFitTile][2][2 * DIM];  // per node of the tile and child side: lo, hi
-    __shared__ uint32_t s_lo[kFitTile], s_hi[kFitTile], s_link[kFitTile];
-    __shared__ uint32_t s_nspan;
+__global__ __launch_bounds__(kFitTile) void k_tree_tiles(const uint64_t* __restrict__ codes,
+                                                         const float* __restrict__ spts,
+                                                         const uint32_t* __restrict__ orig, int64_t n, Rec<DIM>* recs,
+                                                         uint4* meta, uint32_t* __restrict__ rlo,
+                                                         uint32_t* __restrict__ rhi, uint32_t* __restrict__ node_parent,
+                                                         uint64_t* exch, uint32_t* __restrict__ span,
+                                                         uint32_t* __restrict__ span_count, Ctrl* ctrl) {
+    constexpr int kDone = kFitTile, kBoth = 0x101;
+    __shared__ alignas(16) float s_box[kFitTile][2][2 * DIM];  // per node of the tile and child side: lo, hi
+    __shared__ uint2 s_ref[kFitTile];
+    __shared__ uint32_t s_arrive[kFitTile];  // 1 for the left child, 0x100 for the right one
+    __shared__ uint32_t s_lo[kFitTile], s_hi[kFitTile];  // left child's start and right child's end; height << 16
+    __shared__ uint32_t s_link[kFitTile];
+    __shared__ uint8_t s_split[kFitTile + 1];  // of the nodes t0 - 1 .. t0 + kFitTile - 1
+    __shared__ uint32_t s_nspan, s_dups;
     const int t = threadIdx.x;
-    const int64_t t0 = (int64_t)blockIdx.x * kFitTile;
-    const int64_t m = n - 1;
-    if (t == 0) s_nspan = 0;
-    for (int x = t; x < kFitTile; x += 256) s_arrive[x] = 0;
+    const int64_t t0 = (int64_t)blockIdx.x * kFitTile, i = t0 + t, m = n - 1;
+    const bool valid = i < n;
+    float lo[DIM], hi[DIM];
+    uint32_t ref = 0u;
+    if (valid) {
+#pragma unroll
+        for (int d = 0; d < DIM; ++d) lo[d] = hi[d] = spts[i * DIM + d];
+        ref = orig[i] | kLeafFlag;
+    }
+    s_arrive[t] = 0u;
+    if (t == 0) s_nspan = s_dups = 0u;
     __syncthreads();
-    for (int x = t; x < kFitTile; x += 256) {
-        const int64_t k = t0 + x;
-        if (k >= m) break;
-        const NodeInfo v = info[k];
-        rlo[k] = v.lo;
-        rhi[k] = v.hi;
-        node_parent[k] = v.link;
-        s_lo[x] = v.lo;
-        s_hi[x] = v.hi;
-        s_link[x] = v.link;
-        if (v.lo / kFitTile != v.hi / kFitTile) {
-            span[t0 + atomicAdd(&s_nspan, 1u)] = (uint32_t)k;  // the tile's segment has room for all of its nodes
-            arrive[k] = fit_ready(v.lo, v.hi, (uint32_t)k, kFitShift);
+    for (int x = t; x <= kFitTile; x += kFitTile) {
+        const int64_t k = t0 - 1 + x;
+        if (k < 0 || k >= m) continue;
+        s_split[x] = (uint8_t)split_bit(codes, k);
+        if (x < kFitTile && codes[k] == codes[k + 1]) atomicAdd(&s_dups, 1u);
+    }
+    __syncthreads();
+    // (past the threshold nobody needs the exact count, and thousands of
+    // additions to one address would take tens of microseconds)
+    if (t == 0 && s_dups && !many_dups(load_relaxed(&ctrl->dup_codes), n)) atomicAdd(&ctrl->dup_codes, s_dups);
+    // the climb inside the tile: leaves t0 + l .. t0 + r under node `self` (none
+    // for a leaf); it ends at the parent `at` whose other child has not come, at
+    // -1 below the last node of the tile before, or at the root (kDone)
+    int l = t, r = t, self = -1, side = 0, at = kDone;
+    uint32_t h = 0u;
+    if (valid) {
+        for (int step = 0; step <= kFitTile; ++step) {  // (a climb passes every node at most once)
+            if (t0 + l == 0 && t0 + r == m) {
+                s_link[self] = kNone;
+                ctrl->root = (uint32_t)(t0 + self);
+                ctrl->height = h;
+                at = kDone;
+                break;
+            }
+            side = t0 + l == 0 ? 0 : t0 + r == m ? 1 : s_split[r + 1] < s_split[l] ? 0 : 1;
+            at = side ? l - 1 : r;
+            if (self >= 0) s_link[self] = (uint32_t)(t0 + at) << 1 | (uint32_t)side;
+            if (at < 0) {
+                set_child<DIM>(recs, meta, (uint32_t)(t0 - 1), 1, lo, hi, ref);
+                break;
+            }
+#pragma unroll
+            for (int d = 0; d < DIM; ++d) {
+                s_box[at][side][d] = lo[d];
+                s_box[at][side][DIM + d] = hi[d];
+            }
+            if (side) {
+                s_ref[at].y = ref;
+                s_hi[at] = (uint32_t)r | h << 16;
+            } else {
+                s_ref[at].x = ref;
+                s_lo[at] = (uint32_t)l | h << 16;
+            }
+            lds_fence();
+            if (atomicAdd(&s_arrive[at], side ? 0x100u : 1u) == 0u) break;  // the sibling may come
+            lds_fence();
+            const uint32_t other = side ? s_lo[at] : s_hi[at];
+            if (side) l = (int)(other & 0xFFFFu);
+            else r = (int)(other & 0xFFFFu);
+            h = max(h, other >> 16) + 1u;
+#pragma unroll
+            for (int d = 0; d < DIM; ++d) {
+                lo[d] = fminf(lo[d], s_box[at][1 - side][d]);
+                hi[d] = fmaxf(hi[d], s_box[at][1 - side][DIM + d]);
+            }
+            self = at;
+            ref = (uint32_t)(t0 + at);
+        }
+    }
+    __syncthreads();
+    // the tile's nodes, in order
+    const int nodes = (int)min<int64_t>(kFitTile, m - t0);
+    const int whole = min(nodes, kFitTile - 1);  // all but the last node of the tile
+    {
+        constexpr int kChunks = (int)(sizeof(Rec<DIM>) / 16);
+        const uint4* src = reinterpret_cast<const uint4*>(&s_box[0][0][0]);
+        uint4* dst = reinterpret_cast<uint4*>(recs + t0);
+        for (int x = t; x < whole * kChunks; x += kFitTile) dst[x] = src[x];
+    }
+    if (t < nodes) {
+        const bool inside = s_arrive[t] == kBoth;
+        if (t < whole) {
+            *reinterpret_cast<uint2*>(meta + i) = s_ref[t];
+        } else if (s_arrive[t] & 1u) {
+            float* b = s_box[t][0];
+            set_child<DIM>(recs, meta, (uint32_t)i, 0, b, b + DIM, s_ref[t].x);
+        }
+        if (inside) {
+            rlo[i] = (uint32_t)t0 + (s_lo[t] & 0xFFFFu);
+            rhi[i] = (uint32_t)t0 + (s_hi[t] & 0xFFFFu);
+            node_parent[i] = s_link[t];
+        } else {
+            span[t0 + atomicAdd(&s_nspan, 1u)] = (uint32_t)i;  // the tile's segment has room for all of its nodes
         }
     }
     __syncthreads();
     if (t == 0) span_count[blockIdx.x] = s_nspan;
-    const uint32_t lo_in = (uint32_t)t0, hi_in = (uint32_t)min<int64_t>(t0 + kFitTile - 1, n - 1);
-    for (int x = t; x < kFitTile; x += 256) {
-        const int64_t i = t0 + x;
-        if (i >= n) break;
-        float lo[DIM], hi[DIM];
-#pragma unroll
-        for (int k = 0; k < DIM; ++k) lo[k] = hi[k] = spts[i * DIM + k];
-        uint32_t link = leaf_parent[i];
-        uint32_t ref = orig[i] | kLeafFlag;
-        for (int step = 0; step < 160; ++step) {  // a climb passes at most height + 1 <= 129 nodes
-            const uint32_t P = link >> 1;
-            const int side = (int)(link & 1u);
-            if ((int64_t)P >= m) {  // (not from a valid tree)
-                atomicOr(&ctrl->error, kErrStack);
-                break;
-            }
-            set_child<DIM>(recs, meta, P, side, lo, hi, ref);
-            const int64_t ps = (int64_t)P - t0;
-            if (ps < 0 || ps >= kFitTile) break;                    // P spans the tile's border
-            if (s_lo[ps] < lo_in || s_hi[ps] > hi_in) break;         // likewise
-#pragma unroll
-            for (int k = 0; k < DIM; ++k) {
-                s_box[ps][side][k] = lo[k];
-                s_box[ps][side][DIM + k] = hi[k];
-            }
-            lds_fence();
-            if (atomicAdd(&s_arrive[ps], 1u) == 0u) break;  // the sibling completes P
-            lds_fence();
-#pragma unroll
-            for (int k = 0; k < DIM; ++k) {
-                lo[k] = fminf(lo[k], s_box[ps][1 - side][k]);
-                hi[k] = fmaxf(hi[k], s_box[ps][1 - side][DIM + k]);
-            }
-            ref = P;
-            link = s_link[ps];
-            if (link == kNone) break;  // the root
+    if (at == kDone || (at >= 0 && s_arrive[at] == kBoth)) return;  // the sibling came
+    // the climb over the tile's border, through the exchange words
+    int64_t L = t0 + l, R = t0 + r, parent = t0 + at;
+    for (int step = 0;; ++step) {
+        if (step > 128) {  // (a tree over 95-bit augmented keys has height <= 96)
+            atomicOr(&ctrl->error, kErrStack);
+            return;
+        }
+        const uint64_t mine = ((uint64_t)(side ? R : L) << 32) | h;
+        const uint64_t other = atomicExch((unsigned long long*)&exch[parent], (unsigned long long)mine);
+        if (other == ~0ull) return;
+        if (side) L = (int64_t)(other >> 32);
+        else R = (int64_t)(other >> 32);
+        h = max(h, (uint32_t)(other & 0xFFFFFFFFu)) + 1u;
+        const int64_t node = parent;
+        uint32_t link = kNone;
+        const bool top = L == 0 && R == m;
+        if (!top) {
+            side = L == 0 ? 0 : R == m ? 1 : split_bit(codes, R) < split_bit(codes, L - 1) ? 0 : 1;
+            parent = side ? L - 1 : R;
+            link = (uint32_t)parent << 1 | (uint32_t)side;
+        }
+        rlo[node] = (uint32_t)L;
+        rhi[node] = (uint32_t)R;
+        node_parent[node] = link;
+        if (top) {
+            ctrl->root = (uint32_t)node;
+            ctrl->height = h;
+            return;
         }
     }
 }
@@ -600,7 +587,7 @@ __global__ __launch_bounds__(256) void k_fit_tiles(const float* __restrict__ spt
 // its own, larger tile, and lists the others for the level above.  The
 // nodes go to LDS (links resolved to slots through a hash table, the boxes
 // of children fitted by levels below loaded from the records), and the
-// climbs of k_fit_tiles run there.  A group of uniform points lists about
+// climbs of k_tree_tiles run there.  A group of uniform points lists about
 // 11 nodes per tile of the first level and 15 per tile of the others; one
 // with more than kFitSlots nodes (points whose tree is a comb at most tile
 // borders) climbs through the records in memory instead (arrive[k] counts
@@ -659,13 +646,13 @@ __global__ __launch_bounds__(kFitThreads) void k_fit_group(const uint32_t* __res
         const uint32_t lo = rlo[k], hi = rhi[k];
         if ((uint64_t)lo >> up != (uint64_t)hi >> up) {
             out[((int64_t)blockIdx.x << up) + atomicAdd(&s_out, 1u)] = k;
-            arrive[k] = fit_ready(lo, hi, k, up);
             continue;
         }
         const uint32_t slot = atomicAdd(&s_in, 1u);
-        if (slot >= kFitSlots) continue;
         const bool r0 = (uint64_t)lo >> shift == (uint64_t)k >> shift;
         const bool r1 = (uint64_t)(k + 1u) >> shift == (uint64_t)hi >> shift;
+        arrive[k] = (uint32_t)r0 + (uint32_t)r1;  // (for the climbs in memory)
+        if (slot >= kFitSlots) continue;
         s_node[slot] = k;
         s_link[slot] = node_parent[k];
         s_arrive[slot] = (uint32_t)r0 + (uint32_t)r1;
@@ -3064,32 +3051,27 @@ static int batch_edges(emst_ctx* ctx, Bufs<3>& b, int64_t n, const uint32_t* clo
     return EMST_OK;
 }
 
-// Hierarchy (bottom-up, exchange only) and every box.  The node records live
-// in the cells' array; the first level's list of nodes across tile borders
-// and the arrival counts share the exchange words (both arrays are free
-// until the cells and the wave starts are made), the lists of the levels
-// above alternate between the sort's value buffers, and the counts of every
-// level lie one after another in the sort's histogram (free until the next
-// sort).  The control block names the root and the height once the
-// hierarchy kernel has run: with `mirror` its copy is queued right behind
-// that kernel and `ev` marks its arrival, so that the host reads it while
-// the boxes are fitted.
+// Hierarchy and every box (see k_tree_tiles).  The lists of nodes across tile
+// borders go to the sort's value buffers, their numbers to its histogram and
+// the arrival counts to the exchange words (all free by then: tile counts of
+// all levels are fewer than the histogram's words).  The control block names
+// the root and the height once the first kernel has run: with `mirror` its
+// copy is queued right behind that kernel and `ev` marks its arrival, so that
+// the host reads it while the other levels run.
 template <int DIM>
 int build_hierarchy(emst_ctx* ctx, Bufs<DIM>& b, const uint64_t* codes, int64_t n, hipStream_t st,
                     Ctrl* mirror = nullptr, hipEvent_t ev = nullptr) {
-    NodeInfo* info = reinterpret_cast<NodeInfo*>(b.up);
-    k_build<DIM, false><<<grid_for(n), 256, 0, st>>>(codes, b.orig, n, b.meta, b.leaf_parent, info, b.exch, b.ctrl);
+    uint32_t* list = b.v1;
+    uint32_t* next[2] = {b.v0, b.v1};
+    uint32_t* arrive = reinterpret_cast<uint32_t*>(b.exch);
+    uint32_t* counts = b.hist;
+    int64_t tiles = (n + kFitTile - 1) / kFitTile;
+    k_tree_tiles<DIM><<<(unsigned)tiles, kFitTile, 0, st>>>(codes, b.spts, b.orig, n, b.recs, b.meta, b.rlo, b.rhi,
+                                                            b.node_parent, b.exch, list, counts, b.ctrl);
     if (mirror) {
         HIP_TRY(hipMemcpyAsync(mirror, b.ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, st));
         HIP_TRY(hipEventRecord(ev, st));
     }
-    uint32_t* list = reinterpret_cast<uint32_t*>(b.exch);
-    uint32_t* arrive = list + (n - 1);
-    uint32_t* next[2] = {b.v0, b.v1};
-    uint32_t* counts = b.hist;
-    int64_t tiles = (n + kFitTile - 1) / kFitTile;
-    k_fit_tiles<DIM><<<(unsigned)tiles, 256, 0, st>>>(b.spts, b.orig, b.leaf_parent, info, n, b.recs, b.meta, b.rlo,
-                                                      b.rhi, b.node_parent, list, counts, arrive, b.ctrl);
     for (int shift = kFitShift, lvl = 0; tiles > 1; shift += kFitGroupShift, ++lvl) {
         const int64_t groups = (tiles + kFitGroup - 1) / kFitGroup;
         k_fit_group<DIM><<<(unsigned)groups, kFitThreads, 0, st>>>(list, counts, tiles, shift, next[lvl & 1], counts + tiles,
@@ -4912,13 +4894,10 @@ extern "C" int emst_test_tree_from_codes(emst_ctx* ctx, const uint64_t* d_codes,
     uint32_t* run_carry = reinterpret_cast<uint32_t*>(ws + L.run_carry);
     uint4* meta = reinterpret_cast<uint4*>(ws + L.meta);
     uint32_t* node_parent = reinterpret_cast<uint32_t*>(ws + L.node_parent);
-    uint32_t* leaf_parent = reinterpret_cast<uint32_t*>(ws + L.leaf_parent);
     k_init_ctrl<<<1, 64, 0, st>>>(ctrl);
     k_test_prep<<<grid_for(n), 256, 0, st>>>(d_leaf_labels, n, spts, orig, labels, exch);
-    uint8_t* height = reinterpret_cast<uint8_t*>(ws + L.height);
-    NodeInfo* info = reinterpret_cast<NodeInfo*>(ws + L.up);
-    k_build<3, true><<<grid_for(n), 256, 0, st>>>(d_codes, orig, n, meta, leaf_parent, info, exch, ctrl);
-    k_unpack_nodes<<<grid_for(n - 1), 256, 0, st>>>(info, n - 1, rlo, rhi, node_parent, height);
+    Bufs<3> b = carve<3>(ws, L, n);
+    if (int rc = build_hierarchy<3>(ctx, b, d_codes, n, st)) return rc;
     HIP_TRY(propagate_labels(labels, run_part, run_carry, rlo, rhi, meta, n, ctrl, st));
     k_test_extract<<<grid_for(n - 1), 256, 0, st>>>(meta, node_parent, n - 1, d_left, d_right, d_label);
     HIP_TRY(hipGetLastError());
