@@ -367,7 +367,7 @@ template <int DIM>
 // merges or resets it while it is a root.)
 __global__ __launch_bounds__(256) void k_gather(const float* __restrict__ pts, const uint32_t* __restrict__ perm,
                                                 int64_t n, float* __restrict__ spts, uint32_t* __restrict__ orig,
-                                                uint32_t* __restrict__ labels, uint64_t* __restrict__ exch) {
+                                                uint32_t* __restrict__ labels) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const uint32_t o = perm[i];
@@ -375,7 +375,6 @@ __global__ __launch_bounds__(256) void k_gather(const float* __restrict__ pts, c
     for (int k = 0; k < DIM; ++k) spts[i * DIM + k] = pts[(int64_t)o * DIM + k];
     orig[i] = o;
     labels[i] = (uint32_t)i;
-    if (i + 1 < n) exch[i] = ~0ull;
 }
 
 // Highest differing bit between sorted augmented keys (code, index) k and
@@ -386,38 +385,37 @@ __device__ __forceinline__ int split_bit(const uint64_t* __restrict__ codes, int
     return 31 - __clz((uint32_t)k ^ (uint32_t)(k + 1));
 }
 
-// Bottom-up construction of the binary radix tree over the sorted codes
-// (the agglomerative scheme of Apetrei 2014, one of the two constructions
-// the paper's BVH follows), with its boxes, in levels of tiles.  Internal
-// node k is the node that splits between leaves k and k+1.  A node spanning
-// leaves [l, r] becomes the left child of node r if its right neighbour pair
-// (r, r+1) shares a longer prefix than its left neighbour pair (l-1, l), else
-// the right child of node l-1.
+// The binary radix tree over the sorted codes (the tree of Apetrei 2014, one of the
+// two constructions the paper's BVH follows), with its boxes, in levels of
+// tiles.  Internal node k splits between leaves k and k+1; its subtree reaches left
+// and right up to the next nodes that split on a higher bit, and the lower of those
+// two is its parent: the left one if it is that one's right child, else the other.
 //
-// The first level has one workgroup per tile of kFitTile consecutive leaves.
-// Every leaf's thread climbs while the parent is one of the tile's nodes: it
-// leaves its box, reference, range end and height at the parent in LDS; the
-// first of the two children stops there, the second forms the union and climbs
-// on.  So the subtrees inside the tile are complete after one pass over LDS, and
-// their records, ranges and links go out in order.
-// What is left are the few nodes whose range crosses a tile border (about 11
-// of a tile's 512 of uniform points).  Their ranges come from the
-// threads whose climbs ended below them, which go on through one 64-bit
-// exchange word per node in memory in the same manner: only that exchange
-// crosses between workgroups (agent-scope acquire/release would write back and
-// invalidate the per-XCD L2 caches at every step), and every other store is
-// read by later kernels only.  Their boxes come from the next levels
-// (k_fit_group), which take them from the list that each tile leaves.  The
-// copy of a record whose child crosses the border carries nothing for
-// that child; k_fit_group writes it.  Only the last node of a tile has a child
-// in the next tile, whose workgroup writes that half.
+// A tile is a run of entries: a complete subtree (a leaf, at the first level),
+// and the node after it.  One thread per entry, and no climbs: a
+// binary search over maxima of 1, 2, 4 .. splits finds a node's range in the tile;
+// the boxes of its children are put together from boxes over
+// 1, 2, 4 .. entries; and the height of a subtree is the deepest of its entries,
+// whose depths come from jumping over 1, 2, 4 .. parents.  So every lane works in
+// each of the (at most 11) steps of these, all in LDS.  A node whose higher
+// neighbours both lie in the tile, or beside it on the left, is complete: its record,
+// range and link are written, once and in order.  The others, whose subtrees cross
+// a border of the tile, are left, and between two of them there always lies exactly one
+// complete subtree: the entries of the next level (about 12 from a tile of 512
+// uniform points, never more than 191, since the nodes across one border are a chain
+// with a split on another of the 95 bits each).  The last node of a tile always is
+// one of them, and the end of the cloud counts as a node that splits above every bit.
 //
-// Also counts the positions that repeat the previous code (ctrl->dup_codes).
+// k_tree_tiles makes the first level's tiles of 512 leaves, k_tree_group joins
+// 64 of a level's tiles at a time until one holds the root.
 //
-// Bound by the latency of the climbs (one thread per leaf, 32 waves a CU) and the
-// records' stores.  Two kernels, the hierarchy through the exchange words of
-// every node and the boxes through LDS, took 46 us at 50,000 points, 188 at 2M and
-// 3,519 at 37M; this one takes 31, 123 and 2,576.
+// Bound by the records' stores and LDS at the first level, by the latency of one
+// workgroup's chain of steps (10 to 20 us) at the others.  At 50,000, 2M and 37M
+// points it takes 41, 135 and 1,474 us.  One kernel for the hierarchy, with an
+// atomic exchange in memory per node, one for the boxes of tiles, climbing in LDS, and
+// one per level for those of the nodes across borders took 82, 275 and 3,782; climbs
+// through the tile in one kernel, which leave most lanes idle, and through exchanges
+// over the borders 66, 208 and 2,856.
 
 // Sorted positions that repeat the previous code, from which the tree is
 // rebuilt on rank-space codes.
@@ -426,328 +424,300 @@ __host__ __device__ inline bool many_dups(uint32_t dups, int64_t n) { return (in
 constexpr int kFitShift = 9;
 constexpr int kFitTile = 1 << kFitShift;
 
-// The children of node k, with the leaf ranges [lo, k] and [k + 1, hi], that
-// lie inside one tile of 2^shift leaves.
-__device__ __forceinline__ uint32_t fit_ready(uint32_t lo, uint32_t hi, uint32_t k, int shift) {
-    return (uint32_t)((uint64_t)lo >> shift == (uint64_t)k >> shift) +
-           (uint32_t)((uint64_t)(k + 1u) >> shift == (uint64_t)hi >> shift);
+constexpr int kTreeSpan = 193;      // entries a tile leaves at most, and some
+constexpr int kTreeGroupShift = 6;  // tiles joined at a time
+constexpr int kTreeGroup = 1 << kTreeGroupShift;
+constexpr int kTreeChunkShift = 10;
+constexpr int kTreeChunk = 1 << kTreeChunkShift;
+
+template <int DIM> struct TreeEntry {
+    float box[2 * DIM];  // lo, hi
+    uint32_t ref, height;
+    uint32_t node, split;  // the node after the subtree
+};
+
+template <int DIM, int LOG> struct TreeLds {
+    static constexpr int T = 1 << LOG;
+    uint8_t top[LOG + 1][T + 8];  // maxima over 2^q splits from x on; x = 0 is the node before the tile
+    float2 box[DIM][T];           // boxes over 2^q entries (as float2s: consecutive threads, consecutive banks)
+    uint32_t up[T];               // parent, or the thread itself | nodes passed << 16
+    uint32_t height[T];
+    uint32_t node[T + 1];
+    uint2 ref[T];
+    uint32_t waves[T / 64];
+    uint32_t reach;
+};
+
+template <int DIM, int T>
+__device__ __forceinline__ void box_merge(float (&b)[2 * DIM], const float2 (&s)[DIM][T], int x) {
+    float o[2 * DIM];
+#pragma unroll
+    for (int d = 0; d < DIM; ++d) {
+        const float2 v = s[d][x];
+        o[2 * d] = v.x;
+        o[2 * d + 1] = v.y;
+    }
+#pragma unroll
+    for (int d = 0; d < DIM; ++d) {
+        b[d] = fminf(b[d], o[d]);
+        b[DIM + d] = fmaxf(b[DIM + d], o[DIM + d]);
+    }
+}
+
+template <int DIM> struct TreeOut {
+    Rec<DIM>* recs;
+    uint4* meta;
+    uint32_t *rlo, *rhi, *node_parent;
+    Ctrl* ctrl;
+};
+
+// One tile of c entries, entry t in thread t (all 2^LOG threads call it): e.box,
+// e.ref and e.height of its subtree, e.node and e.split after it; before the
+// tile lies prev_node (kNone at the start of the cloud, with split 255).  m nodes in all.
+// Leaves the entries of the next level in `out` (which may be what the entries were
+// read from: nothing is written before the first barrier) and returns their number.
+template <int DIM, int LOG>
+__device__ __forceinline__ uint32_t tree_tile(TreeLds<DIM, LOG>& s, int c, uint32_t prev_node, uint32_t prev_split,
+                                              const TreeEntry<DIM>& e, uint32_t m, const TreeOut<DIM>& a,
+                                              TreeEntry<DIM>* out) {
+    constexpr int T = 1 << LOG;
+    const int t = threadIdx.x;
+    const bool has = t < c, real = has && e.node < m;
+    const uint32_t split = has ? e.split : 255u;
+    __syncthreads();  // (the tile before is done with the LDS)
+    s.top[0][t + 1] = (uint8_t)split;
+    s.node[t + 1] = e.node;
+    s.height[t] = 0u;
+    if (t == 0) {
+        s.top[0][0] = (uint8_t)prev_split;
+        s.node[0] = prev_node;
+        s.reach = 0u;
+    }
+    float own[2 * DIM];
+#pragma unroll
+    for (int d = 0; d < 2 * DIM; ++d) own[d] = e.box[d];
+#pragma unroll
+    for (int d = 0; d < DIM; ++d) s.box[d][t] = make_float2(own[2 * d], own[2 * d + 1]);
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < LOG; ++q) {
+        for (int x = t; x <= T; x += T) {
+            const int y = x + (1 << q);
+            s.top[q + 1][x] = max(s.top[q][x], y <= T ? s.top[q][y] : (uint8_t)0);
+        }
+        __syncthreads();
+    }
+    // the splits l .. r around the own one, t + 1, are the subtree's; entries l - 1 .. r
+    int l = t + 1, r = t + 1;
+#pragma unroll
+    for (int q = LOG; q >= 0; --q) {
+        if (l - (1 << q) >= 0 && s.top[q][l - (1 << q)] < split) l -= 1 << q;
+        if (r + (1 << q) <= c && s.top[q][r + 1] < split) r += 1 << q;
+    }
+    const bool in_l = real && l > 0, in_r = real && r < c;  // the children complete in the tile
+    const bool inside = in_l && in_r;
+    // the parents of the node and of the entry's subtree: the lower of the splits
+    // beside them (side 2: the root)
+    int par = -1, side = 0;
+    if (inside) {
+        const uint32_t before = s.top[0][l - 1], after = s.top[0][r + 1];
+        side = before == 255u && after == 255u ? 2 : after < before ? 0 : 1;
+        par = side ? l - 2 : r;
+    }
+    const int sub_side = split < s.top[0][t] ? 0 : 1;
+    const int sub_par = sub_side ? t - 1 : t;
+    if (inside && side < 2 && par >= 0) reinterpret_cast<uint32_t*>(&s.ref[par])[side] = e.node;
+    if (has && sub_par >= 0) reinterpret_cast<uint32_t*>(&s.ref[sub_par])[sub_side] = e.ref;
+    const int cl = inside ? t + 2 - l : 0, cr = inside ? r - t : 0;  // entries of the children
+    if (inside) atomicMax(&s.reach, (uint32_t)max(cl, cr));
+    s.up[t] = inside ? 1u : 0u;
+    const uint64_t left_mask = __ballot(has && !inside);
+    if (lane_id() == 0) s.waves[t >> 6] = (uint32_t)__popcll(left_mask);
+    __syncthreads();
+    const bool linked = inside && side < 2 && par >= 0 && s.up[par] != 0u;
+    const bool sub_linked = has && sub_par >= 0 && s.up[sub_par] != 0u;
+    uint32_t rank = (uint32_t)__popcll(left_mask & ((1ull << lane_id()) - 1ull)), count = 0u;
+    for (int w = 0; w < T / 64; ++w) {
+        const uint32_t v = s.waves[w];
+        rank += w < (t >> 6) ? v : 0u;
+        count += v;
+    }
+    __syncthreads();
+    // boxes of the children, and the chains of parents inside the tile
+    uint32_t up = linked ? (uint32_t)par | 1u << 16 : (uint32_t)t;
+    s.up[t] = up;
+    const uint32_t reach = s.reach;
+    float bl[2 * DIM], br[2 * DIM];
+#pragma unroll
+    for (int d = 0; d < DIM; ++d) {
+        bl[d] = br[d] = INFINITY;
+        bl[DIM + d] = br[DIM + d] = -INFINITY;
+    }
+    int pl = t + 1, pr = t + 1;  // the next part on the left ends before pl, that on the right starts at pr
+    for (int q = 0; (reach >> q) != 0u; ++q) {  // (reach < T)
+        __syncthreads();
+        const int w = 1 << q;
+        if (cl & w) {
+            pl -= w;
+            box_merge<DIM, T>(bl, s.box, pl);
+        }
+        if (cr & w) {
+            box_merge<DIM, T>(br, s.box, pr);
+            pr += w;
+        }
+        const uint32_t next = s.up[up & 0xFFFFu];
+        if (t + w < T) box_merge<DIM, T>(own, s.box, t + w);
+        __syncthreads();
+        up = (next & 0xFFFFu) | ((up & 0xFFFF0000u) + (next & 0xFFFF0000u));
+        s.up[t] = up;
+#pragma unroll
+        for (int d = 0; d < DIM; ++d) s.box[d][t] = make_float2(own[2 * d], own[2 * d + 1]);
+    }
+    __syncthreads();
+    if (sub_linked) {
+        const uint32_t u = s.up[sub_par];
+        atomicMax(&s.height[u & 0xFFFFu], (u >> 16) + 1u + e.height);
+    }
+    // (a node that stays has its number of those before it where the chains were)
+    __syncthreads();
+    s.up[t] = rank;
+    if (inside) {
+        const uint32_t k = e.node;
+        float4* rec = reinterpret_cast<float4*>(a.recs + k);
+        rec[0] = make_float4(bl[0], bl[1], bl[2], bl[3]);
+        if constexpr (DIM == 3) {
+            rec[1] = make_float4(bl[4], bl[5], br[0], br[1]);
+            rec[2] = make_float4(br[2], br[3], br[4], br[5]);
+        } else {
+            rec[1] = make_float4(br[0], br[1], br[2], br[3]);
+        }
+        *reinterpret_cast<uint2*>(a.meta + k) = s.ref[t];
+        a.rlo[k] = s.node[l - 1] + 1u;
+        a.rhi[k] = s.node[r + 1];
+        a.node_parent[k] = side == 2 ? kNone : s.node[side ? l - 1 : r + 1] << 1 | (uint32_t)side;
+        if (side == 2) {
+            a.ctrl->root = k;
+            a.ctrl->height = s.height[t];
+        }
+    }
+    __syncthreads();
+    if (has && !inside) {
+        out[rank].node = e.node;
+        out[rank].split = split;
+    }
+    if (has && !sub_linked) {
+        TreeEntry<DIM>& o = out[rank];
+#pragma unroll
+        for (int d = 0; d < 2 * DIM; ++d) o.box[d] = e.box[d];
+        o.ref = e.ref;
+        o.height = e.height;
+    }
+    if (inside && side < 2 && !linked) {
+        TreeEntry<DIM>& o = out[s.up[r]];
+#pragma unroll
+        for (int d = 0; d < DIM; ++d) {
+            o.box[d] = fminf(bl[d], br[d]);
+            o.box[DIM + d] = fmaxf(bl[DIM + d], br[DIM + d]);
+        }
+        o.ref = e.node;
+        o.height = s.height[t];
+    }
+    return count;
 }
 
 template <int DIM>
 __global__ __launch_bounds__(kFitTile) void k_tree_tiles(const uint64_t* __restrict__ codes,
                                                          const float* __restrict__ spts,
-                                                         const uint32_t* __restrict__ orig, int64_t n, Rec<DIM>* recs,
-                                                         uint4* meta, uint32_t* __restrict__ rlo,
-                                                         uint32_t* __restrict__ rhi, uint32_t* __restrict__ node_parent,
-                                                         uint64_t* exch, uint32_t* __restrict__ span,
-                                                         uint32_t* __restrict__ span_count, Ctrl* ctrl) {
-    constexpr int kDone = kFitTile, kBoth = 0x101;
-    __shared__ alignas(16) float s_box[kFitTile][2][2 * DIM];  // per node of the tile and child side: lo, hi
-    __shared__ uint2 s_ref[kFitTile];
-    __shared__ uint32_t s_arrive[kFitTile];  // 1 for the left child, 0x100 for the right one
-    __shared__ uint32_t s_lo[kFitTile], s_hi[kFitTile];  // left child's start and right child's end; height << 16
-    __shared__ uint32_t s_link[kFitTile];
-    __shared__ uint8_t s_split[kFitTile + 1];  // of the nodes t0 - 1 .. t0 + kFitTile - 1
-    __shared__ uint32_t s_nspan, s_dups;
+                                                         const uint32_t* __restrict__ orig, int64_t n,
+                                                         TreeOut<DIM> a, TreeEntry<DIM>* __restrict__ out,
+                                                         uint32_t* __restrict__ out_count) {
+    __shared__ TreeLds<DIM, kFitShift> s;
     const int t = threadIdx.x;
     const int64_t t0 = (int64_t)blockIdx.x * kFitTile, i = t0 + t, m = n - 1;
-    const bool valid = i < n;
-    float lo[DIM], hi[DIM];
-    uint32_t ref = 0u;
-    if (valid) {
+    TreeEntry<DIM> e = {};
+    bool same = false;
+    if (i < n) {
 #pragma unroll
-        for (int d = 0; d < DIM; ++d) lo[d] = hi[d] = spts[i * DIM + d];
-        ref = orig[i] | kLeafFlag;
+        for (int d = 0; d < DIM; ++d) e.box[d] = e.box[DIM + d] = spts[i * DIM + d];
+        e.ref = orig[i] | kLeafFlag;
+        e.node = (uint32_t)i;
+        e.split = 255u;
+        if (i < m) {
+            e.split = (uint32_t)split_bit(codes, i);
+            same = e.split < 32u;
+        }
     }
-    s_arrive[t] = 0u;
-    if (t == 0) s_nspan = s_dups = 0u;
-    __syncthreads();
-    for (int x = t; x <= kFitTile; x += kFitTile) {
-        const int64_t k = t0 - 1 + x;
-        if (k < 0 || k >= m) continue;
-        s_split[x] = (uint8_t)split_bit(codes, k);
-        if (x < kFitTile && codes[k] == codes[k + 1]) atomicAdd(&s_dups, 1u);
-    }
-    __syncthreads();
+    const uint32_t prev = t0 > 0 ? (uint32_t)split_bit(codes, t0 - 1) : 255u;
+    const int dups = __syncthreads_count(same);
     // (past the threshold nobody needs the exact count, and thousands of
     // additions to one address would take tens of microseconds)
-    if (t == 0 && s_dups && !many_dups(load_relaxed(&ctrl->dup_codes), n)) atomicAdd(&ctrl->dup_codes, s_dups);
-    // the climb inside the tile: leaves t0 + l .. t0 + r under node `self` (none
-    // for a leaf); it ends at the parent `at` whose other child has not come, at
-    // -1 below the last node of the tile before, or at the root (kDone)
-    int l = t, r = t, self = -1, side = 0, at = kDone;
-    uint32_t h = 0u;
-    if (valid) {
-        for (int step = 0; step <= kFitTile; ++step) {  // (a climb passes every node at most once)
-            if (t0 + l == 0 && t0 + r == m) {
-                s_link[self] = kNone;
-                ctrl->root = (uint32_t)(t0 + self);
-                ctrl->height = h;
-                at = kDone;
-                break;
-            }
-            side = t0 + l == 0 ? 0 : t0 + r == m ? 1 : s_split[r + 1] < s_split[l] ? 0 : 1;
-            at = side ? l - 1 : r;
-            if (self >= 0) s_link[self] = (uint32_t)(t0 + at) << 1 | (uint32_t)side;
-            if (at < 0) {
-                set_child<DIM>(recs, meta, (uint32_t)(t0 - 1), 1, lo, hi, ref);
-                break;
-            }
-#pragma unroll
-            for (int d = 0; d < DIM; ++d) {
-                s_box[at][side][d] = lo[d];
-                s_box[at][side][DIM + d] = hi[d];
-            }
-            if (side) {
-                s_ref[at].y = ref;
-                s_hi[at] = (uint32_t)r | h << 16;
-            } else {
-                s_ref[at].x = ref;
-                s_lo[at] = (uint32_t)l | h << 16;
-            }
-            lds_fence();
-            if (atomicAdd(&s_arrive[at], side ? 0x100u : 1u) == 0u) break;  // the sibling may come
-            lds_fence();
-            const uint32_t other = side ? s_lo[at] : s_hi[at];
-            if (side) l = (int)(other & 0xFFFFu);
-            else r = (int)(other & 0xFFFFu);
-            h = max(h, other >> 16) + 1u;
-#pragma unroll
-            for (int d = 0; d < DIM; ++d) {
-                lo[d] = fminf(lo[d], s_box[at][1 - side][d]);
-                hi[d] = fmaxf(hi[d], s_box[at][1 - side][DIM + d]);
-            }
-            self = at;
-            ref = (uint32_t)(t0 + at);
-        }
-    }
-    __syncthreads();
-    // the tile's nodes, in order
-    const int nodes = (int)min<int64_t>(kFitTile, m - t0);
-    const int whole = min(nodes, kFitTile - 1);  // all but the last node of the tile
-    {
-        constexpr int kChunks = (int)(sizeof(Rec<DIM>) / 16);
-        const uint4* src = reinterpret_cast<const uint4*>(&s_box[0][0][0]);
-        uint4* dst = reinterpret_cast<uint4*>(recs + t0);
-        for (int x = t; x < whole * kChunks; x += kFitTile) dst[x] = src[x];
-    }
-    if (t < nodes) {
-        const bool inside = s_arrive[t] == kBoth;
-        if (t < whole) {
-            *reinterpret_cast<uint2*>(meta + i) = s_ref[t];
-        } else if (s_arrive[t] & 1u) {
-            float* b = s_box[t][0];
-            set_child<DIM>(recs, meta, (uint32_t)i, 0, b, b + DIM, s_ref[t].x);
-        }
-        if (inside) {
-            rlo[i] = (uint32_t)t0 + (s_lo[t] & 0xFFFFu);
-            rhi[i] = (uint32_t)t0 + (s_hi[t] & 0xFFFFu);
-            node_parent[i] = s_link[t];
-        } else {
-            span[t0 + atomicAdd(&s_nspan, 1u)] = (uint32_t)i;  // the tile's segment has room for all of its nodes
-        }
-    }
-    __syncthreads();
-    if (t == 0) span_count[blockIdx.x] = s_nspan;
-    if (at == kDone || (at >= 0 && s_arrive[at] == kBoth)) return;  // the sibling came
-    // the climb over the tile's border, through the exchange words
-    int64_t L = t0 + l, R = t0 + r, parent = t0 + at;
-    for (int step = 0;; ++step) {
-        if (step > 128) {  // (a tree over 95-bit augmented keys has height <= 96)
-            atomicOr(&ctrl->error, kErrStack);
-            return;
-        }
-        const uint64_t mine = ((uint64_t)(side ? R : L) << 32) | h;
-        const uint64_t other = atomicExch((unsigned long long*)&exch[parent], (unsigned long long)mine);
-        if (other == ~0ull) return;
-        if (side) L = (int64_t)(other >> 32);
-        else R = (int64_t)(other >> 32);
-        h = max(h, (uint32_t)(other & 0xFFFFFFFFu)) + 1u;
-        const int64_t node = parent;
-        uint32_t link = kNone;
-        const bool top = L == 0 && R == m;
-        if (!top) {
-            side = L == 0 ? 0 : R == m ? 1 : split_bit(codes, R) < split_bit(codes, L - 1) ? 0 : 1;
-            parent = side ? L - 1 : R;
-            link = (uint32_t)parent << 1 | (uint32_t)side;
-        }
-        rlo[node] = (uint32_t)L;
-        rhi[node] = (uint32_t)R;
-        node_parent[node] = link;
-        if (top) {
-            ctrl->root = (uint32_t)node;
-            ctrl->height = h;
-            return;
-        }
-    }
+    if (t == 0 && dups && !many_dups(load_relaxed(&a.ctrl->dup_codes), n)) atomicAdd(&a.ctrl->dup_codes, (uint32_t)dups);
+    const uint32_t left = tree_tile<DIM, kFitShift>(s, (int)min<int64_t>(kFitTile, n - t0), (uint32_t)(t0 - 1), prev, e,
+                                                    (uint32_t)m, a, out + (int64_t)blockIdx.x * kTreeSpan);
+    if (t == 0) out_count[blockIdx.x] = left;
 }
 
-// The next levels: one workgroup per kFitGroup tiles of the level below
-// (2^shift leaves each) fits the listed nodes whose leaf range lies inside
-// its own, larger tile, and lists the others for the level above.  The
-// nodes go to LDS (links resolved to slots through a hash table, the boxes
-// of children fitted by levels below loaded from the records), and the
-// climbs of k_tree_tiles run there.  A group of uniform points lists about
-// 11 nodes per tile of the first level and 15 per tile of the others; one
-// with more than kFitSlots nodes (points whose tree is a comb at most tile
-// borders) climbs through the records in memory instead (arrive[k] counts
-// the finished children of a listed node there), whose dependent loads and
-// stores cost 3 us a step.  The latency of loading a group bounds the
-// rest: two launches of 27 and 56 us at 2M points, three of 156, 71 and
-// 26 us at 37M.  One launch per height over all listed nodes took 39
-// launches and 116 us of kernel time (400 us with the gaps between them
-// where the host was behind) and 53 launches and 331 us.
-constexpr int kFitGroupShift = 6;
-constexpr int kFitGroup = 1 << kFitGroupShift;
-constexpr int kFitSlots = 1536;
-constexpr int kFitHash = 4096;
-constexpr int kFitThreads = 512;
-
-__device__ __forceinline__ uint32_t fit_hash(uint32_t k) { return (k * 2654435761u) >> (32 - 12); }
-static_assert(kFitHash == 1 << 12, "fit_hash gives 12 bits");
-
+// One workgroup joins kTreeGroup tiles of the level below, whose entries lie
+// kTreeSpan apart (`leaves` leaves for the group).  Entries beyond kTreeChunk at a
+// time (points whose tree is a comb at most tile borders) are taken in
+// chunks, whose remaining entries go back to the front of the group's, again
+// and again until one chunk holds them.
 template <int DIM>
-__global__ __launch_bounds__(kFitThreads) void k_fit_group(const uint32_t* __restrict__ span,
-                                                   const uint32_t* __restrict__ span_count, int64_t tiles, int shift,
-                                                   uint32_t* __restrict__ out, uint32_t* __restrict__ out_count,
-                                                   uint32_t* arrive, const uint32_t* __restrict__ rlo,
-                                                   const uint32_t* __restrict__ rhi,
-                                                   const uint32_t* __restrict__ node_parent, Rec<DIM>* recs,
-                                                   uint4* meta, const Ctrl* ctrl) {
-    if (ctrl->error) return;
-    __shared__ uint32_t s_off[kFitGroup + 1];
-    __shared__ uint32_t s_out, s_in;
-    __shared__ uint32_t s_node[kFitSlots], s_link[kFitSlots], s_arrive[kFitSlots];
-    __shared__ uint32_t s_par[kFitSlots];  // (slot of the parent) << 1 | side, or kNone outside the group
-    __shared__ float s_box[kFitSlots][2][2 * DIM];
-    __shared__ uint32_t s_hash[kFitHash];  // slots
+__global__ __launch_bounds__(kTreeChunk) void k_tree_group(const uint64_t* __restrict__ codes, int64_t n,
+                                                           TreeOut<DIM> a, TreeEntry<DIM>* in,
+                                                           const uint32_t* __restrict__ in_count, int64_t tiles,
+                                                           int64_t leaves, TreeEntry<DIM>* __restrict__ out,
+                                                           uint32_t* __restrict__ out_count) {
+    __shared__ TreeLds<DIM, kTreeChunkShift> s;
+    __shared__ uint32_t s_off[kTreeGroup + 1];
     const int t = threadIdx.x;
-    const int64_t g0 = (int64_t)blockIdx.x * kFitGroup;  // first tile of the group
-    const int up = shift + kFitGroupShift;
-    for (int x = t; x < kFitHash; x += kFitThreads) s_hash[x] = kNone;
-    if (t < kFitGroup) {
-        uint32_t x = g0 + t < tiles ? span_count[g0 + t] : 0u;
+    const int64_t g0 = (int64_t)blockIdx.x * kTreeGroup, first = (int64_t)blockIdx.x * leaves;
+    if (t < kTreeGroup) {
+        uint32_t x = g0 + t < tiles ? in_count[g0 + t] : 0u;
 #pragma unroll
         for (int off = 1; off < 64; off <<= 1) {
             const uint32_t y = __shfl_up(x, off);
             if (t >= off) x += y;
         }
         s_off[t + 1] = x;
-        if (t == 0) s_off[0] = s_out = s_in = 0u;
+        if (t == 0) s_off[0] = 0u;
     }
+    const uint32_t group_split = first > 0 ? (uint32_t)split_bit(codes, first - 1) : 255u;
     __syncthreads();
-    const uint32_t total = s_off[kFitGroup];
-    for (uint32_t x = t; x < total; x += kFitThreads) {
-        int a = 0;  // the tile that listed entry x: the last one that starts at or before it
+    TreeEntry<DIM>* list = in + g0 * kTreeSpan;
+    uint32_t total = s_off[kTreeGroup];
+    bool packed = false;  // (else tile by tile)
+    for (;;) {
+        uint32_t kept = 0, prev_node = (uint32_t)(first - 1), prev_split = group_split;
+        const bool last = total <= kTreeChunk;
+        for (uint32_t c0 = 0; c0 < total; c0 += kTreeChunk) {
+            const uint32_t x = c0 + (uint32_t)t;
+            const int c = (int)min(total - c0, (uint32_t)kTreeChunk);
+            TreeEntry<DIM> e = {};
+            if (x < total) {
+                uint32_t at = x;
+                if (!packed) {
+                    int b = 0;  // the tile of entry x: the last one that starts at or before it
 #pragma unroll
-        for (int b = kFitGroup / 2; b > 0; b >>= 1)
-            if (s_off[a + b] <= x) a += b;
-        const uint32_t k = span[((g0 + a) << shift) + (x - s_off[a])];
-        const uint32_t lo = rlo[k], hi = rhi[k];
-        if ((uint64_t)lo >> up != (uint64_t)hi >> up) {
-            out[((int64_t)blockIdx.x << up) + atomicAdd(&s_out, 1u)] = k;
-            continue;
+                    for (int w = kTreeGroup / 2; w > 0; w >>= 1)
+                        if (s_off[b + w] <= x) b += w;
+                    at = (uint32_t)b * kTreeSpan + (x - s_off[b]);
+                }
+                e = list[at];
+            }
+            kept += tree_tile<DIM, kTreeChunkShift>(s, c, prev_node, prev_split, e, (uint32_t)(n - 1), a,
+                                                    last ? out + (int64_t)blockIdx.x * kTreeSpan : list + kept);
+            prev_node = s.node[c];
+            prev_split = s.top[0][c];
         }
-        const uint32_t slot = atomicAdd(&s_in, 1u);
-        const bool r0 = (uint64_t)lo >> shift == (uint64_t)k >> shift;
-        const bool r1 = (uint64_t)(k + 1u) >> shift == (uint64_t)hi >> shift;
-        arrive[k] = (uint32_t)r0 + (uint32_t)r1;  // (for the climbs in memory)
-        if (slot >= kFitSlots) continue;
-        s_node[slot] = k;
-        s_link[slot] = node_parent[k];
-        s_arrive[slot] = (uint32_t)r0 + (uint32_t)r1;
-        if (r0 || r1) {
-            Child<DIM> c[2];
-            unpack<DIM>(recs[k], c[0], c[1]);
-#pragma unroll
-            for (int side = 0; side < 2; ++side)
-                if (side ? r1 : r0)
-#pragma unroll
-                    for (int d = 0; d < DIM; ++d) {
-                        s_box[slot][side][d] = c[side].lo[d];
-                        s_box[slot][side][DIM + d] = c[side].hi[d];
-                    }
+        if (last) {
+            if (t == 0) out_count[blockIdx.x] = kept;
+            return;
         }
-        // (room for every slot: the table is larger than their number)
-        for (uint32_t h = fit_hash(k); atomicCAS(&s_hash[h], kNone, slot) != kNone; h = (h + 1) % kFitHash) {}
-    }
-    __syncthreads();
-    const uint32_t inside = s_in;
-    if (t == 0) out_count[blockIdx.x] = s_out;
-    if (inside <= kFitSlots) {
-        for (uint32_t x = t; x < inside; x += kFitThreads) {
-            const uint32_t link = s_link[x];
-            uint32_t par = kNone;
-            if (link != kNone)
-                for (uint32_t h = fit_hash(link >> 1); s_hash[h] != kNone; h = (h + 1) % kFitHash)
-                    if (s_node[s_hash[h]] == link >> 1) {
-                        par = (s_hash[h] << 1) | (link & 1u);
-                        break;
-                    }
-            s_par[x] = par;
-            // only climbs change the counts from here on, so the starts are marked now
-            if (s_arrive[x] == 2u) s_arrive[x] = 3u;
-        }
+        __threadfence_block();
         __syncthreads();
-        for (uint32_t x = t; x < inside; x += kFitThreads) {
-            if (s_arrive[x] != 3u) continue;  // a climb arrives here
-            uint32_t cur = x;
-            for (int step = 0; step < 160; ++step) {
-                const uint32_t link = s_link[cur], par = s_par[cur];
-                if (link == kNone) break;  // the root
-                float lo[DIM], hi[DIM];
-#pragma unroll
-                for (int d = 0; d < DIM; ++d) {
-                    lo[d] = fminf(s_box[cur][0][d], s_box[cur][1][d]);
-                    hi[d] = fmaxf(s_box[cur][0][DIM + d], s_box[cur][1][DIM + d]);
-                }
-                set_child<DIM>(recs, meta, link >> 1, (int)(link & 1u), lo, hi, s_node[cur]);
-                if (par == kNone) break;
-                const uint32_t P = par >> 1;
-#pragma unroll
-                for (int d = 0; d < DIM; ++d) {
-                    s_box[P][par & 1u][d] = lo[d];
-                    s_box[P][par & 1u][DIM + d] = hi[d];
-                }
-                lds_fence();
-                if (atomicAdd(&s_arrive[P], 1u) == 0u) break;  // the sibling's climb goes on
-                lds_fence();
-                cur = P;
-            }
-        }
-        return;
-    }
-    for (uint32_t x = t; x < total; x += kFitThreads) {
-        int a = 0;
-#pragma unroll
-        for (int b = kFitGroup / 2; b > 0; b >>= 1)
-            if (s_off[a + b] <= x) a += b;
-        const uint32_t k = span[((g0 + a) << shift) + (x - s_off[a])];
-        const uint32_t klo = rlo[k], khi = rhi[k];
-        if ((uint64_t)klo >> up != (uint64_t)khi >> up) continue;    // listed above
-        if (fit_ready(klo, khi, k, shift) != 2u) continue;  // a climb arrives here
-        uint32_t cur = k;
-        for (int step = 0; step < 160; ++step) {
-            const uint32_t link = node_parent[cur];
-            if (link == kNone) break;  // the root
-            const uint32_t P = link >> 1;
-            const uint32_t plo = rlo[P], phi = rhi[P];
-            Child<DIM> c0, c1;
-            unpack<DIM>(recs[cur], c0, c1);
-            float lo[DIM], hi[DIM];
-#pragma unroll
-            for (int d = 0; d < DIM; ++d) {
-                lo[d] = fminf(c0.lo[d], c1.lo[d]);
-                hi[d] = fmaxf(c0.hi[d], c1.hi[d]);
-            }
-            set_child<DIM>(recs, meta, P, (int)(link & 1u), lo, hi, cur);
-            if ((uint64_t)plo >> up != (uint64_t)phi >> up) break;
-            __threadfence_block();
-            if (__hip_atomic_fetch_add(&arrive[P], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == 0u)
-                break;  // the sibling's climb goes on
-            __threadfence_block();
-            cur = P;
-        }
+        total = kept;
+        packed = true;
     }
 }
 
@@ -777,8 +747,7 @@ __device__ __forceinline__ uint32_t compact2(uint64_t x) {
 // wave_lca[w]: the node over the leaves 64w .. 64w + 63 is the one among the
 // 63 (or fewer) splits between them with the highest split bit, which one
 // wave finds by reading their codes in order (climbing to it from a leaf,
-// one thread per wave of queries, took 301 us at 37M points).  Written over
-// the exchange words of the build, which are dead once the hierarchy exists.
+// one thread per wave of queries, took 301 us at 37M points). 
 //
 // up[k], for every node a climb can pass, that is over 64 leaves or more or
 // over the last leaf: its link and its cell.  A node that splits on a code
@@ -2208,7 +2177,7 @@ __global__ __launch_bounds__(256) void k_batch_edge_write(const uint4* __restric
 // workspace layout
 
 struct Layout {
-    size_t ctrl, bpart, k0, k1, v0, v1, hist, spts, orig, cand_p, recs, meta, height, node_parent, leaf_parent, up, exch, rlo, rhi, run_part, run_carry, qcnt, qoff, qflag, qlist, labels, ub, compkey, compmax, succ, par, cand_d, cand_j, eud, core_s, spare, total;
+    size_t ctrl, bpart, k0, k1, v0, v1, hist, spts, orig, cand_p, recs, meta, height, node_parent, leaf_parent, up, starts, rlo, rhi, run_part, run_carry, qcnt, qoff, qflag, qlist, labels, ub, compkey, compmax, succ, par, cand_d, cand_j, eud, core_s, spare, total;
 };
 
 static size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -2255,7 +2224,7 @@ static Layout make_layout(int64_t n, int dim) {
     L.node_parent = take(4 * M);
     L.leaf_parent = take(4 * N);
     L.up = take(sizeof(Up) * M);
-    L.exch = take(8 * M);
+    L.starts = take(8 * M);
     L.rlo = take(4 * M);
     L.rhi = take(4 * M);
     L.run_part = take(8 * (N / kRunTile + 2));
@@ -2557,7 +2526,7 @@ struct Bufs {
     uint8_t* height;
     uint32_t *node_parent, *leaf_parent;
     Up* up;
-    uint64_t* exch;
+    uint32_t* starts;
     uint32_t *rlo, *rhi, *run_part, *run_carry, *labels, *ub;
     uint32_t *qcnt, *qoff, *qlist;
     uint8_t* qflag;
@@ -2586,7 +2555,7 @@ Bufs<DIM> carve(char* ws, const Layout& L, int64_t n) {
     b.node_parent = reinterpret_cast<uint32_t*>(ws + L.node_parent);
     b.leaf_parent = reinterpret_cast<uint32_t*>(ws + L.leaf_parent);
     b.up = reinterpret_cast<Up*>(ws + L.up);
-    b.exch = reinterpret_cast<uint64_t*>(ws + L.exch);
+    b.starts = reinterpret_cast<uint32_t*>(ws + L.starts);
     b.rlo = reinterpret_cast<uint32_t*>(ws + L.rlo);
     b.rhi = reinterpret_cast<uint32_t*>(ws + L.rhi);
     b.run_part = reinterpret_cast<uint32_t*>(ws + L.run_part);
@@ -3051,34 +3020,32 @@ static int batch_edges(emst_ctx* ctx, Bufs<3>& b, int64_t n, const uint32_t* clo
     return EMST_OK;
 }
 
-// Hierarchy and every box (see k_tree_tiles).  The lists of nodes across tile
-// borders go to the sort's value buffers, their numbers to its histogram and
-// the arrival counts to the exchange words (all free by then: tile counts of
-// all levels are fewer than the histogram's words).  The control block names
-// the root and the height once the first kernel has run: with `mirror` its
-// copy is queued right behind that kernel and `ev` marks its arrival, so that
-// the host reads it while the other levels run.
+// Hierarchy and every box (see k_tree_tiles).  The entries of the levels alternate
+// between the cells' array and the edge slots, their numbers lie one after another
+// in the sort's histogram (all free until the rounds, and large enough: 7,720 bytes
+// per 512 points against 16,384, and per 32,768 points against 8,208 at least).
+// The control block names the root and the height: with `mirror` its copy is queued
+// and `ev` marks its arrival.
 template <int DIM>
 int build_hierarchy(emst_ctx* ctx, Bufs<DIM>& b, const uint64_t* codes, int64_t n, hipStream_t st,
                     Ctrl* mirror = nullptr, hipEvent_t ev = nullptr) {
-    uint32_t* list = b.v1;
-    uint32_t* next[2] = {b.v0, b.v1};
-    uint32_t* arrive = reinterpret_cast<uint32_t*>(b.exch);
+    const TreeOut<DIM> out{b.recs, b.meta, b.rlo, b.rhi, b.node_parent, b.ctrl};
+    TreeEntry<DIM>* list[2] = {reinterpret_cast<TreeEntry<DIM>*>(b.up), reinterpret_cast<TreeEntry<DIM>*>(b.eud)};
     uint32_t* counts = b.hist;
     int64_t tiles = (n + kFitTile - 1) / kFitTile;
-    k_tree_tiles<DIM><<<(unsigned)tiles, kFitTile, 0, st>>>(codes, b.spts, b.orig, n, b.recs, b.meta, b.rlo, b.rhi,
-                                                            b.node_parent, b.exch, list, counts, b.ctrl);
+    k_tree_tiles<DIM><<<(unsigned)tiles, kFitTile, 0, st>>>(codes, b.spts, b.orig, n, out, list[0], counts);
+    int64_t leaves = kFitTile;
+    for (int lvl = 0; tiles > 1; ++lvl) {
+        const int64_t groups = (tiles + kTreeGroup - 1) / kTreeGroup;
+        leaves *= kTreeGroup;
+        k_tree_group<DIM><<<(unsigned)groups, kTreeChunk, 0, st>>>(codes, n, out, list[lvl & 1], counts, tiles, leaves,
+                                                                   list[(lvl + 1) & 1], counts + tiles);
+        counts += tiles;
+        tiles = groups;
+    }
     if (mirror) {
         HIP_TRY(hipMemcpyAsync(mirror, b.ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, st));
         HIP_TRY(hipEventRecord(ev, st));
-    }
-    for (int shift = kFitShift, lvl = 0; tiles > 1; shift += kFitGroupShift, ++lvl) {
-        const int64_t groups = (tiles + kFitGroup - 1) / kFitGroup;
-        k_fit_group<DIM><<<(unsigned)groups, kFitThreads, 0, st>>>(list, counts, tiles, shift, next[lvl & 1], counts + tiles,
-                                                           arrive, b.rlo, b.rhi, b.node_parent, b.recs, b.meta, b.ctrl);
-        list = next[lvl & 1];
-        counts += tiles;
-        tiles = groups;
     }
     HIP_TRY(hipGetLastError());
     return EMST_OK;
@@ -3187,7 +3154,7 @@ template <int DIM>
 static TraverseArgs<DIM> job_args(const Job& j, const Bufs<DIM>& b) {
     TraverseArgs<DIM> ta = traverse_args<DIM>(b, j.n, j.root);
     ta.lds_depth = j.lds_depth;
-    if (wave_starts(j)) ta.wave_lca = reinterpret_cast<const uint32_t*>(b.exch);  // (free once the tree is built)
+    if (wave_starts(j)) ta.wave_lca = b.starts;
     if (j.k_pts >= 2) ta.core_s = b.core_s;
     return ta;
 }
@@ -3211,7 +3178,7 @@ int job_enqueue(emst_ctx* ctx, Job& j, hipStream_t st) {
         HIP_TRY(radix_sort_pairs(st, b.k0, b.v0, b.k1, b.v1, b.hist, n, shifts, 8, &j.codes_in1));
         const uint64_t* codes = j.codes_in1 ? b.k1 : b.k0;
         k_gather<DIM><<<grid_for(n), 256, 0, st>>>(j.pts, j.codes_in1 ? b.v1 : b.v0, n, b.spts, b.orig,
-                                                   b.labels, b.exch);
+                                                   b.labels);
         return build_hierarchy<DIM>(ctx, b, codes, n, st, j.h, ctx->sev[0]);
     }
     case kPhRank: {
@@ -3232,13 +3199,13 @@ int job_enqueue(emst_ctx* ctx, Job& j, hipStream_t st) {
         HIP_TRY(radix_sort_pairs(st, b.k0, b.v0, b.k1, b.v1, b.hist, n, csh, cq, &j.codes_in1));
         const uint64_t* codes = j.codes_in1 ? b.k1 : b.k0;
         k_gather<DIM><<<grid_for(n), 256, 0, st>>>(j.pts, j.codes_in1 ? b.v1 : b.v0, n, b.spts, b.orig,
-                                                   b.labels, b.exch);
+                                                   b.labels);
         return build_hierarchy<DIM>(ctx, b, codes, n, st, j.h, ctx->sev[0]);
     }
     case kPhFit: {  // wave starts and their Morton cells, core distances; then round 0
         if (wave_starts(j)) {
             k_starts<DIM><<<grid_for(n), 256, 0, st>>>(j.codes_in1 ? b.k1 : b.k0, b.rlo, b.rhi, b.node_parent, n, j.mp,
-                                                       j.ranks, reinterpret_cast<uint32_t*>(b.exch), b.up);
+                                                       j.ranks, b.starts, b.up);
             HIP_TRY(hipGetLastError());
         }
         TraverseArgs<DIM> ta = job_args<DIM>(j, b);
@@ -3629,11 +3596,11 @@ int batched_impl(emst_ctx* ctx, const float* pts, const int64_t* h_offsets, cons
     const uint64_t* codes = in1 ? b.k1 : b.k0;
     const uint32_t* perm = in1 ? b.v1 : b.v0;
     // ---- one tree over all clouds
-    k_gather<3><<<grid_for(n), 256, 0, st>>>(pts3, perm, n, b.spts, b.orig, b.labels, b.exch);
-    // (a batch of single points runs no round, which would write every slot)
-    if (n <= nonempty) k_fill_u32<<<grid_for(4 * n), 256, 0, st>>>(reinterpret_cast<uint32_t*>(b.eud), 4 * n, kNone);
+    k_gather<3><<<grid_for(n), 256, 0, st>>>(pts3, perm, n, b.spts, b.orig, b.labels);
     k_batch_sorted_cloud<<<grid_for(n), 256, 0, st>>>(cloud_of, perm, n, cloud_sorted);
     if (int rc = build_tree<3>(ctx, b, codes, n, st)) return rc;
+    // (a batch of single points runs no round, which would write every slot)
+    if (n <= nonempty) k_fill_u32<<<grid_for(4 * n), 256, 0, st>>>(reinterpret_cast<uint32_t*>(b.eud), 4 * n, kNone);
     k_fill_u32<<<grid_for(B), 256, 0, st>>>(d_croot, B, kNone);
     k_cloud_roots<<<grid_for(n - 1), 256, 0, st>>>(b.rlo, b.rhi, cloud_sorted, d_cin, n - 1, d_croot);
     HIP_TRY(hipGetLastError());
@@ -3918,7 +3885,7 @@ static int bjob_enqueue(emst_ctx* ctx, BJob& j, hipStream_t st, Ctrl* mirror, in
         HIP_TRY(radix_sort_pairs(st, b.k0, b.v0, b.k1, b.v1, b.hist, n, j.shifts, j.nshifts, &j.codes_in1));
         const uint64_t* codes = j.codes_in1 ? b.k1 : b.k0;
         const uint32_t* perm = j.codes_in1 ? b.v1 : b.v0;
-        k_gather<3><<<grid_for(n), 256, 0, st>>>(x.pts3, perm, n, b.spts, b.orig, b.labels, b.exch);
+        k_gather<3><<<grid_for(n), 256, 0, st>>>(x.pts3, perm, n, b.spts, b.orig, b.labels);
         k_batch_sorted_cloud<<<grid_for(n), 256, 0, st>>>(x.cloud_of, perm, n, x.cloud_sorted);
         if (int rc = build_hierarchy<3>(ctx, b, codes, n, st)) return rc;
         j.wait = true;
@@ -4634,13 +4601,12 @@ namespace emst {
 
 __global__ __launch_bounds__(256) void k_test_prep(const uint32_t* __restrict__ leaf_labels, int64_t n,
                                                    float* __restrict__ spts, uint32_t* __restrict__ orig,
-                                                   uint32_t* __restrict__ labels, uint64_t* __restrict__ exch) {
+                                                   uint32_t* __restrict__ labels) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     spts[3 * i] = spts[3 * i + 1] = spts[3 * i + 2] = 0.f;
     orig[i] = (uint32_t)i;
     labels[i] = leaf_labels[i];
-    if (i + 1 < n) exch[i] = ~0ull;
 }
 
 __global__ __launch_bounds__(256) void k_test_extract(const uint4* __restrict__ meta,
@@ -4887,7 +4853,6 @@ extern "C" int emst_test_tree_from_codes(emst_ctx* ctx, const uint64_t* d_codes,
     float* spts = reinterpret_cast<float*>(ws + L.spts);
     uint32_t* orig = reinterpret_cast<uint32_t*>(ws + L.orig);
     uint32_t* labels = reinterpret_cast<uint32_t*>(ws + L.labels);
-    uint64_t* exch = reinterpret_cast<uint64_t*>(ws + L.exch);
     uint32_t* rlo = reinterpret_cast<uint32_t*>(ws + L.rlo);
     uint32_t* rhi = reinterpret_cast<uint32_t*>(ws + L.rhi);
     uint32_t* run_part = reinterpret_cast<uint32_t*>(ws + L.run_part);
@@ -4895,7 +4860,7 @@ extern "C" int emst_test_tree_from_codes(emst_ctx* ctx, const uint64_t* d_codes,
     uint4* meta = reinterpret_cast<uint4*>(ws + L.meta);
     uint32_t* node_parent = reinterpret_cast<uint32_t*>(ws + L.node_parent);
     k_init_ctrl<<<1, 64, 0, st>>>(ctrl);
-    k_test_prep<<<grid_for(n), 256, 0, st>>>(d_leaf_labels, n, spts, orig, labels, exch);
+    k_test_prep<<<grid_for(n), 256, 0, st>>>(d_leaf_labels, n, spts, orig, labels);
     Bufs<3> b = carve<3>(ws, L, n);
     if (int rc = build_hierarchy<3>(ctx, b, d_codes, n, st)) return rc;
     HIP_TRY(propagate_labels(labels, run_part, run_carry, rlo, rhi, meta, n, ctrl, st));
@@ -4965,7 +4930,7 @@ extern "C" int emst_test_tree_boxes(emst_ctx* ctx, const float* d_points, int64_
     HIP_TRY(radix_sort_pairs(st, b.k0, b.v0, b.k1, b.v1, b.hist, n, shifts, 8, &in1));
     const uint64_t* codes = in1 ? b.k1 : b.k0;
     const uint32_t* perm = in1 ? b.v1 : b.v0;
-    k_gather<3><<<grid_for(n), 256, 0, st>>>(d_points, perm, n, b.spts, b.orig, b.labels, b.exch);
+    k_gather<3><<<grid_for(n), 256, 0, st>>>(d_points, perm, n, b.spts, b.orig, b.labels);
     if (int rc = build_tree<3>(ctx, b, codes, n, st)) return rc;
     k_test_boxes<<<grid_for(n - 1), 256, 0, st>>>(b.recs, b.meta, n - 1, d_left, d_right, d_lo, d_hi);
     HIP_TRY(hipGetLastError());
