@@ -107,6 +107,22 @@ __device__ __forceinline__ void init_ctrl(Ctrl* ctrl) {
     for (uint32_t& c : ctrl->flat_comps) c = 0;
 }
 
+// The host's copy of the control block (mirror: pinned memory), by the first wave
+// of a workgroup all of which has called __threadfence() after its last change.
+// The host, which has cleared mirror->arrived, reads it while the next kernels
+// run (await_mirror): a copy and an event queued behind the kernel kept the
+// device from those for 10 us each time.
+__device__ __forceinline__ void mirror_ctrl(const Ctrl* ctrl, Ctrl* mirror) {
+    static_assert(sizeof(Ctrl) <= 256 && offsetof(Ctrl, arrived) < 256, "one word per lane");
+    if (threadIdx.x >= 64u) return;
+    uint32_t* m = reinterpret_cast<uint32_t*>(mirror);
+    if (threadIdx.x < offsetof(Ctrl, arrived) / 4)
+        __hip_atomic_store(m + threadIdx.x, load_relaxed(reinterpret_cast<const uint32_t*>(ctrl) + threadIdx.x),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __threadfence_system();
+    if (threadIdx.x == 0) __hip_atomic_store(&mirror->arrived, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 __global__ void k_init_ctrl(Ctrl* ctrl) {
     if (threadIdx.x == 0) init_ctrl(ctrl);
 }
@@ -630,7 +646,7 @@ __global__ __launch_bounds__(kFitTile) void k_tree_tiles(const uint64_t* __restr
                                                          const float* __restrict__ spts,
                                                          const uint32_t* __restrict__ orig, int64_t n,
                                                          TreeOut<DIM> a, TreeEntry<DIM>* __restrict__ out,
-                                                         uint32_t* __restrict__ out_count) {
+                                                         uint32_t* __restrict__ out_count, Ctrl* mirror) {
     __shared__ TreeLds<DIM, kFitShift> s;
     const int t = threadIdx.x;
     const int64_t t0 = (int64_t)blockIdx.x * kFitTile, i = t0 + t, m = n - 1;
@@ -655,6 +671,11 @@ __global__ __launch_bounds__(kFitTile) void k_tree_tiles(const uint64_t* __restr
     const uint32_t left = tree_tile<DIM, kFitShift>(s, (int)min<int64_t>(kFitTile, n - t0), (uint32_t)(t0 - 1), prev, e,
                                                     (uint32_t)m, a, out + (int64_t)blockIdx.x * kTreeSpan);
     if (t == 0) out_count[blockIdx.x] = left;
+    if (mirror && gridDim.x == 1) {
+        __threadfence();
+        __syncthreads();
+        mirror_ctrl(a.ctrl, mirror);
+    }
 }
 
 // One workgroup joins kTreeGroup tiles of the level below, whose entries lie
@@ -667,7 +688,7 @@ __global__ __launch_bounds__(kTreeChunk) void k_tree_group(const uint64_t* __res
                                                            TreeOut<DIM> a, TreeEntry<DIM>* in,
                                                            const uint32_t* __restrict__ in_count, int64_t tiles,
                                                            int64_t leaves, TreeEntry<DIM>* __restrict__ out,
-                                                           uint32_t* __restrict__ out_count) {
+                                                           uint32_t* __restrict__ out_count, Ctrl* mirror) {
     __shared__ TreeLds<DIM, kTreeChunkShift> s;
     __shared__ uint32_t s_off[kTreeGroup + 1];
     const int t = threadIdx.x;
@@ -712,6 +733,11 @@ __global__ __launch_bounds__(kTreeChunk) void k_tree_group(const uint64_t* __res
         }
         if (last) {
             if (t == 0) out_count[blockIdx.x] = kept;
+            if (mirror && gridDim.x == 1) {  // (the root is known)
+                __threadfence();
+                __syncthreads();
+                mirror_ctrl(a.ctrl, mirror);
+            }
             return;
         }
         __threadfence_block();
@@ -1623,7 +1649,7 @@ template <int PER>
 __global__ __launch_bounds__(256) void k_relabel(uint32_t* labels, const uint32_t* __restrict__ par, int64_t n,
                                                  int steps, uint32_t* __restrict__ tile_part,
                                                  const uint2* __restrict__ part, int nparts, Ctrl* ctrl,
-                                                 int64_t target) {
+                                                 int64_t target, Ctrl* mirror) {
     __shared__ uint32_t s_new[run_lds_words(PER)];
     __shared__ uint32_t s_w[8];
     const int tid = threadIdx.x;
@@ -1709,6 +1735,12 @@ __global__ __launch_bounds__(256) void k_relabel(uint32_t* labels, const uint32_
     if (tid == 0) {
         tile_part[2 * blockIdx.x] = hmax;
         tile_part[2 * blockIdx.x + 1] = tmin;
+    }
+    // (the wave that has completed the block; kErrJump of another workgroup may come
+    // with the next round's)
+    if (mirror && blockIdx.x == 0 && tid < 64) {
+        __threadfence();
+        mirror_ctrl(ctrl, mirror);
     }
 }
 
@@ -2602,6 +2634,23 @@ TraverseArgs<DIM> traverse_args(const Bufs<DIM>& b, int64_t n, uint32_t root) {
     return ta;
 }
 
+// Waits until a kernel on st has filled the mirror (see mirror_ctrl).  The
+// stream is asked now and then, so that a failed launch ends the wait.
+static int await_mirror(emst_ctx* ctx, Ctrl* mirror, hipStream_t st) {
+    for (uint32_t spin = 1;; ++spin) {
+        if (__atomic_load_n(&mirror->arrived, __ATOMIC_ACQUIRE)) return EMST_OK;
+        if (spin % 4096u == 0u) {
+            const hipError_t e = hipStreamQuery(st);
+            if (e == hipSuccess) {
+                if (__atomic_load_n(&mirror->arrived, __ATOMIC_ACQUIRE)) return EMST_OK;
+                return fail(ctx, EMST_EHIP, "a round did not report");
+            }
+            if (e != hipErrorNotReady) return fail(ctx, EMST_EHIP, hipGetErrorString(e));
+        }
+        __builtin_ia32_pause();
+    }
+}
+
 int read_ctrl(emst_ctx* ctx, Ctrl* ctrl, hipStream_t st) {
     HIP_TRY(hipMemcpyAsync(ctx->h_ctrl, ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
@@ -2658,10 +2707,11 @@ __global__ __launch_bounds__(256) void k_test_capture(const uint32_t* __restrict
     cap.comp_v[o] = has ? (int32_t)v : -1;
 }
 
-// One Boruvka round, enqueued on st (no host wait).
+// One Boruvka round, enqueued on st (no host wait).  mirror (nullable, pinned
+// host memory) receives the control block.
 template <int DIM>
 int enqueue_round(emst_ctx* ctx, Bufs<DIM>& b, TraverseArgs<DIM>& ta, int64_t n, int round, int height,
-                  int variant, const uint32_t* cloud_of, int64_t target, bool prof, hipStream_t st,
+                  int variant, const uint32_t* cloud_of, int64_t target, bool prof, hipStream_t st, Ctrl* mirror,
                   const RoundCapture* cap = nullptr) {
     hipEvent_t* E = ctx->ev;
     // record labels and bounds; the run partials of round r > 0 come from
@@ -2743,7 +2793,8 @@ int enqueue_round(emst_ctx* ctx, Bufs<DIM>& b, TraverseArgs<DIM>& ta, int64_t n,
     k_merge_jump<<<merge_grid, 256, 0, st>>>(b.labels, b.par, n, 1024, b.ctrl, first, rl);
     with_run_per(per, [&](auto P) {
         k_relabel<P.value><<<nt, 256, 0, st>>>(b.labels, b.par, n, 4096, b.run_part,
-                                               reinterpret_cast<const uint2*>(b.bpart), mp_blocks, b.ctrl, target);
+                                               reinterpret_cast<const uint2*>(b.bpart), mp_blocks, b.ctrl, target,
+                                               mirror);
     });
     HIP_TRY(hipGetLastError());
     return EMST_OK;
@@ -2796,9 +2847,9 @@ int round_pair_graph(emst_ctx* ctx, Bufs<DIM>& b, TraverseArgs<DIM>& ta, int64_t
         }
     if (!ctx->cap_stream) HIP_TRY(hipStreamCreateWithFlags(&ctx->cap_stream, hipStreamNonBlocking));
     HIP_TRY(hipStreamBeginCapture(ctx->cap_stream, hipStreamCaptureModeThreadLocal));
-    int rc = enqueue_round<DIM>(ctx, b, ta, n, 2, height, variant, cloud_of, target, false, ctx->cap_stream);
+    int rc = enqueue_round<DIM>(ctx, b, ta, n, 2, height, variant, cloud_of, target, false, ctx->cap_stream, nullptr);
     if (rc == EMST_OK)
-        rc = enqueue_round<DIM>(ctx, b, ta, n, 3, height, variant, cloud_of, target, false, ctx->cap_stream);
+        rc = enqueue_round<DIM>(ctx, b, ta, n, 3, height, variant, cloud_of, target, false, ctx->cap_stream, nullptr);
     hipGraph_t graph = nullptr;
     const hipError_t ec = hipStreamEndCapture(ctx->cap_stream, &graph);
     if (rc) {
@@ -2884,10 +2935,8 @@ int run_rounds(emst_ctx* ctx, Bufs<DIM>& b, TraverseArgs<DIM>& ta, int64_t n, in
     const bool graphs = ctx->graphs && !prof && !ctx->counting;
     Ctrl* mirror[2] = {ctx->h_ctrl, ctx->h_ctrl + 1};
     auto queue = [&](int r) -> int {
-        if (int rc = enqueue_round<DIM>(ctx, b, ta, n, r, height, variant, cloud_of, target, prof, st)) return rc;
-        HIP_TRY(hipMemcpyAsync(mirror[r & 1], b.ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipEventRecord(ctx->sev[r & 1], st));
-        return EMST_OK;
+        mirror[r & 1]->arrived = 0u;
+        return enqueue_round<DIM>(ctx, b, ta, n, r, height, variant, cloud_of, target, prof, st, mirror[r & 1]);
     };
     if (n <= target) {  // every cloud is a single point: no round at all
         S.rounds = 0;
@@ -2911,7 +2960,10 @@ int run_rounds(emst_ctx* ctx, Bufs<DIM>& b, TraverseArgs<DIM>& ta, int64_t n, in
             if (int rc = queue(round + 1)) return rc;
             queued = round + 1;
         }
-        HIP_TRY(hipEventSynchronize(ctx->sev[round & 1]));
+        if (int rc = await_mirror(ctx, mirror[round & 1], st)) {
+            (void)hipStreamSynchronize(st);
+            return rc;
+        }
         const Ctrl* h = mirror[round & 1];
         S.components[round] = ncomp;
         S.queries_round[round] = uses_qlist(variant, round, n) ? (int64_t)h->qcount : n;
@@ -3024,28 +3076,26 @@ static int batch_edges(emst_ctx* ctx, Bufs<3>& b, int64_t n, const uint32_t* clo
 // between the cells' array and the edge slots, their numbers lie one after another
 // in the sort's histogram (all free until the rounds, and large enough: 7,720 bytes
 // per 512 points against 16,384, and per 32,768 points against 8,208 at least).
-// The control block names the root and the height: with `mirror` its copy is queued
-// and `ev` marks its arrival.
+// The control block names the root and the height; `mirror` (pinned host memory)
+// receives a copy.
 template <int DIM>
 int build_hierarchy(emst_ctx* ctx, Bufs<DIM>& b, const uint64_t* codes, int64_t n, hipStream_t st,
-                    Ctrl* mirror = nullptr, hipEvent_t ev = nullptr) {
+                    Ctrl* mirror = nullptr) {
+    if (mirror) mirror->arrived = 0u;
     const TreeOut<DIM> out{b.recs, b.meta, b.rlo, b.rhi, b.node_parent, b.ctrl};
     TreeEntry<DIM>* list[2] = {reinterpret_cast<TreeEntry<DIM>*>(b.up), reinterpret_cast<TreeEntry<DIM>*>(b.eud)};
     uint32_t* counts = b.hist;
     int64_t tiles = (n + kFitTile - 1) / kFitTile;
-    k_tree_tiles<DIM><<<(unsigned)tiles, kFitTile, 0, st>>>(codes, b.spts, b.orig, n, out, list[0], counts);
+    k_tree_tiles<DIM><<<(unsigned)tiles, kFitTile, 0, st>>>(codes, b.spts, b.orig, n, out, list[0], counts,
+                                                            mirror);
     int64_t leaves = kFitTile;
     for (int lvl = 0; tiles > 1; ++lvl) {
         const int64_t groups = (tiles + kTreeGroup - 1) / kTreeGroup;
         leaves *= kTreeGroup;
         k_tree_group<DIM><<<(unsigned)groups, kTreeChunk, 0, st>>>(codes, n, out, list[lvl & 1], counts, tiles, leaves,
-                                                                   list[(lvl + 1) & 1], counts + tiles);
+                                                                   list[(lvl + 1) & 1], counts + tiles, mirror);
         counts += tiles;
         tiles = groups;
-    }
-    if (mirror) {
-        HIP_TRY(hipMemcpyAsync(mirror, b.ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipEventRecord(ev, st));
     }
     HIP_TRY(hipGetLastError());
     return EMST_OK;
@@ -3062,9 +3112,9 @@ static int check_hierarchy(emst_ctx* ctx, const Ctrl* h, int64_t n) {
 // height.
 template <int DIM>
 int build_tree(emst_ctx* ctx, Bufs<DIM>& b, const uint64_t* codes, int64_t n, hipStream_t st) {
-    if (int rc = build_hierarchy<DIM>(ctx, b, codes, n, st, ctx->h_ctrl, ctx->sev[0])) return rc;
-    HIP_TRY(hipEventSynchronize(ctx->sev[0]));
-    const int rc = check_hierarchy(ctx, ctx->h_ctrl, n);
+    if (int rc = build_hierarchy<DIM>(ctx, b, codes, n, st, ctx->h_ctrl)) return rc;
+    int rc = await_mirror(ctx, ctx->h_ctrl, st);
+    if (!rc) rc = check_hierarchy(ctx, ctx->h_ctrl, n);
     if (rc) (void)hipStreamSynchronize(st);  // nothing stays queued on the caller's workspace
     return rc;
 }
@@ -3179,7 +3229,7 @@ int job_enqueue(emst_ctx* ctx, Job& j, hipStream_t st) {
         const uint64_t* codes = j.codes_in1 ? b.k1 : b.k0;
         k_gather<DIM><<<grid_for(n), 256, 0, st>>>(j.pts, j.codes_in1 ? b.v1 : b.v0, n, b.spts, b.orig,
                                                    b.labels);
-        return build_hierarchy<DIM>(ctx, b, codes, n, st, j.h, ctx->sev[0]);
+        return build_hierarchy<DIM>(ctx, b, codes, n, st, j.h);
     }
     case kPhRank: {
         // many equal codes: rebuild on rank-space codes (the node records
@@ -3200,7 +3250,7 @@ int job_enqueue(emst_ctx* ctx, Job& j, hipStream_t st) {
         const uint64_t* codes = j.codes_in1 ? b.k1 : b.k0;
         k_gather<DIM><<<grid_for(n), 256, 0, st>>>(j.pts, j.codes_in1 ? b.v1 : b.v0, n, b.spts, b.orig,
                                                    b.labels);
-        return build_hierarchy<DIM>(ctx, b, codes, n, st, j.h, ctx->sev[0]);
+        return build_hierarchy<DIM>(ctx, b, codes, n, st, j.h);
     }
     case kPhFit: {  // wave starts and their Morton cells, core distances; then round 0
         if (wave_starts(j)) {
@@ -3225,15 +3275,14 @@ int job_enqueue(emst_ctx* ctx, Job& j, hipStream_t st) {
         }
         j.phase = kPhRound;  // round 0 goes out with this phase
         j.S.components[0] = n;
-        if (int rc = enqueue_round<DIM>(ctx, b, ta, n, 0, j.height, j.variant, nullptr, 1, j.prof, st)) return rc;
-        break;
+        j.h->arrived = 0u;
+        return enqueue_round<DIM>(ctx, b, ta, n, 0, j.height, j.variant, nullptr, 1, j.prof, st, j.h);
     }
     case kPhRound: {
         TraverseArgs<DIM> ta = job_args<DIM>(j, b);
         j.S.components[j.round] = j.ncomp;
-        if (int rc = enqueue_round<DIM>(ctx, b, ta, n, j.round, j.height, j.variant, nullptr, 1, j.prof, st))
-            return rc;
-        break;
+        j.h->arrived = 0u;
+        return enqueue_round<DIM>(ctx, b, ta, n, j.round, j.height, j.variant, nullptr, 1, j.prof, st, j.h);
     }
     case kPhFinal: {  // canonical order (the full sort only after a long run of ties)
         const uint32_t* order = nullptr;
@@ -3324,15 +3373,12 @@ int job_advance(emst_ctx* ctx, Job& j) {
 template <int DIM>
 int job_rounds(emst_ctx* ctx, Job& j, hipStream_t st) {
     Ctrl* mirror[2] = {ctx->h_ctrl, ctx->h_ctrl + 1};
-    HIP_TRY(hipEventRecord(ctx->sev[0], st));
     const Layout L = make_layout(j.n, DIM);
     Bufs<DIM> b = carve<DIM>(j.ws, L, j.n);
     TraverseArgs<DIM> ta = job_args<DIM>(j, b);
     auto queue = [&](int r) -> int {
-        if (int rc = enqueue_round<DIM>(ctx, b, ta, j.n, r, j.height, j.variant, nullptr, 1, j.prof, st)) return rc;
-        HIP_TRY(hipMemcpyAsync(mirror[r & 1], b.ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipEventRecord(ctx->sev[r & 1], st));
-        return EMST_OK;
+        mirror[r & 1]->arrived = 0u;
+        return enqueue_round<DIM>(ctx, b, ta, j.n, r, j.height, j.variant, nullptr, 1, j.prof, st, mirror[r & 1]);
     };
     int queued = 0;      // last round on the stream
     int64_t prev = 0;    // components entering the previous round (0: none yet)
@@ -3343,7 +3389,7 @@ int job_rounds(emst_ctx* ctx, Job& j, hipStream_t st) {
             if (int rc = queue(r + 1)) return rc;
             queued = r + 1;
         }
-        HIP_TRY(hipEventSynchronize(ctx->sev[r & 1]));
+        if (int rc = await_mirror(ctx, mirror[r & 1], st)) return rc;
         j.h = mirror[r & 1];
         j.round = r;
         j.S.components[r] = now;
@@ -3375,9 +3421,9 @@ int job_run(emst_ctx* ctx, Job& j, hipStream_t st) {
             }
             continue;
         }
-        // the tree phases' control block arrives before their boxes are done
         const bool tree = rc == EMST_OK && (j.phase == kPhTree || j.phase == kPhRank);
-        const hipError_t w = tree ? hipEventSynchronize(ctx->sev[0]) : hipStreamSynchronize(st);
+        if (tree) rc = await_mirror(ctx, j.h, st);
+        const hipError_t w = tree && !rc ? hipSuccess : hipStreamSynchronize(st);
         if (rc) return rc;
         if (w != hipSuccess) return fail(ctx, EMST_EHIP, hipGetErrorString(w));
         if (int rc2 = job_advance<DIM>(ctx, j)) {
@@ -3887,29 +3933,28 @@ static int bjob_enqueue(emst_ctx* ctx, BJob& j, hipStream_t st, Ctrl* mirror, in
         const uint32_t* perm = j.codes_in1 ? b.v1 : b.v0;
         k_gather<3><<<grid_for(n), 256, 0, st>>>(x.pts3, perm, n, b.spts, b.orig, b.labels);
         k_batch_sorted_cloud<<<grid_for(n), 256, 0, st>>>(x.cloud_of, perm, n, x.cloud_sorted);
-        if (int rc = build_hierarchy<3>(ctx, b, codes, n, st)) return rc;
         j.wait = true;
-        break;
+        return build_hierarchy<3>(ctx, b, codes, n, st, mirror);
     }
     case kBFit: {  // every cloud's subtree root, the first round
         k_fill_u32<<<grid_for(j.B), 256, 0, st>>>(x.croot, j.B, kNone);
         k_cloud_roots<<<grid_for(n - 1), 256, 0, st>>>(b.rlo, b.rhi, x.cloud_sorted, x.cin, n - 1, x.croot);
         HIP_TRY(hipGetLastError());
         TraverseArgs<3> ta = bjob_args(j, x);
-        if (int rc = enqueue_round<3>(ctx, b, ta, n, 0, j.height, j.variant, x.cloud_sorted, j.B, false, st))
+        if (int rc = enqueue_round<3>(ctx, b, ta, n, 0, j.height, j.variant, x.cloud_sorted, j.B, false, st, mirror))
             return rc;
         j.next_round = 1;
         j.phase = kBRound;
-        break;
+        return EMST_OK;
     }
     case kBRound: {
         if (j.next_round >= 64) return fail(ctx, EMST_EINTERNAL, "too many rounds");
         TraverseArgs<3> ta = bjob_args(j, x);
         if (int rc = enqueue_round<3>(ctx, b, ta, n, j.next_round, j.height, j.variant, x.cloud_sorted, j.B, false,
-                                      st))
+                                      st, mirror))
             return rc;
         ++j.next_round;
-        break;
+        return EMST_OK;
     }
     case kBFinal: {  // per-cloud canonical order (the full sort only after a long run of ties)
         if (int rc = batch_edges(ctx, b, n, x.cloud_sorted, x.cin, j.cloud_bits,
@@ -4739,7 +4784,8 @@ int test_round(emst_ctx* ctx, const float* pts, int64_t n, const int32_t* comp, 
     rl.cap = root_list_cap(n);
     k_test_root_list<<<root_list_blocks(n), 256, 0, st>>>(b.labels, n, rl);
     HIP_TRY(hipGetLastError());
-    if (int rc = enqueue_round<DIM>(ctx, b, ta, n, round, j.height, variant, nullptr, 1, false, st, &cap)) return rc;
+    if (int rc = enqueue_round<DIM>(ctx, b, ta, n, round, j.height, variant, nullptr, 1, false, st, nullptr, &cap))
+        return rc;
     k_test_comp_out<<<grid_for(n), 256, 0, st>>>(b.labels, b.orig, n, comp_out);
     HIP_TRY(hipGetLastError());
     if (int rc = read_ctrl(ctx, b.ctrl, st)) return rc;

@@ -29,7 +29,7 @@ struct Ctrl {
     uint32_t rounds_run;     // rounds that ran before the loop reached its target
     uint32_t flat_bad;       // clouds without a tree: 1 non-finite coordinate, 2 overflowing extent
     uint32_t flat_comps[17]; // clouds without a tree: components each round left (0: it did not run)
-    uint32_t pad;
+    uint32_t arrived;        // in a host mirror: the copy is complete (see mirror_ctrl)
 };
 static_assert(sizeof(Ctrl) <= 256, "the control block keeps its place in the workspace");
 
