@@ -437,8 +437,8 @@ __device__ __forceinline__ int split_bit(const uint64_t* __restrict__ codes, int
 // rebuilt on rank-space codes.
 __host__ __device__ inline bool many_dups(uint32_t dups, int64_t n) { return (int64_t)dups * 64 > n; }
 
-constexpr int kFitShift = 9;
-constexpr int kFitTile = 1 << kFitShift;
+constexpr int kTreeTileShift = 9;
+constexpr int kTreeTile = 1 << kTreeTileShift;
 
 constexpr int kTreeSpan = 193;      // entries a tile leaves at most, and some
 constexpr int kTreeGroupShift = 6;  // tiles joined at a time
@@ -642,14 +642,14 @@ __device__ __forceinline__ uint32_t tree_tile(TreeLds<DIM, LOG>& s, int c, uint3
 }
 
 template <int DIM>
-__global__ __launch_bounds__(kFitTile) void k_tree_tiles(const uint64_t* __restrict__ codes,
+__global__ __launch_bounds__(kTreeTile) void k_tree_tiles(const uint64_t* __restrict__ codes,
                                                          const float* __restrict__ spts,
                                                          const uint32_t* __restrict__ orig, int64_t n,
                                                          TreeOut<DIM> a, TreeEntry<DIM>* __restrict__ out,
                                                          uint32_t* __restrict__ out_count, Ctrl* mirror) {
-    __shared__ TreeLds<DIM, kFitShift> s;
+    __shared__ TreeLds<DIM, kTreeTileShift> s;
     const int t = threadIdx.x;
-    const int64_t t0 = (int64_t)blockIdx.x * kFitTile, i = t0 + t, m = n - 1;
+    const int64_t t0 = (int64_t)blockIdx.x * kTreeTile, i = t0 + t, m = n - 1;
     TreeEntry<DIM> e = {};
     bool same = false;
     if (i < n) {
@@ -668,7 +668,7 @@ __global__ __launch_bounds__(kFitTile) void k_tree_tiles(const uint64_t* __restr
     // (past the threshold nobody needs the exact count, and thousands of
     // additions to one address would take tens of microseconds)
     if (t == 0 && dups && !many_dups(load_relaxed(&a.ctrl->dup_codes), n)) atomicAdd(&a.ctrl->dup_codes, (uint32_t)dups);
-    const uint32_t left = tree_tile<DIM, kFitShift>(s, (int)min<int64_t>(kFitTile, n - t0), (uint32_t)(t0 - 1), prev, e,
+    const uint32_t left = tree_tile<DIM, kTreeTileShift>(s, (int)min<int64_t>(kTreeTile, n - t0), (uint32_t)(t0 - 1), prev, e,
                                                     (uint32_t)m, a, out + (int64_t)blockIdx.x * kTreeSpan);
     if (t == 0) out_count[blockIdx.x] = left;
     if (mirror && gridDim.x == 1) {
@@ -3085,10 +3085,10 @@ int build_hierarchy(emst_ctx* ctx, Bufs<DIM>& b, const uint64_t* codes, int64_t 
     const TreeOut<DIM> out{b.recs, b.meta, b.rlo, b.rhi, b.node_parent, b.ctrl};
     TreeEntry<DIM>* list[2] = {reinterpret_cast<TreeEntry<DIM>*>(b.up), reinterpret_cast<TreeEntry<DIM>*>(b.eud)};
     uint32_t* counts = b.hist;
-    int64_t tiles = (n + kFitTile - 1) / kFitTile;
-    k_tree_tiles<DIM><<<(unsigned)tiles, kFitTile, 0, st>>>(codes, b.spts, b.orig, n, out, list[0], counts,
+    int64_t tiles = (n + kTreeTile - 1) / kTreeTile;
+    k_tree_tiles<DIM><<<(unsigned)tiles, kTreeTile, 0, st>>>(codes, b.spts, b.orig, n, out, list[0], counts,
                                                             mirror);
-    int64_t leaves = kFitTile;
+    int64_t leaves = kTreeTile;
     for (int lvl = 0; tiles > 1; ++lvl) {
         const int64_t groups = (tiles + kTreeGroup - 1) / kTreeGroup;
         leaves *= kTreeGroup;

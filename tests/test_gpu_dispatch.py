@@ -22,9 +22,9 @@ def combs(n, seed):
     """Cells of a 16^3 grid, each with 60 points at its corner and a
     geometric comb of 48 points that halves its offset along one axis after
     the other: the radix tree nests about 48 nodes around every corner, so
-    most tile borders of the box fit cross dozens of nodes, and 64 tiles
-    list more of them (about 1700) than a workgroup of the second level keeps in
-    LDS (1536)."""
+    most tile borders cross dozens of nodes, and 64 tiles leave more of
+    them (about 1700) than a workgroup of the second level takes at a time
+    (1024)."""
     rng = np.random.default_rng(seed)
     corner = rng.permutation(16 ** 3)[:-(-n // 108)]
     corner = np.stack([corner % 16, corner // 16 % 16, corner // 256], 1) / 16.0
@@ -51,11 +51,12 @@ def node_boxes(pts, left, right, root):
 
 
 # tiles of 512 leaves, groups of 64 tiles: one tile, two, one full group, the
-# smallest second group, a third level of one workgroup
+# smallest second group, a third level of one workgroup; whole tiles below one node
 @pytest.mark.parametrize("n,kind", [(512, "uniform"), (513, "uniform"), (1025, "dup"), (32768, "uniform"),
-                                    (32769, "uniform"), (65537, "comb"), (100_000, "comb")])
+                                    (32769, "uniform"), (65537, "comb"), (100_000, "comb"),
+                                    (1024, "same"), (40_000, "same")])
 def test_boxes_of_nodes_across_tiles(ctx, n, kind):
-    pts = combs(n, 5) if kind == "comb" else W.small_random(n, 3, 5, kind)
+    pts = combs(n, 5) if kind == "comb" else W.identical(n) if kind == "same" else W.small_random(n, 3, 5, kind)
     print(f"case boxes n={n} {kind}", flush=True)
     left, right, lo, hi, root = ctx.test_tree_boxes(torch.from_numpy(pts).cuda())
     mn, mx = node_boxes(pts, left.cpu().numpy(), right.cpu().numpy(), root)
