@@ -55,35 +55,36 @@ TRAFFIC_SOURCES = ("traverse.h", "emst_common.h", "emst_kernels.h")
 FETCH_FACTOR, WRITE_FACTOR = 2.0, 1.0
 MEASURED_TRAFFIC = {
     # (workload, variant, source hash): (FETCH_SIZE KiB, WRITE_SIZE KiB, TCC hit fraction, profile)
-    ("cosmology3d_37m", 13, "a2025fcf28faa80d"):
-        (1172456.2, 294876.0, 0.881, "profiles/k_traverse_fast_cosmology3d_37m.md"),
-    ("clustered3d_2m", 13, "a2025fcf28faa80d"):
-        (70849.3, 18651.3, 0.878, "profiles/k_traverse_fast_clustered3d_2m.md"),
+    ("cosmology3d_37m", 13, "e1b7ca87cf972178"):
+        (1225629.0, 291148.0, 0.908, "profiles/k_traverse_fast_cosmology3d_37m.md"),
+    ("clustered3d_2m", 13, "e1b7ca87cf972178"):
+        (77958.0, 18400.9, 0.904, "profiles/k_traverse_fast_clustered3d_2m.md"),
 }
 # What bounds the traversal, from counters of the same runs (per launch
-# type): VALU busy = VALU issue cycles / (SIMDs x kernel cycles), lane
-# utilisation = active lanes per VALU instruction / 64, resident waves per
-# CU, scalar instructions per vector instruction.
+# type): TA busy = busy cycles of the texture addressers / kernel cycles, VALU
+# busy = VALU issue cycles / (SIMDs x kernel cycles), lane utilisation = active
+# lanes per VALU instruction / 64, resident waves per CU, scalar instructions
+# per vector instruction.
 MEASURED_LIMITER = {
     # (workload, variant, source hash): {"full": {...}, "list": {...}, "profile": path}
-    ("cosmology3d_37m", 13, "a2025fcf28faa80d"): {
-        "bound_by": "instruction issue x lane divergence (not HBM)",
-        "full": {"launches": "rounds 0-1", "valu_busy": 0.568, "lane_utilisation": 0.406,
-                 "salu_per_valu": 0.94, "waves_per_cu": 27.2, "of_waves_per_cu": 32, "l2_hit": 0.907,
-                 "hbm_frac": 0.098},
-        "list": {"launches": "rounds 2-10", "valu_busy": 0.415, "lane_utilisation": 0.532,
-                 "salu_per_valu": 1.00, "waves_per_cu": 24.7, "of_waves_per_cu": 32, "l2_hit": 0.854,
-                 "hbm_frac": 0.150},
+    ("cosmology3d_37m", 13, "e1b7ca87cf972178"): {
+        "bound_by": "texture addresser (gathers of node records), not HBM",
+        "full": {"launches": "rounds 0-1", "ta_busy": 0.942, "valu_busy": 0.639, "lane_utilisation": 0.473,
+                 "salu_per_valu": 0.86, "waves_per_cu": 27.2, "of_waves_per_cu": 32, "l2_hit": 0.939,
+                 "hbm_frac": 0.095},
+        "list": {"launches": "rounds 2-10", "ta_busy": 0.865, "valu_busy": 0.518, "lane_utilisation": 0.587,
+                 "salu_per_valu": 0.88, "waves_per_cu": 24.9, "of_waves_per_cu": 32, "l2_hit": 0.868,
+                 "hbm_frac": 0.174},
         "profile": "profiles/k_traverse_fast_cosmology3d_37m.md",
     },
-    ("clustered3d_2m", 13, "a2025fcf28faa80d"): {
-        "bound_by": "instruction issue x lane divergence (not HBM)",
-        "full": {"launches": "rounds 0-1", "valu_busy": 0.511, "lane_utilisation": 0.403,
-                 "salu_per_valu": 0.94, "waves_per_cu": 23.8, "of_waves_per_cu": 32, "l2_hit": 0.914,
-                 "hbm_frac": 0.083},
-        "list": {"launches": "rounds 2-8", "valu_busy": 0.291, "lane_utilisation": 0.566,
-                 "salu_per_valu": 0.99, "waves_per_cu": 15.3, "of_waves_per_cu": 32, "l2_hit": 0.828,
-                 "hbm_frac": 0.111},
+    ("clustered3d_2m", 13, "e1b7ca87cf972178"): {
+        "bound_by": "texture addresser (gathers of node records), not HBM",
+        "full": {"launches": "rounds 0-1", "ta_busy": 0.855, "valu_busy": 0.640, "lane_utilisation": 0.437,
+                 "salu_per_valu": 0.86, "waves_per_cu": 24.3, "of_waves_per_cu": 32, "l2_hit": 0.945,
+                 "hbm_frac": 0.088},
+        "list": {"launches": "rounds 2-8", "ta_busy": 0.586, "valu_busy": 0.381, "lane_utilisation": 0.598,
+                 "salu_per_valu": 0.88, "waves_per_cu": 15.9, "of_waves_per_cu": 32, "l2_hit": 0.831,
+                 "hbm_frac": 0.152},
         "profile": "profiles/k_traverse_fast_clustered3d_2m.md",
     },
 }
