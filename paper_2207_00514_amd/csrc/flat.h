@@ -27,11 +27,12 @@
 namespace emst {
 
 // The rule: a cloud of up to 16,384 points is solved this way.  Measured
-// against the tree (us a build, tree / flat): uniform 2D 1,000 points 681 /
-// 144, 10,000 943 / 280, 16,384 930 / 270; clustered 3D 16,384 1054 / 368;
+// against the tree (us a build, tree / flat): uniform 2D 4,000 points 480 /
+// 208, 16,384 581 / 342; clustered 3D 4,000 542 / 243, 16,384 628 / 381;
 // skewed 3D, whose points share a few codes so that no tile is skipped,
-// 10,000 1444 / 813 and 16,384 1476 / 1123.  At 20,000 points the skewed
-// cloud takes 2638 against 1391, the others 434-558 against 928-1031.
+// 8,000 843 / 633, 12,000 868 / 838 and 16,384 950 / 1,243, the only form of
+// cloud that the tree solves faster below the line (it took 1,530 when the
+// line was drawn).  At 20,000 points that form takes 2,638 without a tree.
 constexpr int64_t kFlatMax = 16384;
 constexpr int kFlatTile = 64;         // one query per lane
 static_assert(kFlatMax <= 65536, "two indices and D fill the key");
