@@ -56,6 +56,16 @@ int emst_test_radix_sort(emst_ctx *ctx, uint64_t *d_keys, uint32_t *d_vals, int6
                          void *d_workspace, size_t ws_bytes, void *stream);
 
 /*
+ * The same sort with another bound on the wait of a look-back for the tiles
+ * before it: after `polls` polls (0: at the first missing word) a thread
+ * counts their keys itself.  *counted_out (host, nullable) receives how many
+ * prefixes were counted that way.
+ */
+int emst_test_radix_sort_polls(emst_ctx *ctx, uint64_t *d_keys, uint32_t *d_vals, int64_t n,
+                               uint32_t polls, uint32_t *counted_out, void *d_workspace,
+                               size_t ws_bytes, void *stream);
+
+/*
  * One Boruvka round of emst_build from a given partition (Section 3,
  * Figure 3): label propagation and component bounds (Optimizations 1 and
  * 2), the nearest-other-component traversal with stage A (Algorithm 2),

@@ -32,7 +32,7 @@ ERRORS = {
 EXPORTS = [
     "emst_create", "emst_destroy", "emst_last_error", "emst_workspace_bytes", "emst_build",
     "emst_set_profiling", "emst_set_counting", "emst_set_traversal", "emst_get_stats",
-    "emst_test_tree_from_codes", "emst_test_radix_sort",
+    "emst_test_tree_from_codes", "emst_test_radix_sort", "emst_test_radix_sort_polls",
     "emst_workspace_bytes_batched", "emst_build_batched", "emst_test_tree_boxes",
     "emst_core_distances", "emst_build_mreach", "emst_set_autotune", "emst_get_autotune",
     "emst_solver_slot_bytes", "emst_solver_create", "emst_solver_destroy", "emst_solver_admit",
@@ -150,6 +150,9 @@ def lib():
         L.emst_test_tree_boxes.restype = i32
         L.emst_test_radix_sort.argtypes = [vp, vp, vp, i64, vp, sz, vp]
         L.emst_test_radix_sort.restype = i32
+        L.emst_test_radix_sort_polls.argtypes = [vp, vp, vp, i64, ctypes.c_uint32, ctypes.POINTER(ctypes.c_uint32),
+                                                 vp, sz, vp]
+        L.emst_test_radix_sort_polls.restype = i32
         L.emst_test_round.argtypes = [vp, vp, i64, i32, vp, ctypes.c_int32, ctypes.c_int32, vp, vp, vp, vp, vp,
                                       vp, vp, ctypes.POINTER(ctypes.c_int64), vp, sz, vp]
         L.emst_test_round.restype = i32
@@ -298,6 +301,17 @@ class Context:
         self._check(lib().emst_test_radix_sort(
             self._h, ctypes.c_void_p(keys.data_ptr()), ctypes.c_void_p(vals.data_ptr()), int(n),
             ws, wsb, _stream_handle(stream)))
+
+    def test_radix_sort_polls(self, keys, vals, polls: int, stream=None) -> int:
+        """test_radix_sort whose look-backs wait for at most `polls` polls;
+        returns how many prefixes were counted instead."""
+        n = keys.shape[0]
+        ws, wsb = self._ws_ptr(max(n, 2), 3)
+        counted = ctypes.c_uint32()
+        self._check(lib().emst_test_radix_sort_polls(
+            self._h, ctypes.c_void_p(keys.data_ptr()), ctypes.c_void_p(vals.data_ptr()), int(n), int(polls),
+            ctypes.byref(counted), ws, wsb, _stream_handle(stream)))
+        return counted.value
 
     def test_round(self, points, comp, round_: int = 1, variant: int = 13, stream=None):
         """One Boruvka round from the partition `comp` (int32 [n], input

@@ -4923,10 +4923,12 @@ extern "C" int emst_test_tree_from_codes(emst_ctx* ctx, const uint64_t* d_codes,
     return EMST_OK;
 }
 
-extern "C" int emst_test_radix_sort(emst_ctx* ctx, uint64_t* d_keys, uint32_t* d_vals, int64_t n, void* d_workspace,
-                                    size_t ws_bytes, void* stream) {
+extern "C" int emst_test_radix_sort_polls(emst_ctx* ctx, uint64_t* d_keys, uint32_t* d_vals, int64_t n,
+                                          uint32_t polls, uint32_t* counted_out, void* d_workspace, size_t ws_bytes,
+                                          void* stream) {
     if (!ctx) return EMST_EINVAL;
     ctx->err.clear();
+    if (counted_out) *counted_out = 0u;
     if (n < 0 || n > 0x7FFFFFFFll || (n > 0 && (!d_keys || !d_vals || !d_workspace)))
         return fail(ctx, EMST_EINVAL, "bad argument");
     if (n < 2) return EMST_OK;
@@ -4942,13 +4944,21 @@ extern "C" int emst_test_radix_sort(emst_ctx* ctx, uint64_t* d_keys, uint32_t* d
     int shifts[8];
     for (int q = 0; q < 8; ++q) shifts[q] = 8 * q;
     int in1 = 0;
-    HIP_TRY(radix_sort_pairs(st, d_keys, d_vals, k1, v1, hist, n, shifts, 8, &in1));
+    HIP_TRY(radix_sort_pairs(st, d_keys, d_vals, k1, v1, hist, n, shifts, 8, &in1, polls));
+    if (counted_out && radix_one_launch(n))
+        HIP_TRY(hipMemcpyAsync(counted_out, radix_one_scratch(hist, n) + kRadixCounters + 8, sizeof(uint32_t),
+                               hipMemcpyDeviceToHost, st));
     if (in1) {
         HIP_TRY(hipMemcpyAsync(d_keys, k1, 8 * (size_t)n, hipMemcpyDeviceToDevice, st));
         HIP_TRY(hipMemcpyAsync(d_vals, v1, 4 * (size_t)n, hipMemcpyDeviceToDevice, st));
     }
     HIP_TRY(hipStreamSynchronize(st));
     return EMST_OK;
+}
+
+extern "C" int emst_test_radix_sort(emst_ctx* ctx, uint64_t* d_keys, uint32_t* d_vals, int64_t n, void* d_workspace,
+                                    size_t ws_bytes, void* stream) {
+    return emst_test_radix_sort_polls(ctx, d_keys, d_vals, n, kRadixPolls, nullptr, d_workspace, ws_bytes, stream);
 }
 
 extern "C" int emst_test_tree_boxes(emst_ctx* ctx, const float* d_points, int64_t n, int32_t* d_left,

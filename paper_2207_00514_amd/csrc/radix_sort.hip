@@ -241,7 +241,9 @@ __global__ __launch_bounds__(kRsThreads) void rs_downsweep(const uint64_t* __res
 // per-digit counts, and adds up the counts of the tiles before it -- each
 // tile publishes its own count before it looks back, and the inclusive
 // prefix once it knows it, so a look-back stops at the first inclusive
-// prefix it meets and only ever waits on tiles that have started.
+// prefix it meets and only ever waits on tiles that have started.  The wait is
+// bounded all the same: a thread whose polls run out counts its digit in the
+// keys of the tiles it still misses, so its prefix is right without them.
 // A status word is (flag << 30) | count: flag 1 = the tile's own count,
 // 2 = inclusive prefix (counts stay below 2^30: kRadixOneMin <= n < 2^30).
 // The words go through device-coherent atomics; each one holds its datum.
@@ -306,6 +308,13 @@ __device__ __forceinline__ uint32_t os_load(const uint32_t* p) {
 __device__ __forceinline__ void os_store(uint32_t* p, uint32_t v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+// Occurrences of digit d at `shift` among the first n keys (by one thread).
+__device__ __forceinline__ uint32_t os_count(const uint64_t* __restrict__ keys, int n, int shift, uint32_t d) {
+    uint32_t c = 0;
+#pragma unroll 4
+    for (int i = 0; i < n; ++i) c += ((uint32_t)(keys[i] >> shift) & 255u) == d;
+    return c;
+}
 
 // Each wave owns a contiguous chunk of 64 x ITEMS keys of the tile (item s
 // of lane l is key s * 64 + l of the chunk), so the tile's order is (wave,
@@ -322,7 +331,7 @@ template <int THREADS, int ITEMS, bool SCAN>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(6))) void rs_onesweep(
     const uint64_t* __restrict__ kin, const uint32_t* __restrict__ vin, uint64_t* __restrict__ kout,
     uint32_t* __restrict__ vout, int64_t n, int shift, const uint32_t* __restrict__ gstart, uint32_t* status,
-    uint32_t* status_next, uint32_t* counter, uint32_t* err) {
+    uint32_t* status_next, uint32_t* counter, uint32_t* counted, uint32_t polls) {
     constexpr int kWaves = THREADS / 64;
     constexpr int kTile = THREADS * ITEMS;
     static_assert(THREADS >= 256 && THREADS % 64 == 0, "one digit per thread of the first 256");
@@ -417,6 +426,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(6))) vo
             // the status words of kOsWindow tiles before are loaded at once,
             // then added up nearest first until an inclusive one
             bool found = false;
+            int missing = 0;  // tiles in front whose counts did not come
             for (int64_t p = tile - 1; !found; p -= kOsWindow) {
                 uint32_t v[kOsWindow];
 #pragma unroll
@@ -424,9 +434,9 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(6))) vo
 #pragma unroll
                 for (int j = 0; j < kOsWindow; ++j) {
                     if (found) break;
-                    for (uint32_t spin = 0; (v[j] >> 30) == 0u; ++spin) {
-                        if (spin > (1u << 22)) {  // (bounded: a missing tile is a bug, not a wait)
-                            atomicOr(err, 1u);
+                    for (uint32_t poll = 0; (v[j] >> 30) == 0u; ++poll) {
+                        if (poll >= polls) {
+                            missing = (int)(p - j) + 1;
                             v[j] = kOsIncl;
                             break;
                         }
@@ -436,6 +446,10 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(6))) vo
                     excl += v[j] & kOsMask;
                     found = (v[j] >> 30) == 2u;
                 }
+            }
+            if (missing) {
+                excl += os_count(kin, missing * kTile, shift, (uint32_t)t);
+                atomicAdd(counted, 1u);
             }
             os_store(&status[tile * 256 + t], kOsIncl | (excl + total));
         }
@@ -484,14 +498,15 @@ constexpr int kOsItems = kRadixOneTile / kOsThreads;
 constexpr int kOsSmallItems = 4;
 
 // One-sweep passes; `scratch` holds the global counts and starts of every
-// pass, the pass counters and an error word, and two status arrays.
+// pass, the pass counters, the number of prefixes that were counted for want
+// of a status word, and two status arrays.
 template <int ITEMS, bool SCAN>
 static void rs_one(hipStream_t stream, uint64_t* ka, uint32_t* va, uint64_t* kb, uint32_t* vb, uint32_t* scratch,
-                   int64_t n, const int* shifts, int nshifts) {
+                   int64_t n, const int* shifts, int nshifts, uint32_t polls) {
     const int64_t tiles = (n + kOsThreads * ITEMS - 1) / (kOsThreads * ITEMS);
     uint32_t* ghist = scratch;
     uint32_t* gstart = scratch + 8 * 256;
-    uint32_t* counters = scratch + 3 * 8 * 256;  // [8] pass counters, [9] error
+    uint32_t* counters = scratch + kRadixCounters;  // of the 8 passes, then of counted prefixes
     uint32_t* status[2] = {counters + 64, counters + 64 + tiles * 256};
     RsShifts sh;
     for (int q = 0; q < 8; ++q) sh.s[q] = q < nshifts ? shifts[q] : 0;
@@ -503,7 +518,7 @@ static void rs_one(hipStream_t stream, uint64_t* ka, uint32_t* va, uint64_t* kb,
     for (int q = 0; q < nshifts; ++q) {
         rs_onesweep<kOsThreads, ITEMS, SCAN><<<(unsigned)tiles, kOsThreads, 0, stream>>>(
             ka, va, kb, vb, n, shifts[q], (SCAN ? ghist : gstart) + q * 256, status[q & 1], status[(q + 1) & 1],
-            counters + q, counters + 8);
+            counters + q, counters + 8, polls);
         std::swap(ka, kb);
         std::swap(va, vb);
     }
@@ -531,16 +546,17 @@ static void rs_pass(hipStream_t stream, const RadixPlan& p, const uint64_t* ka, 
 }
 
 hipError_t radix_sort_pairs(hipStream_t stream, uint64_t* k0, uint32_t* v0, uint64_t* k1, uint32_t* v1,
-                            uint32_t* hist, int64_t n, const int* shifts, int nshifts, int* result_in_1) {
+                            uint32_t* hist, int64_t n, const int* shifts, int nshifts, int* result_in_1,
+                            uint32_t polls) {
     *result_in_1 = 0;
     if (n <= 1 || nshifts == 0) return hipSuccess;
     uint64_t *ka = k0, *kb = k1;
     uint32_t *va = v0, *vb = v1;
-    if (nshifts <= 8 && (n < kRadixSmallOne || (n >= kRadixOneMin && n < ((int64_t)1 << 30)))) {
-        if (n < kRadixSmallOne)  // in the count table's place
-            rs_one<kOsSmallItems, true>(stream, ka, va, kb, vb, hist, n, shifts, nshifts);
+    if (nshifts <= 8 && radix_one_launch(n)) {
+        if (n < kRadixSmallOne)
+            rs_one<kOsSmallItems, true>(stream, ka, va, kb, vb, radix_one_scratch(hist, n), n, shifts, nshifts, polls);
         else
-            rs_one<kOsItems, false>(stream, ka, va, kb, vb, hist + radix_hist_elems(), n, shifts, nshifts);
+            rs_one<kOsItems, false>(stream, ka, va, kb, vb, radix_one_scratch(hist, n), n, shifts, nshifts, polls);
         *result_in_1 = (nshifts & 1);
         return hipGetLastError();
     }

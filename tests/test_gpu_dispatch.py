@@ -182,6 +182,23 @@ def test_sort_sizes(ctx, n):
     assert np.array_equal(v.cpu().numpy(), vals[order])
 
 
+# a look-back that does not wait for the tiles before it: passes on tiles of
+# 2,048 keys (two, many and the most of them) and of 4,096
+@pytest.mark.parametrize("n", [4096, 65_537, 524_287, 4_194_304])
+def test_sort_whose_look_backs_do_not_wait(ctx, n):
+    rng = np.random.default_rng(n + 1)
+    keys = rng.integers(-2 ** 63, 2 ** 63, n, dtype=np.int64)
+    keys[n // 2:] = rng.integers(0, 3, n - n // 2)
+    vals = np.arange(n, dtype=np.int32)
+    k, v = torch.from_numpy(keys).cuda(), torch.from_numpy(vals).cuda()
+    print(f"case sort without waits n={n}", flush=True)
+    counted = ctx.test_radix_sort_polls(k, v, 0)
+    assert counted > 0 or n == 4096  # (one predecessor, which may have been done)
+    order = np.argsort(keys.view(np.uint64), kind="stable")
+    assert np.array_equal(k.cpu().numpy(), keys[order])
+    assert np.array_equal(v.cpu().numpy(), vals[order])
+
+
 def core_reference(pts, k):
     """The k-th smallest D(i, j) over all j, float32 in the kernels' order."""
     n, out = len(pts), np.empty(len(pts), np.float32)
