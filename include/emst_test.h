@@ -66,6 +66,12 @@ int emst_test_radix_sort_polls(emst_ctx *ctx, uint64_t *d_keys, uint32_t *d_vals
                                size_t ws_bytes, void *stream);
 
 /*
+ * *out = 1 if the host memory that kernels report their rounds to, and that
+ * calls poll meanwhile, was allocated as coherent, else 0.
+ */
+int emst_test_mirror_is_coherent(emst_ctx *ctx, int32_t *out);
+
+/*
  * One Boruvka round of emst_build from a given partition (Section 3,
  * Figure 3): label propagation and component bounds (Optimizations 1 and
  * 2), the nearest-other-component traversal with stage A (Algorithm 2),

@@ -33,6 +33,7 @@ EXPORTS = [
     "emst_create", "emst_destroy", "emst_last_error", "emst_workspace_bytes", "emst_build",
     "emst_set_profiling", "emst_set_counting", "emst_set_traversal", "emst_get_stats",
     "emst_test_tree_from_codes", "emst_test_radix_sort", "emst_test_radix_sort_polls",
+    "emst_test_mirror_is_coherent",
     "emst_workspace_bytes_batched", "emst_build_batched", "emst_test_tree_boxes",
     "emst_core_distances", "emst_build_mreach", "emst_set_autotune", "emst_get_autotune",
     "emst_solver_slot_bytes", "emst_solver_create", "emst_solver_destroy", "emst_solver_admit",
@@ -153,6 +154,8 @@ def lib():
         L.emst_test_radix_sort_polls.argtypes = [vp, vp, vp, i64, ctypes.c_uint32, ctypes.POINTER(ctypes.c_uint32),
                                                  vp, sz, vp]
         L.emst_test_radix_sort_polls.restype = i32
+        L.emst_test_mirror_is_coherent.argtypes = [vp, ctypes.POINTER(ctypes.c_int32)]
+        L.emst_test_mirror_is_coherent.restype = i32
         L.emst_test_round.argtypes = [vp, vp, i64, i32, vp, ctypes.c_int32, ctypes.c_int32, vp, vp, vp, vp, vp,
                                       vp, vp, ctypes.POINTER(ctypes.c_int64), vp, sz, vp]
         L.emst_test_round.restype = i32
@@ -312,6 +315,12 @@ class Context:
             self._h, ctypes.c_void_p(keys.data_ptr()), ctypes.c_void_p(vals.data_ptr()), int(n), int(polls),
             ctypes.byref(counted), ws, wsb, _stream_handle(stream)))
         return counted.value
+
+    def test_mirror_is_coherent(self) -> bool:
+        """Whether the polled host memory is coherent by its own flags."""
+        out = ctypes.c_int32(0)
+        self._check(lib().emst_test_mirror_is_coherent(self._h, ctypes.byref(out)))
+        return bool(out.value)
 
     def test_round(self, points, comp, round_: int = 1, variant: int = 13, stream=None):
         """One Boruvka round from the partition `comp` (int32 [n], input

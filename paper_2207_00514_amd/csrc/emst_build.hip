@@ -2356,7 +2356,9 @@ struct emst_ctx {
     int lds_depth = 0;             // 0: the autotune table, else 4, 8 or 16 (variant 13)
     TuneTable tune;
     emst_stats stats;
-    Ctrl* h_ctrl = nullptr;        // pinned host mirror of the control block
+    // pinned host mirrors of the control block, which kernels store to while the
+    // host polls them: coherent memory, whatever the runtime's default is
+    Ctrl* h_ctrl = nullptr;
     hipEvent_t ev[2 * 64 + 8];
     bool ev_ok = false;
     hipEvent_t sev[2] = {nullptr, nullptr};  // completion of the control copies of two rounds in flight
@@ -2429,7 +2431,7 @@ extern "C" int emst_create(emst_ctx** out, int hip_device, const char* autotune_
     }
     memset(&ctx->stats, 0, sizeof(ctx->stats));
     if (hipSetDevice(hip_device) != hipSuccess ||
-        hipHostMalloc((void**)&ctx->h_ctrl, 2 * sizeof(Ctrl) + 256, hipHostMallocDefault) != hipSuccess ||
+        hipHostMalloc((void**)&ctx->h_ctrl, 2 * sizeof(Ctrl) + 256, hipHostMallocCoherent) != hipSuccess ||
         hipEventCreateWithFlags(&ctx->sev[0], hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&ctx->sev[1], hipEventDisableTiming) != hipSuccess) {
         for (auto& e : ctx->sev)
@@ -4959,6 +4961,14 @@ extern "C" int emst_test_radix_sort_polls(emst_ctx* ctx, uint64_t* d_keys, uint3
 extern "C" int emst_test_radix_sort(emst_ctx* ctx, uint64_t* d_keys, uint32_t* d_vals, int64_t n, void* d_workspace,
                                     size_t ws_bytes, void* stream) {
     return emst_test_radix_sort_polls(ctx, d_keys, d_vals, n, kRadixPolls, nullptr, d_workspace, ws_bytes, stream);
+}
+
+extern "C" int emst_test_mirror_is_coherent(emst_ctx* ctx, int32_t* out) {
+    if (!ctx || !out) return EMST_EINVAL;
+    unsigned flags = 0;
+    HIP_TRY(hipHostGetFlags(&flags, ctx->h_ctrl));
+    *out = (flags & hipHostMallocCoherent) != 0u;
+    return EMST_OK;
 }
 
 extern "C" int emst_test_tree_boxes(emst_ctx* ctx, const float* d_points, int64_t n, int32_t* d_left,

@@ -199,6 +199,10 @@ def test_sort_whose_look_backs_do_not_wait(ctx, n):
     assert np.array_equal(v.cpu().numpy(), vals[order])
 
 
+def test_polled_memory_is_coherent(ctx):
+    assert ctx.test_mirror_is_coherent()
+
+
 def core_reference(pts, k):
     """The k-th smallest D(i, j) over all j, float32 in the kernels' order."""
     n, out = len(pts), np.empty(len(pts), np.float32)
