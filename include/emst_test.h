@@ -72,6 +72,13 @@ int emst_test_radix_sort_polls(emst_ctx *ctx, uint64_t *d_keys, uint32_t *d_vals
 int emst_test_mirror_is_coherent(emst_ctx *ctx, int32_t *out);
 
 /*
+ * The wait of a call for its kernels' reports, on a word of host memory
+ * (no device, no context): returns once *h_word is set by another thread, or
+ * after max_polls polls; the result is the polls it took, in steps of 4,096.
+ */
+int64_t emst_test_poll_word(const uint32_t *h_word, int64_t max_polls);
+
+/*
  * One Boruvka round of emst_build from a given partition (Section 3,
  * Figure 3): label propagation and component bounds (Optimizations 1 and
  * 2), the nearest-other-component traversal with stage A (Algorithm 2),

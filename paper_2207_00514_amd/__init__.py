@@ -33,7 +33,7 @@ EXPORTS = [
     "emst_create", "emst_destroy", "emst_last_error", "emst_workspace_bytes", "emst_build",
     "emst_set_profiling", "emst_set_counting", "emst_set_traversal", "emst_get_stats",
     "emst_test_tree_from_codes", "emst_test_radix_sort", "emst_test_radix_sort_polls",
-    "emst_test_mirror_is_coherent",
+    "emst_test_mirror_is_coherent", "emst_test_poll_word",
     "emst_workspace_bytes_batched", "emst_build_batched", "emst_test_tree_boxes",
     "emst_core_distances", "emst_build_mreach", "emst_set_autotune", "emst_get_autotune",
     "emst_solver_slot_bytes", "emst_solver_create", "emst_solver_destroy", "emst_solver_admit",
@@ -156,6 +156,8 @@ def lib():
         L.emst_test_radix_sort_polls.restype = i32
         L.emst_test_mirror_is_coherent.argtypes = [vp, ctypes.POINTER(ctypes.c_int32)]
         L.emst_test_mirror_is_coherent.restype = i32
+        L.emst_test_poll_word.argtypes = [ctypes.POINTER(ctypes.c_uint32), i64]
+        L.emst_test_poll_word.restype = i64
         L.emst_test_round.argtypes = [vp, vp, i64, i32, vp, ctypes.c_int32, ctypes.c_int32, vp, vp, vp, vp, vp,
                                       vp, vp, ctypes.POINTER(ctypes.c_int64), vp, sz, vp]
         L.emst_test_round.restype = i32

@@ -2640,21 +2640,34 @@ TraverseArgs<DIM> traverse_args(const Bufs<DIM>& b, int64_t n, uint32_t root) {
     return ta;
 }
 
+// Polls a word of host memory until it is set; false after 4,096 polls.  The
+// first kEagerPolls of a wait (some 20 us, what a round of a small cloud takes) only
+// pause; from then on every poll offers the core to the threads that could
+// run, of which a program with several builds at once has as many as cores.
+constexpr uint32_t kEagerPolls = 512;
+
+static bool poll_word(const uint32_t* word, uint32_t* polls) {
+    do {
+        if (__atomic_load_n(word, __ATOMIC_ACQUIRE)) return true;
+        if (*polls < kEagerPolls) __builtin_ia32_pause();
+        else std::this_thread::yield();
+    } while (++*polls % 4096u);
+    return false;
+}
+
 // Waits until a kernel on st has filled the mirror (see mirror_ctrl).  The
 // stream is asked now and then, so that a failed launch ends the wait.
 static int await_mirror(emst_ctx* ctx, Ctrl* mirror, hipStream_t st) {
-    for (uint32_t spin = 1;; ++spin) {
-        if (__atomic_load_n(&mirror->arrived, __ATOMIC_ACQUIRE)) return EMST_OK;
-        if (spin % 4096u == 0u) {
-            const hipError_t e = hipStreamQuery(st);
-            if (e == hipSuccess) {
-                if (__atomic_load_n(&mirror->arrived, __ATOMIC_ACQUIRE)) return EMST_OK;
-                return fail(ctx, EMST_EHIP, "a round did not report");
-            }
-            if (e != hipErrorNotReady) return fail(ctx, EMST_EHIP, hipGetErrorString(e));
+    for (uint32_t polls = 0; !poll_word(&mirror->arrived, &polls);) {
+        if (polls < kEagerPolls) polls = kEagerPolls;  // (the count wraps after hours)
+        const hipError_t e = hipStreamQuery(st);
+        if (e == hipSuccess) {
+            if (__atomic_load_n(&mirror->arrived, __ATOMIC_ACQUIRE)) return EMST_OK;
+            return fail(ctx, EMST_EHIP, "a round did not report");
         }
-        __builtin_ia32_pause();
+        if (e != hipErrorNotReady) return fail(ctx, EMST_EHIP, hipGetErrorString(e));
     }
+    return EMST_OK;
 }
 
 int read_ctrl(emst_ctx* ctx, Ctrl* ctrl, hipStream_t st) {
@@ -4961,6 +4974,16 @@ extern "C" int emst_test_radix_sort_polls(emst_ctx* ctx, uint64_t* d_keys, uint3
 extern "C" int emst_test_radix_sort(emst_ctx* ctx, uint64_t* d_keys, uint32_t* d_vals, int64_t n, void* d_workspace,
                                     size_t ws_bytes, void* stream) {
     return emst_test_radix_sort_polls(ctx, d_keys, d_vals, n, kRadixPolls, nullptr, d_workspace, ws_bytes, stream);
+}
+
+extern "C" int64_t emst_test_poll_word(const uint32_t* h_word, int64_t max_polls) {
+    int64_t waited = 0;
+    uint32_t polls = 0;
+    while (h_word && waited < max_polls && !poll_word(h_word, &polls)) {
+        waited += 4096;
+        polls = kEagerPolls;
+    }
+    return waited;
 }
 
 extern "C" int emst_test_mirror_is_coherent(emst_ctx* ctx, int32_t* out) {

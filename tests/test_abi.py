@@ -100,3 +100,39 @@ def test_noalloc_limit_matches_the_header():
     wb = emst.workspace_bytes
     assert wb(270_000, 3) <= emst.NOALLOC_WORKSPACE_BYTES < wb(290_000, 3)
     assert wb(290_000, 2) <= emst.NOALLOC_WORKSPACE_BYTES < wb(320_000, 2)
+
+
+def test_a_wait_leaves_the_core_to_others():
+    """A call that waits for its kernels, on the same core as a thread that
+    computes: the computing thread gets nearly all of the core (a wait that
+    only spins takes half of it)."""
+    import threading
+    import time
+    if not hasattr(os, "sched_setaffinity"):
+        pytest.skip("no affinity calls")
+    L = emst.lib()
+    word = ctypes.c_uint32(0)
+    core = sorted(os.sched_getaffinity(0))[-1:]
+    used = {}
+
+    def wait():
+        os.sched_setaffinity(0, core)
+        t0 = time.thread_time()
+        L.emst_test_poll_word(ctypes.byref(word), 1 << 40)
+        used["wait"] = time.thread_time() - t0
+
+    def compute():
+        os.sched_setaffinity(0, core)
+        t0 = time.thread_time()
+        while time.thread_time() - t0 < 0.5:
+            sum(range(1000))
+        used["compute"] = time.thread_time() - t0
+        word.value = 1
+
+    threads = [threading.Thread(target=f) for f in (wait, compute)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join(60)
+    assert word.value == 1 and set(used) == {"wait", "compute"}
+    assert used["wait"] < 0.4 * used["compute"], used
