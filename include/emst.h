@@ -354,7 +354,7 @@ int emst_set_counting(emst_ctx *ctx, int on);
  * -1 (the default) takes the variant from the context's autotune table
  * (emst_set_autotune) for the call's mode, dimension and size, else 13, or
  * for emst_build of up to 16,384 points a search without a tree (unless
- * the table, emst_set_lds_depth or emst_set_counting ask for a traversal).
+ * a table entry, emst_set_lds_depth or emst_set_counting ask for a traversal).
  * Batches (emst_build_batched) run 0, 5, 8 or 13 as chosen and 7
  * for 10 and 11; emst_build_mreach runs 7 for all but 13.
  * Returns EMST_EINVAL for any other value. */
@@ -370,13 +370,17 @@ int emst_set_lds_depth(emst_ctx *ctx, int depth);
 /* Traversal-shape table (the autotuner's output), a JSON document
  *
  *   {"entries": [{"mode": "single" | "batched", "dim": 2 | 3,
- *                 "n_min": <points>, "variant": <0, 5, 7, 8, 10, 11 or 13>,
+ *                 "n_min": <points>, "variant": <0, 5, 7, 8, 10, 11, 13 or -1>,
  *                 "lds_depth": <4, 8 or 16; optional, default 8>}, ...]}
  *
  * (other keys are ignored).  A call in auto mode (emst_set_traversal -1,
  * emst_set_lds_depth 0) with n points uses the entry of its mode and
- * dimension with the largest n_min <= n.  NULL clears the table.  EMST_EINVAL on a malformed table,
- * which then stays as it was.  Every variant gives the same result. */
+ * dimension with the largest n_min <= n.  Variant -1, for "single" entries
+ * only, is the choice of a call without an entry: no tree up to 16,384 points,
+ * else 13.  Any other variant is a traversal at every size, so a table that
+ * names one from n_min 0 on gives small clouds a tree.  NULL clears the table.
+ * EMST_EINVAL on a malformed table, which then stays as it was.  Every variant
+ * gives the same result. */
 int emst_set_autotune(emst_ctx *ctx, const char *json);
 
 /* The table as JSON into buf (capacity cap bytes, NUL-terminated); *len

@@ -2413,7 +2413,7 @@ static int fail(emst_ctx* ctx, int code, const char* msg) {
 // LDS ring.
 static void pick_shape(const emst_ctx* ctx, int batched, int dim, int64_t n, int* variant, int* depth) {
     const TuneEntry* e = ctx->tune.pick(batched, dim, n);
-    *variant = ctx->traversal >= 0 ? ctx->traversal : (e ? e->variant : 13);
+    *variant = ctx->traversal >= 0 ? ctx->traversal : (e && e->variant != kTuneAuto ? e->variant : 13);
     *depth = ctx->lds_depth > 0 ? ctx->lds_depth : (e ? e->lds_depth : 8);
 }
 
@@ -3556,8 +3556,9 @@ int build_impl(emst_ctx* ctx, const float* pts, int64_t n, int32_t* edges, float
                hipStream_t st, int k_pts = 0, float* core_out = nullptr, bool core_only = false) {
     // a small cloud needs no tree, unless the caller asked for a traversal
     // shape or for the traversal's counts
+    const TuneEntry* e = ctx->tune.pick(0, DIM, n);
     if (n <= kFlatMax && k_pts == 0 && !ctx->counting && ctx->traversal < 0 && ctx->lds_depth == 0 &&
-        !ctx->tune.pick(0, DIM, n))
+        (!e || e->variant == kTuneAuto))
         return flat_impl<DIM>(ctx, pts, n, edges, weights, d2, ws, st);
     Job j = make_job(ctx, pts, n, DIM, ws, edges, weights, d2, k_pts, core_out, core_only, ctx->h_ctrl,
                      ctx->profiling && ctx->ev_ok);

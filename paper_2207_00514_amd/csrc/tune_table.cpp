@@ -137,7 +137,8 @@ bool TuneTable::parse(const char* json, uint32_t valid_variants, std::string* er
                     ++r.p;
                 } else {
                     for (;;) {
-                        TuneEntry e{-1, -1, -1, -1, 8};
+                        constexpr int kNoVariant = -2;
+                        TuneEntry e{-1, -1, -1, kNoVariant, 8};
                         if (!r.expect('{')) return fail(r.err);
                         r.ws();
                         if (*r.p != '}') {
@@ -155,7 +156,7 @@ bool TuneTable::parse(const char* json, uint32_t valid_variants, std::string* er
                                     if (!r.integer(&v)) return fail(r.err);
                                     if (k == "dim") e.dim = (int)v;
                                     else if (k == "n_min") e.n_min = v;
-                                    else if (k == "variant") e.variant = (int)v;
+                                    else if (k == "variant") e.variant = v == kTuneAuto || (v >= 0 && v <= 31) ? (int)v : kNoVariant;
                                     else e.lds_depth = (v == 4 || v == 8 || v == 16) ? (int)v : -1;
                                 } else if (!r.skip()) {
                                     return fail(r.err);
@@ -171,8 +172,9 @@ bool TuneTable::parse(const char* json, uint32_t valid_variants, std::string* er
                         } else {
                             ++r.p;
                         }
-                        if (e.batched < 0 || (e.dim != 2 && e.dim != 3) || e.n_min < 0 || e.variant < 0 ||
-                            e.variant > 31 || !((valid_variants >> e.variant) & 1u) || e.lds_depth < 0)
+                        const bool valid = e.variant == kTuneAuto ? e.batched == 0
+                                                                  : e.variant >= 0 && ((valid_variants >> e.variant) & 1u);
+                        if (e.batched < 0 || (e.dim != 2 && e.dim != 3) || e.n_min < 0 || !valid || e.lds_depth < 0)
                             return fail("every entry needs mode, dim in {2, 3}, n_min >= 0, a valid variant "
                                         "and lds_depth 4, 8 or 16 if given");
                         out.push_back(e);

@@ -15,9 +15,13 @@ struct TuneEntry {
     int batched;    // 0: emst_build, 1: emst_build_batched
     int dim;        // 2 or 3
     int64_t n_min;  // the entry applies from this many points on
-    int variant;
+    int variant;    // or kTuneAuto
     int lds_depth;  // LDS stack ring entries per lane of variant 13: 4, 8 or 16
 };
+
+// The choice a call without an entry makes (emst_build only): no tree up to
+// its size limit, else the default variant with the entry's depth.
+constexpr int kTuneAuto = -1;
 
 class TuneTable {
 public:
@@ -26,7 +30,7 @@ public:
     //                 "n_min": <int >= 0>, "variant": <int>,
     //                 "lds_depth": 4|8|16 (optional, default 8)}, ...]}
     // (other keys are ignored).  A variant v is valid if bit v of
-    // `valid_variants` is set.  Returns false, leaving the table as it was,
+    // `valid_variants` is set, kTuneAuto for "single" entries.  Returns false, leaving the table as it was,
     // on malformed input or out-of-range values; `err` says why.
     bool parse(const char* json, uint32_t valid_variants, std::string* err);
     void clear() { entries_.clear(); }

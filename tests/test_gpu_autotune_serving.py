@@ -141,6 +141,59 @@ def test_autotune_bad_tables():
     assert json.loads(ctx.get_autotune()) == {"entries": []}
 
 
+def test_autotune_offers_the_search_without_a_tree():
+    """A context tuned on a small size keeps the path without a tree there
+    (two to three times as fast as any traversal) and gets a traversal above
+    that path's limit, whatever table it had before."""
+    import paper_2207_00514_amd as emst
+    from paper_2207_00514_amd import autotune
+    before = '{"entries": [{"mode": "single", "dim": 3, "n_min": 0, "variant": 7, "lds_depth": 8}]}'
+    ctx = emst.Context(0, autotune_json=before)
+    autotune.tune_single(ctx, sizes=(2000,), dims=(3,), repeats=1)
+    assert ctx.get_autotune() == before
+    table = json.loads(autotune.autotune(ctx, single_sizes=(10_000, 40_000), repeats=3))["entries"]
+    assert [(e["dim"], e["n_min"]) for e in table] == [(2, 0), (2, 16_385), (2, 20_000), (3, 0), (3, 16_385), (3, 20_000)]
+    assert [e["variant"] < 0 for e in table] == [True, False, False] * 2
+    for n in (1000, 10_000, 16_384, 16_385, 25_000):
+        for pts in (W.clustered3d(n), W.uniform2d(n)):
+            print(f"case tuned n={n} dim={pts.shape[1]}", flush=True)
+            got = host(ctx.build(dev(pts)))
+            want = [e["variant"] for e in table if e["dim"] == pts.shape[1] and e["n_min"] <= n][-1]
+            assert ctx.stats()["traversal_variant"] == want
+            assert same_tree(got, oracle_tree(pts))
+
+
+def test_table_entries_without_a_tree():
+    import paper_2207_00514_amd as emst
+    table = {"entries": [{"mode": "single", "dim": 3, "n_min": 0, "variant": -1, "lds_depth": 4},
+                         {"mode": "single", "dim": 3, "n_min": 30_000, "variant": 5}]}
+    ctx = emst.Context(0, autotune_json=json.dumps(table))
+    assert [e["variant"] for e in json.loads(ctx.get_autotune())["entries"]] == [-1, 5]
+    # beyond the limit the entry is the default variant with its depth
+    for n, want in ((5000, (-1, 0)), (16_384, (-1, 0)), (16_385, (13, 4)), (30_000, (5, 0))):
+        pts = W.clustered3d(n)
+        got = host(ctx.build(dev(pts)))
+        st = ctx.stats()
+        assert (st["traversal_variant"], st["traversal_lds_depth"]) == want
+        assert same_tree(got, oracle_tree(pts))
+    # mutual reachability and counting runs need the tree
+    pts = W.clustered3d(5000)
+    ctx.build_mreach(dev(pts), 4)
+    assert ctx.stats()["traversal_variant"] == 13
+    ctx.set_counting(True)
+    assert same_tree(host(ctx.build(dev(pts))), oracle_tree(pts))
+    assert ctx.stats()["traversal_variant"] == 13
+    ctx.set_counting(False)
+    kept = ctx.get_autotune()
+    for bad in ('{"entries": [{"mode": "batched", "dim": 3, "n_min": 0, "variant": -1}]}',
+                '{"entries": [{"mode": "single", "dim": 3, "n_min": 0}]}',
+                '{"entries": [{"mode": "single", "dim": 3, "n_min": 0, "variant": -2}]}',
+                '{"entries": [{"mode": "single", "dim": 3, "n_min": 0, "variant": 4294967295}]}'):
+        with pytest.raises(emst.EmstError) as ei:
+            ctx.set_autotune(bad)
+        assert ei.value.name == "EMST_EINVAL" and ctx.get_autotune() == kept
+
+
 def test_only_the_offered_traversal_shapes_are_accepted():
     import paper_2207_00514_amd as emst
     ctx = emst.Context(0)
