@@ -342,6 +342,11 @@ __global__ __launch_bounds__(256) void k_flat_codes(const float* __restrict__ pt
 // a point's quantised coordinate on that axis is its rank scaled to the
 // code width.  Ranks are monotone in the coordinates, so the Z-curve of the
 // ranks is still a spatial order, with resolution where the points are.
+// Points with the same coordinate share the rank of the first of them: ranks of
+// their own would scatter them over the axis in the order of their indices,
+// and an axis that many of them share would be noise in the codes (points of a
+// line in 3D: 1,000,000 took 76 to 82 ms, now 2.2, 3,000,000 466 to 562, now 5.1;
+// 2,000,000 skewed points, some 60 to a coordinate, 5.7 ms either way).
 
 // keys = order-preserving bits of coordinate `axis`, values = point index
 template <int DIM>
@@ -353,14 +358,29 @@ __global__ __launch_bounds__(256) void k_axis_keys(const float* __restrict__ pts
     vals[i] = (uint32_t)i;
 }
 
-// The point at rank r on `axis` gets the quantised coordinate r * 2^bits / n,
-// spread into its Morton position; acc collects the axes.
+// A point of rank r on `axis`, which is the first position of its key among the
+// sorted ones, gets the quantised coordinate r * 2^bits / n, spread into its
+// Morton position; acc collects the axes.
 template <int DIM>
-__global__ __launch_bounds__(256) void k_axis_rank(const uint32_t* __restrict__ order, int64_t n, int axis, int bits,
+__global__ __launch_bounds__(256) void k_axis_rank(const uint64_t* __restrict__ keys,
+                                                   const uint32_t* __restrict__ order, int64_t n, int axis, int bits,
                                                    uint64_t* __restrict__ acc) {
     const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (r >= n) return;
-    const uint64_t q = ((uint64_t)r << bits) / (uint64_t)n;  // r < 2^31, bits <= 32
+    // back in steps of 1, 2, 4 .. while the key is the same, then by halves
+    const uint64_t key = keys[r];
+    int64_t first = r, below = r - 1;
+    for (int64_t step = 1; below >= 0 && keys[below] == key; step *= 2) {
+        first = below;
+        below -= step;
+    }
+    if (below < -1) below = -1;
+    while (first - below > 1) {
+        const int64_t mid = below + (first - below) / 2;
+        if (keys[mid] == key) first = mid;
+        else below = mid;
+    }
+    const uint64_t q = ((uint64_t)first << bits) / (uint64_t)n;  // below 2^31, bits <= 32
     const uint64_t part = (DIM == 3 ? spread3(q) : spread2(q)) << (DIM - 1 - axis);
     const uint32_t i = order[r];
     acc[i] = axis == 0 ? part : (acc[i] | part);
@@ -3260,7 +3280,7 @@ int job_enqueue(emst_ctx* ctx, Job& j, hipStream_t st) {
         for (int axis = 0; axis < DIM; ++axis) {
             k_axis_keys<DIM><<<grid_for(n), 256, 0, st>>>(j.pts, n, axis, b.k0, b.v0);
             HIP_TRY(radix_sort_pairs(st, b.k0, b.v0, b.k1, b.v1, b.hist, n, ash, 4, &in1));
-            k_axis_rank<DIM><<<grid_for(n), 256, 0, st>>>(in1 ? b.v1 : b.v0, n, axis, bits, acc);
+            k_axis_rank<DIM><<<grid_for(n), 256, 0, st>>>(in1 ? b.k1 : b.k0, in1 ? b.v1 : b.v0, n, axis, bits, acc);
         }
         k_codes_from<<<grid_for(n), 256, 0, st>>>(acc, n, b.k0, b.v0);
         int csh[8], cq = 0;

@@ -203,6 +203,37 @@ def test_polled_memory_is_coherent(ctx):
     assert ctx.test_mirror_is_coherent()
 
 
+# dense clouds (codes by rank) with an axis that all points, or many, share
+SHARED_AXES = {"line": (150_000, lambda r, x: np.stack([x, 0.5 * x, 0.0 * x], 1), 0),
+               "plane": (60_000, lambda r, x: np.stack([x, r.random(len(x)), 0.0 * x], 1), 1),
+               "terraces": (60_000, lambda r, x: np.stack([x, r.random(len(x)), np.floor(8 * r.random(len(x)))], 1), 1)}
+
+
+@pytest.mark.parametrize("name", sorted(SHARED_AXES))
+def test_rank_codes_of_points_that_share_a_coordinate(ctx, name):
+    n, make, far = SHARED_AXES[name]
+    rng = np.random.default_rng(17)
+    pts = make(rng, rng.random(n)).astype(np.float32)
+    if far:
+        pts[n // 2] = 2.0 ** 20  # every other point in one cell of the box
+    print(f"case shared axis {name}", flush=True)
+    assert_tree(solve(ctx, pts), oracle.emst(pts, threads=8), name)
+    assert ctx.stats()["rank_codes"] == 1
+    if name == "terraces":
+        return
+    # an axis without information costs a search nothing: in 2D, where codes of
+    # 32 bits an axis hold the line's and the unit square's points apart, as many
+    # boxes are tested up to a factor of 2 (5 times as many where the shared
+    # coordinate's ranks follow the indices)
+    ctx.set_counting(True)
+    ctx.build(torch.from_numpy(pts).cuda())
+    tests = ctx.stats()["child_tests"]
+    ctx.build(torch.from_numpy(np.ascontiguousarray(pts[np.arange(n) != n // 2 if far else slice(None), :2])).cuda())
+    plain = ctx.stats()["child_tests"]
+    ctx.set_counting(False)
+    assert tests <= 2 * plain, (tests, plain)
+
+
 def core_reference(pts, k):
     """The k-th smallest D(i, j) over all j, float32 in the kernels' order."""
     n, out = len(pts), np.empty(len(pts), np.float32)
