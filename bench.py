@@ -198,6 +198,80 @@ def main() -> int:
     return bench_single(args)
 
 
+def traversal_report(workload, dim: int, st: dict, cst: dict, trav_ms: float, launches: int, trav_round):
+    """(rounds, roofline, per-round table) of a single-cloud run: `st` the
+    statistics of a timed step, `cst` those of the counting run, trav_ms and
+    launches summed over the timed steps, trav_round the shortest traversal
+    launch of every round.  `workload` is None for a resized one (no measured
+    counters).  A counting run always builds the tree; where the timed steps
+    did not, its counts are of something else than what was timed, so
+    everything that comes from them is null."""
+    variant, no_tree = int(st["traversal_variant"]), int(st["traversal_variant"]) < 0
+    src = st if no_tree else cst
+    rounds = src["rounds"]
+    avg_launch_ms = trav_ms / max(launches, 1)
+    sec_launch = avg_launch_ms * 1e-3
+    src_hash = traversal_source_hash()
+    roofline = {
+        "bound": None if no_tree else "hbm",
+        "achieved": None,
+        "peak": HBM_PEAK_GBS,
+        "unit": "GB/s",
+        "frac": None,
+        "traffic": None,
+        "traffic_frac": None,
+        "kernel": {0: "k_traverse_lane", -1: "k_flat_search"}.get(variant, "k_traverse_fast"),
+        "variant": variant,
+        "source_hash": src_hash,
+        "avg_launch_ms": round(avg_launch_ms, 4),
+        "launches_per_step": rounds,
+    }
+    if not no_tree:
+        q_round, t_round = cst["queries_round"], cst["records_touched_round"]
+        uniq = [unique_bytes(dim, q, t) for q, t in zip(q_round, t_round)]
+        logi = [logical_bytes(dim, q, ci, li)
+                for q, ci, li in zip(q_round, cst["child_tests_round"], cst["leaf_tests_round"])]
+        uniq_launch = sum(uniq) / max(rounds, 1)
+        logi_launch = sum(logi) / max(rounds, 1)
+        achieved = uniq_launch / sec_launch / 1e9 if avg_launch_ms > 0 else 0.0
+        logical_rate = logi_launch / sec_launch / 1e9 if avg_launch_ms > 0 else 0.0
+        key = (workload, variant, src_hash)
+        meas, lim = MEASURED_TRAFFIC.get(key), MEASURED_LIMITER.get(key)
+        traffic = None if meas is None else int(meas[0] * 1024 * FETCH_FACTOR + meas[1] * 1024 * WRITE_FACTOR)
+        queries = max(sum(q_round), 1)
+        roofline.update({
+            "achieved": round(achieved, 1),
+            "frac": round(achieved / HBM_PEAK_GBS, 4),
+            "traffic": traffic,
+            "traffic_frac": None if traffic is None else round(traffic / sec_launch / 1e9 / HBM_PEAK_GBS, 4),
+            "algorithmic_bytes_per_launch": int(uniq_launch),
+            "algorithmic_bytes": "node records loaded in the launch, each once (64 B, 48 B in 2D), plus "
+                                 "4*dim + 16 B per query",
+            "records_touched_per_launch": int(sum(t_round) / max(rounds, 1)),
+            "logical": {"bytes_per_launch": int(logi_launch), "rate_gbs": round(logical_rate, 1),
+                        "rate_frac": round(logical_rate / HBM_PEAK_GBS, 4),
+                        "cache_served": None if traffic is None else round(1.0 - traffic / logi_launch, 4)},
+            "l2_hit": None if meas is None else meas[2],
+            "traffic_profile": None if meas is None else meas[3],
+            "limiter": lim,
+            "children_examined_per_query_round": round((cst["child_tests"] + cst["leaf_tests"]) / queries, 2),
+            "dist_evals_per_query_round": round(cst["dist_evals"] / queries, 2),
+        })
+    # per Borůvka round: components and queries, with a tree the counting
+    # run's tests per query and node records loaded, and the shortest search
+    # launch of the timed steps (HIP events)
+    table = []
+    for r in range(rounds):
+        q = int(src["queries_round"][r])
+        row = {"round": r, "components": int(src["components"][r]), "queries": q}
+        for name in ("child_tests", "leaf_tests"):
+            row[name + "_per_query"] = None if no_tree else round(cst[name + "_round"][r] / max(q, 1), 2)
+        row["records_loaded"] = None if no_tree else int(cst["records_touched_round"][r])
+        row["traversal_ms_min"] = None if trav_round is None or r >= len(trav_round) else round(trav_round[r], 3)
+        table.append(row)
+    return rounds, roofline, table
+
+
 def bench_single(args) -> int:
     import numpy as np
     import torch
@@ -263,53 +337,10 @@ def bench_single(args) -> int:
     value = n * args.steps / secs / 1e6
     log(f"timed {args.steps} steps: {ms_per_step:.3f} ms/step, {value:.1f} Mpoints/s")
 
-    rounds = cst["rounds"]
-    q_round, t_round = cst["queries_round"], cst["records_touched_round"]
-    uniq = [unique_bytes(dim, q, t) for q, t in zip(q_round, t_round)]
-    logi = [logical_bytes(dim, q, ci, li)
-            for q, ci, li in zip(q_round, cst["child_tests_round"], cst["leaf_tests_round"])]
-    avg_launch_ms = trav_ms / max(launches, 1)
-    sec_launch = avg_launch_ms * 1e-3
-    uniq_launch = sum(uniq) / max(rounds, 1)
-    logi_launch = sum(logi) / max(rounds, 1)
-    achieved = uniq_launch / sec_launch / 1e9 if avg_launch_ms > 0 else 0.0
-    logical_rate = logi_launch / sec_launch / 1e9 if avg_launch_ms > 0 else 0.0
-    variant_ran = int(st["traversal_variant"])
-    if variant_ran < 0:
-        log("the timed steps solved the cloud without a tree; the counts are those of a traversal of its tree")
-    src_hash = traversal_source_hash()
-    key = (args.workload, variant_ran, src_hash)
-    meas = None if args.n is not None else MEASURED_TRAFFIC.get(key)
-    lim = None if args.n is not None else MEASURED_LIMITER.get(key)
-    traffic = None if meas is None else int(meas[0] * 1024 * FETCH_FACTOR + meas[1] * 1024 * WRITE_FACTOR)
-    queries = max(sum(q_round), 1)
-
-    roofline = {
-        "bound": "hbm",
-        "achieved": round(achieved, 1),
-        "peak": HBM_PEAK_GBS,
-        "unit": "GB/s",
-        "frac": round(achieved / HBM_PEAK_GBS, 4),
-        "traffic": traffic,
-        "traffic_frac": None if traffic is None else round(traffic / sec_launch / 1e9 / HBM_PEAK_GBS, 4),
-        "kernel": {0: "k_traverse_lane", -1: "k_flat_search"}.get(variant_ran, "k_traverse_fast"),
-        "variant": variant_ran,
-        "source_hash": src_hash,
-        "avg_launch_ms": round(avg_launch_ms, 4),
-        "launches_per_step": rounds,
-        "algorithmic_bytes_per_launch": int(uniq_launch),
-        "algorithmic_bytes": "node records loaded in the launch, each once (64 B, 48 B in 2D), plus "
-                             "4*dim + 16 B per query",
-        "records_touched_per_launch": int(sum(t_round) / max(rounds, 1)),
-        "logical": {"bytes_per_launch": int(logi_launch), "rate_gbs": round(logical_rate, 1),
-                    "rate_frac": round(logical_rate / HBM_PEAK_GBS, 4),
-                    "cache_served": None if traffic is None else round(1.0 - traffic / logi_launch, 4)},
-        "l2_hit": None if meas is None else meas[2],
-        "traffic_profile": None if meas is None else meas[3],
-        "limiter": lim,
-        "children_examined_per_query_round": round((cst["child_tests"] + cst["leaf_tests"]) / queries, 2),
-        "dist_evals_per_query_round": round(cst["dist_evals"] / queries, 2),
-    }
+    rounds, roofline, round_table = traversal_report(None if args.n is not None else args.workload, dim, st, cst,
+                                                     trav_ms, launches, trav_round)
+    if st["traversal_variant"] < 0:
+        log("the timed steps solved the cloud without a tree; no counts of a traversal are reported")
 
     line = {
         "metric": METRIC,
@@ -330,16 +361,7 @@ def bench_single(args) -> int:
         "rounds": rounds,
         "phases_ms_per_step": {k: round(v / args.steps, 4) for k, v in phases.items()},
         "roofline": roofline,
-        # per Borůvka round: the counting run's components, queries, tests per
-        # query and node records loaded; the shortest traversal launch of the
-        # timed steps (HIP events)
-        "round_table": [
-            {"round": r, "components": int(cst["components"][r]), "queries": int(q_round[r]),
-             "child_tests_per_query": round(cst["child_tests_round"][r] / max(q_round[r], 1), 2),
-             "leaf_tests_per_query": round(cst["leaf_tests_round"][r] / max(q_round[r], 1), 2),
-             "records_loaded": int(t_round[r]),
-             "traversal_ms_min": None if trav_round is None or r >= len(trav_round) else round(trav_round[r], 3)}
-            for r in range(rounds)],
+        "round_table": round_table,
     }
     edges, w, d2 = (t.cpu().numpy() for t in out)
     del ctx, out
