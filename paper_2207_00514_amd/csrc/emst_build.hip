@@ -3578,8 +3578,11 @@ int build_impl(emst_ctx* ctx, const float* pts, int64_t n, int32_t* edges, float
     // shape or for the traversal's counts
     const TuneEntry* e = ctx->tune.pick(0, DIM, n);
     if (n <= kFlatMax && k_pts == 0 && !ctx->counting && ctx->traversal < 0 && ctx->lds_depth == 0 &&
-        (!e || e->variant == kTuneAuto))
-        return flat_impl<DIM>(ctx, pts, n, edges, weights, d2, ws, st);
+        (!e || e->variant == kTuneAuto)) {
+        const int rc = flat_impl<DIM>(ctx, pts, n, edges, weights, d2, ws, st);
+        if (rc) (void)hipStreamSynchronize(st);  // nothing stays queued on the caller's workspace
+        return rc;
+    }
     Job j = make_job(ctx, pts, n, DIM, ws, edges, weights, d2, k_pts, core_out, core_only, ctx->h_ctrl,
                      ctx->profiling && ctx->ev_ok);
     if (int rc = job_run<DIM>(ctx, j, st)) return rc;
