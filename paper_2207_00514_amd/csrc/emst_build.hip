@@ -2233,7 +2233,7 @@ __global__ __launch_bounds__(256) void k_batch_edge_write(const uint4* __restric
 // workspace layout
 
 struct Layout {
-    size_t ctrl, bpart, k0, k1, v0, v1, hist, spts, orig, cand_p, recs, meta, height, node_parent, leaf_parent, up, starts, rlo, rhi, run_part, run_carry, qcnt, qoff, qflag, qlist, labels, ub, compkey, compmax, succ, par, cand_d, cand_j, eud, core_s, spare, total;
+    size_t ctrl, bpart, k0, k1, v0, v1, hist, spts, orig, cand_p, recs, meta, height, node_parent, tile_label, up, starts, rlo, rhi, run_part, run_carry, qcnt, qoff, qflag, qlist, labels, ub, compkey, compmax, succ, par, cand_d, cand_j, eud, core_s, reserve, total;
 };
 
 static size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -2278,9 +2278,11 @@ static Layout make_layout(int64_t n, int dim) {
     L.meta = take(16 * M);
     L.height = take(M);
     L.node_parent = take(4 * M);
-    L.leaf_parent = take(4 * N);
+    const size_t tile_labels = 4 * (((size_t)std::min<int64_t>((int64_t)N, kFlatMax) + kFlatTile - 1) / kFlatTile);
+    L.tile_label = take(tile_labels);
     L.up = take(sizeof(Up) * M);
-    L.starts = take(8 * M);
+    const size_t starts = 4 * ((N + 63) / 64);
+    L.starts = take(starts);
     L.rlo = take(4 * M);
     L.rhi = take(4 * M);
     L.run_part = take(8 * (N / kRunTile + 2));
@@ -2299,7 +2301,10 @@ static Layout make_layout(int64_t n, int dim) {
     L.cand_j = take(4 * N);
     L.eud = take(16 * N);
     L.core_s = take(4 * N);
-    L.spare = take(12 * N);  // (keeps emst_workspace_bytes what it was)
+    // 24 bytes a point less the two arrays above, which no kernel uses: programs
+    // size workspaces and budgets by emst_workspace_bytes, and the largest cloud
+    // of emst_build_noalloc follows from it
+    L.reserve = take(align_up(4 * N) + align_up(8 * M) + align_up(12 * N) - align_up(tile_labels) - align_up(starts));
     L.total = o;
     return L;
 }
@@ -2381,7 +2386,7 @@ struct emst_ctx {
     Ctrl* h_ctrl = nullptr;
     hipEvent_t ev[2 * 64 + 8];
     bool ev_ok = false;
-    hipEvent_t sev[2] = {nullptr, nullptr};  // completion of the control copies of two rounds in flight
+    hipEvent_t sev[2] = {nullptr, nullptr};  // completion of the control copies of two graph replays in flight
     void* h_stage = nullptr;       // pinned host staging for per-cloud tables
     size_t h_stage_bytes = 0;
     // captured round pairs of batches (emst_set_graphs): a few instantiated
@@ -2582,7 +2587,7 @@ struct Bufs {
     Rec<DIM>* recs;
     uint4* meta;
     uint8_t* height;
-    uint32_t *node_parent, *leaf_parent;
+    uint32_t *node_parent, *tile_label;
     Up* up;
     uint32_t* starts;
     uint32_t *rlo, *rhi, *run_part, *run_carry, *labels, *ub;
@@ -2611,7 +2616,7 @@ Bufs<DIM> carve(char* ws, const Layout& L, int64_t n) {
     b.meta = reinterpret_cast<uint4*>(ws + L.meta);
     b.height = reinterpret_cast<uint8_t*>(ws + L.height);
     b.node_parent = reinterpret_cast<uint32_t*>(ws + L.node_parent);
-    b.leaf_parent = reinterpret_cast<uint32_t*>(ws + L.leaf_parent);
+    b.tile_label = reinterpret_cast<uint32_t*>(ws + L.tile_label);
     b.up = reinterpret_cast<Up*>(ws + L.up);
     b.starts = reinterpret_cast<uint32_t*>(ws + L.starts);
     b.rlo = reinterpret_cast<uint32_t*>(ws + L.rlo);
@@ -3174,9 +3179,9 @@ void finish_stats(emst_ctx* ctx, emst_stats& S) {
 }
 
 // One cloud's build as a resumable sequence of phases.  Each phase
-// enqueues its work and a copy of the control block into the job's pinned
-// host mirror; after it has arrived, advance() reads the mirror and
-// picks the next phase.  emst_build, emst_build_mreach and the one-round
+// enqueues its work, whose last kernel or a copy puts the control block into
+// the job's pinned host mirror; after it has arrived, advance() reads the
+// mirror and picks the next phase.  emst_build, emst_build_mreach and the one-round
 // test hook run one job to the end.
 //
 // k_pts = 0: the EMST.  k_pts >= 1: the MST under mutual reachability with
@@ -3248,7 +3253,8 @@ static TraverseArgs<DIM> job_args(const Job& j, const Bufs<DIM>& b) {
     return ta;
 }
 
-// Enqueue the current phase (ending with the control block copy).
+// Enqueue the current phase (ending with the control block on its way to the
+// mirror).
 template <int DIM>
 int job_enqueue(emst_ctx* ctx, Job& j, hipStream_t st) {
     const int64_t n = j.n;
@@ -3342,7 +3348,7 @@ int job_enqueue(emst_ctx* ctx, Job& j, hipStream_t st) {
     return EMST_OK;
 }
 
-// After the stream has drained: read the mirror, choose the next phase.
+// After the mirror has arrived: read it, choose the next phase.
 template <int DIM>
 int job_advance(emst_ctx* ctx, Job& j) {
     const Ctrl* h = j.h;
@@ -3403,12 +3409,12 @@ int job_advance(emst_ctx* ctx, Job& j) {
 
 // The rounds of one job, with the next round queued before the host reads
 // the last one back, so that the device does not idle while the host
-// checks a round: round r's control block goes to mirror r % 2 and an event
-// marks its arrival.  A round queued past the end finds `done` raised and
+// checks a round: the last kernel of round r stores the control block to mirror
+// r % 2 and marks its arrival there.  A round queued past the end finds `done` raised and
 // returns at once, but still costs its launches, so round r + 1 is queued
 // early only while the shrink of the last round predicts that round r
 // leaves at least two components.  Round 0 is already queued (by the fit
-// phase) with its copy going to mirror 0.
+// phase) and reports to mirror 0.
 template <int DIM>
 int job_rounds(emst_ctx* ctx, Job& j, hipStream_t st) {
     Ctrl* mirror[2] = {ctx->h_ctrl, ctx->h_ctrl + 1};
@@ -3502,7 +3508,7 @@ int flat_impl(emst_ctx* ctx, const float* pts, int64_t n, int32_t* edges, float*
     a.inv = b.succ;
     a.box = box;
     a.labels = b.labels;
-    a.tile_label = b.leaf_parent;
+    a.tile_label = b.tile_label;
     a.cand_d = b.cand_d;
     a.cand_p = b.cand_p;
     a.compkey = b.compkey;

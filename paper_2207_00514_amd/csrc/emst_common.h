@@ -80,26 +80,6 @@ __device__ __forceinline__ void unpack<2>(const Rec<2>& r, Child<2>& c0, Child<2
     c1.lo[0] = r.box1.x; c1.lo[1] = r.box1.y; c1.hi[0] = r.box1.z; c1.hi[1] = r.box1.w;
 }
 
-// Write the reference of child `side` of node k.
-__device__ __forceinline__ void set_child_ref(uint4* meta, uint32_t k, int side, uint32_t ref) {
-    reinterpret_cast<uint32_t*>(meta + k)[side] = ref;
-}
-
-// Box and reference of child `side` of node k.
-template <int DIM>
-__device__ __forceinline__ void set_child(Rec<DIM>* recs, uint4* meta, uint32_t k, int side, const float* lo,
-                                          const float* hi, uint32_t ref) {
-    if constexpr (DIM == 3) {
-        float2* f = reinterpret_cast<float2*>(recs + k) + 3 * side;
-        f[0] = make_float2(lo[0], lo[1]);
-        f[1] = make_float2(lo[2], hi[0]);
-        f[2] = make_float2(hi[1], hi[2]);
-    } else {
-        reinterpret_cast<float4*>(recs + k)[side] = make_float4(lo[0], lo[1], hi[0], hi[1]);
-    }
-    set_child_ref(meta, k, side, ref);
-}
-
 // ---------------------------------------------------------------------------
 // Distances.  The float32 squared distance D is evaluated in one fixed
 // order -- d = a0 - b0; s = d*d; then s = s + (ak - bk)^2 for k = 1.. --
@@ -148,13 +128,6 @@ __device__ __forceinline__ uint32_t load_relaxed(const uint32_t* p) {
 }
 __device__ __forceinline__ uint64_t load_relaxed64(const uint64_t* p) {
     return __hip_atomic_load(const_cast<uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Orders the LDS accesses of the workgroup's threads around it.  Unlike
-// __threadfence_block it does not wait for stores to memory, which nothing
-// in the launch reads back.
-__device__ __forceinline__ void lds_fence() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup", "local");
 }
 
 __device__ __forceinline__ int lane_id() { return __lane_id(); }
