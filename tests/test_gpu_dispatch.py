@@ -318,3 +318,73 @@ def test_batch_whose_order_needs_more_than_64_bits(ctx):
     dx, dy = (pairs[:, 0] - pairs[:, 1]).T
     assert np.array_equal(edges, np.tile(np.array([[0, 1]], np.int32), (69_999, 1)))
     assert np.array_equal(got.view(np.uint32), (dx * dx + dy * dy).view(np.uint32))
+
+
+# Tiles of the round kernels: 1, 2, 4 and 8 positions a thread up to 2^19, 2^20,
+# 2^21 points and above, their partials in the sort's histogram below 8; up to
+# 2,048 tiles (2^22 points) their scans are folded into the consumers
+@pytest.mark.parametrize("n", [1 << 19, (1 << 19) + 1, 1 << 20, (1 << 20) + 1, 1 << 21, (1 << 21) + 1, 1 << 22,
+                               (1 << 22) + 1])
+def test_tile_sizes_of_the_round_kernels(n):
+    import paper_2207_00514_amd as emst
+    ctx = emst.Context(0)
+    ctx.set_traversal(13)
+    pts = W.clustered3d(n, seed=33) if n <= 1 << 20 else W.uniform2d(n, seed=34)
+    print(f"case tiles n={n}", flush=True)
+    assert_tree(solve(ctx, pts), oracle.kdboruvka(pts, threads=16), f"n={n}")
+    if n > 3 << 18:
+        assert any(q < n for q in ctx.stats()["queries_round"][2:])  # query lists ran
+
+
+# edges of equal length and equal smaller endpoint, which the order by (D, u)
+# leaves to the in-place order by v: with a tree, by variant and by size
+@pytest.mark.parametrize("dim,span", [(2, 6000), (3, 600)])
+def test_short_runs_of_equal_lengths_with_a_tree(dim, span):
+    import paper_2207_00514_amd as emst
+    ctx = emst.Context(0)
+    ties = 0
+    for n, variant in [(3000, 13)] * 6 + [(20_000, -1)] * 2:
+        rng = np.random.default_rng(500 + ties + n)
+        pts = rng.integers(0, span * (1 if n == 3000 else 3), (n, dim)).astype(np.float32)
+        ctx.set_traversal(variant)
+        print(f"case ties n={n} dim={dim}", flush=True)
+        ref = oracle.emst(pts, threads=8)
+        assert_tree(solve(ctx, pts), ref, f"n={n} dim={dim}")
+        assert ctx.stats()["traversal_variant"] == 13
+        k = np.sort((ref.d2.view(np.uint32).astype(np.uint64) << np.uint64(32)) | ref.edges[:, 0].astype(np.uint64))
+        ties += int((k[1:] == k[:-1]).sum())
+    assert ties > 0
+
+
+def test_every_build_of_several_threads():
+    """Four threads with a context and a stream each, clouds with and without a
+    tree: every build is made, none raises, and edges, lengths and weights are
+    the oracle's."""
+    import threading
+    import paper_2207_00514_amd as emst
+    clouds = [W.clustered3d(16_384, seed=1), W.uniform2d(9_000, seed=2), W.clustered3d(30_000, seed=3),
+              W.small_random(20_001, 2, 4, "dup")]
+    refs = [oracle.emst(p, threads=8) for p in clouds]
+    done, wrong = [], []
+
+    def work(k):
+        try:
+            ctx, st = emst.Context(0), torch.cuda.Stream()
+            with torch.cuda.stream(st):
+                dev = [torch.from_numpy(p).cuda() for p in clouds]
+                for rep in range(12):
+                    c = (k + rep) % len(clouds)
+                    got = ctx.build(dev[c], stream=st)
+                    st.synchronize()
+                    e, w, d2 = (t.cpu().numpy() for t in got)
+                    assert_tree((e, w, d2), refs[c], f"thread {k} build {rep}")
+                    done.append((k, rep))
+        except BaseException as exc:  # (a thread's exception fails no test by itself)
+            wrong.append((k, repr(exc)))
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong and len(done) == 48, (wrong, len(done))
