@@ -2301,10 +2301,14 @@ static Layout make_layout(int64_t n, int dim) {
     L.cand_j = take(4 * N);
     L.eud = take(16 * N);
     L.core_s = take(4 * N);
-    // 24 bytes a point less the two arrays above, which no kernel uses: programs
-    // size workspaces and budgets by emst_workspace_bytes, and the largest cloud
-    // of emst_build_noalloc follows from it
-    L.reserve = take(align_up(4 * N) + align_up(8 * M) + align_up(12 * N) - align_up(tile_labels) - align_up(starts));
+    // Some 24 bytes a point that no kernel uses.  They make a workspace as large,
+    // to the byte, as with records of 64 (48) bytes, labels of 8, and 4 N + 8 M + 4 N
+    // bytes of links, exchange words and core distances by index: programs keep
+    // workspaces and budgets of such sizes, and the largest cloud of
+    // emst_build_noalloc follows from them.
+    const size_t sized = align_up((dim == 3 ? 64 : 48) * M) + 2 * align_up(8 * M) + 2 * align_up(4 * N);
+    L.reserve = take(sized - align_up(M * (dim == 3 ? sizeof(Rec<3>) : sizeof(Rec<2>))) - align_up(16 * M) -
+                     align_up(tile_labels) - align_up(starts));
     L.total = o;
     return L;
 }

@@ -102,6 +102,14 @@ def test_noalloc_limit_matches_the_header():
     assert wb(290_000, 2) <= emst.NOALLOC_WORKSPACE_BYTES < wb(320_000, 2)
 
 
+@pytest.mark.parametrize("n,dim,size", [(2, 3, 1_125_376), (6, 3, 1_125_632), (7, 2, 1_125_632), (1000, 2, 1_337_600),
+                                        (2999, 3, 1_831_680), (277_248, 3, 67_104_512), (302_688, 2, 67_108_096),
+                                        (4_194_305, 2, 917_653_248)])
+def test_workspaces_keep_their_size(n, dim, size):
+    """Programs hold workspaces and solver budgets of these sizes."""
+    assert emst.workspace_bytes(n, dim) == size
+
+
 def test_a_wait_leaves_the_core_to_others():
     """A call that waits for its kernels, on the same core as a thread that
     computes: the computing thread gets nearly all of the core (a wait that
