@@ -55,10 +55,10 @@ TRAFFIC_SOURCES = ("traverse.h", "emst_common.h", "emst_kernels.h")
 FETCH_FACTOR, WRITE_FACTOR = 2.0, 1.0
 MEASURED_TRAFFIC = {
     # (workload, variant, source hash): (FETCH_SIZE KiB, WRITE_SIZE KiB, TCC hit fraction, profile)
-    ("cosmology3d_37m", 13, "e1b7ca87cf972178"):
-        (1225629.0, 291148.0, 0.908, "profiles/k_traverse_fast_cosmology3d_37m.md"),
-    ("clustered3d_2m", 13, "e1b7ca87cf972178"):
-        (77958.0, 18400.9, 0.904, "profiles/k_traverse_fast_clustered3d_2m.md"),
+    ("cosmology3d_37m", 13, "7d69eb3c6a8884eb"):
+        (1225731.0, 291146.0, 0.908, "profiles/k_traverse_fast_cosmology3d_37m.md"),
+    ("clustered3d_2m", 13, "7d69eb3c6a8884eb"):
+        (77896.5, 18401.4, 0.904, "profiles/k_traverse_fast_clustered3d_2m.md"),
 }
 # What bounds the traversal, from counters of the same runs (per launch
 # type): TA busy = busy cycles of the texture addressers / kernel cycles, VALU
@@ -67,24 +67,24 @@ MEASURED_TRAFFIC = {
 # per vector instruction.
 MEASURED_LIMITER = {
     # (workload, variant, source hash): {"full": {...}, "list": {...}, "profile": path}
-    ("cosmology3d_37m", 13, "e1b7ca87cf972178"): {
+    ("cosmology3d_37m", 13, "7d69eb3c6a8884eb"): {
         "bound_by": "texture addresser (gathers of node records), not HBM",
-        "full": {"launches": "rounds 0-1", "ta_busy": 0.942, "valu_busy": 0.639, "lane_utilisation": 0.473,
-                 "salu_per_valu": 0.86, "waves_per_cu": 27.2, "of_waves_per_cu": 32, "l2_hit": 0.939,
+        "full": {"launches": "rounds 0-1", "ta_busy": 0.939, "valu_busy": 0.641, "lane_utilisation": 0.472,
+                 "salu_per_valu": 0.86, "waves_per_cu": 27.1, "of_waves_per_cu": 32, "l2_hit": 0.939,
                  "hbm_frac": 0.095},
-        "list": {"launches": "rounds 2-10", "ta_busy": 0.865, "valu_busy": 0.518, "lane_utilisation": 0.587,
+        "list": {"launches": "rounds 2-10", "ta_busy": 0.864, "valu_busy": 0.517, "lane_utilisation": 0.587,
                  "salu_per_valu": 0.88, "waves_per_cu": 24.9, "of_waves_per_cu": 32, "l2_hit": 0.868,
-                 "hbm_frac": 0.174},
+                 "hbm_frac": 0.175},
         "profile": "profiles/k_traverse_fast_cosmology3d_37m.md",
     },
-    ("clustered3d_2m", 13, "e1b7ca87cf972178"): {
+    ("clustered3d_2m", 13, "7d69eb3c6a8884eb"): {
         "bound_by": "texture addresser (gathers of node records), not HBM",
-        "full": {"launches": "rounds 0-1", "ta_busy": 0.855, "valu_busy": 0.640, "lane_utilisation": 0.437,
-                 "salu_per_valu": 0.86, "waves_per_cu": 24.3, "of_waves_per_cu": 32, "l2_hit": 0.945,
-                 "hbm_frac": 0.088},
-        "list": {"launches": "rounds 2-8", "ta_busy": 0.586, "valu_busy": 0.381, "lane_utilisation": 0.598,
-                 "salu_per_valu": 0.88, "waves_per_cu": 15.9, "of_waves_per_cu": 32, "l2_hit": 0.831,
-                 "hbm_frac": 0.152},
+        "full": {"launches": "rounds 0-1", "ta_busy": 0.855, "valu_busy": 0.641, "lane_utilisation": 0.437,
+                 "salu_per_valu": 0.86, "waves_per_cu": 24.4, "of_waves_per_cu": 32, "l2_hit": 0.945,
+                 "hbm_frac": 0.090},
+        "list": {"launches": "rounds 2-8", "ta_busy": 0.580, "valu_busy": 0.377, "lane_utilisation": 0.598,
+                 "salu_per_valu": 0.88, "waves_per_cu": 15.8, "of_waves_per_cu": 32, "l2_hit": 0.832,
+                 "hbm_frac": 0.155},
         "profile": "profiles/k_traverse_fast_clustered3d_2m.md",
     },
 }

@@ -67,7 +67,7 @@ __device__ __forceinline__ uint64_t flat_key(uint32_t d, uint32_t a, uint32_t b)
 // workgroup's waves in slices: wave w of W compares one key per lane with
 // the keys [w n / W, (w + 1) n / W), which are the same for all lanes and
 // come through scalar loads.  All n^2 comparisons of 10,000 keys take 17 us,
-// a radix sort of them 8 passes of three launches, 100 us.
+// the eight passes of a radix sort of 20,000 keys 87 us.
 template <int W>
 __device__ __forceinline__ uint32_t flat_rank(const uint64_t* __restrict__ keys, int n, uint64_t mine, int w,
                                               uint32_t (*s_cnt)[64]) {
